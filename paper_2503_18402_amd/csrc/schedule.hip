@@ -4,12 +4,15 @@
 //
 // Frequency map: M(i,j) = (1/N) sum_n ||F^n(i,j)||_2 with F^n the
 // unnormalised 2D DFT of view n and the norm taken over the colour channels.
-// It is computed once per scene, in FP64, as a direct DFT: a row pass on the
-// real image (only the non-negative column frequencies: the rest follow by
-// conjugate symmetry) and a column pass per output column, which takes the
-// norm over channels.  O(HW(H + W)) work: about 0.5 ms for a 1600x1064 view.
+// It is computed once per scene, in FP64, by fast Fourier transforms in LDS: a
+// row pass on the real image (two rows per transform, only the non-negative
+// column frequencies: the rest follow by conjugate symmetry) and a column pass
+// over the three channels, which takes the norm over channels.  A 1200x800 view
+// takes 0.05 ms (16 us rows, 30 us columns: rounds of LDS and L2 latency; the
+// 54 MB that it moves would take 10 us), against 1.49 ms for a direct DFT of
+// HW(H + W) terms, which was bound by FP64 arithmetic.
 // Views are added in order, so the map is deterministic.  H and W are at most
-// kDftMax (both passes keep their twiddles and one line of data in LDS).
+// kDftMax (a line, or its Bluestein padding of at most 8192 values, fits in LDS).
 //
 // Schedule: from the map, X(F_r) is the sum of M over the centred crop
 // |k_y| <= H/(2r), |k_x| <= W/(2r) (the spectrum of the ideal downsample by r),
@@ -22,6 +25,7 @@
 // Downsampling: separable anti-aliased linear resampling; output sample i is
 // centred at input coordinate (i + 0.5) * in/out and weighs the inputs with a
 // triangle of half-width max(1, in/out), normalised to sum 1.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -30,100 +34,365 @@
 namespace gsk {
 namespace {
 
-constexpr int kDftThreads = 256;
+// ---- a block-wide FFT in LDS, FP64.  One Stockham stage per factor of the
+// length: radices 8, 4, 2, 3, 5, 7 as register butterflies, a prime of 11 to
+// kMaxPrime as a direct sum of that many terms; the values of a stage are held
+// in registers across the barrier, so one LDS buffer is enough.  A length with
+// a larger prime factor p goes through Bluestein's chirp convolution: two
+// transforms of a 7-smooth length >= 2n - 1 instead of p terms per value.
+constexpr int kMaxStages = 13;   // 2^13 is the longest length
+constexpr int kMaxPrime = 61;
 
-// twiddles e^{-2 pi i k / n} for k < n (cos, sin as double2)
-__global__ __launch_bounds__(256) void k_twiddles(int n, double2* __restrict__ tw) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  double s, c;
-  sincospi(2.0 * double(k) / double(n), &s, &c);
-  tw[k] = make_double2(c, -s);
+struct FftPlan {
+  int n;       // the transform's length
+  int len;     // the length run through the stages: n, or Bluestein's m
+  int stages;
+  int radix[kMaxStages];
+  uint32_t magic_ns[kMaxStages];  // x / ns and x / (len / radix) as multiplications
+  uint32_t magic_m[kMaxStages];
+  uint32_t magic_len;
+  // complex tables: len roots of unity; with Bluestein n chirps and the len
+  // values of the chirp filter's transform, scaled by 1 / len
+  __host__ __device__ bool blue() const { return len != n; }
+  __host__ __device__ size_t table() const { return size_t(len) + (blue() ? size_t(n) + len : 0u); }
+};
+
+// x / d for x d < 2^32 with magic = ceil(2^32 / d) (0 for d = 1)
+__device__ __forceinline__ uint32_t div_magic(uint32_t x, uint32_t magic) {
+  return magic ? __umulhi(x, magic) : x;
 }
 
-// Row pass: one block per (channel, row) of one image; outputs the
-// non-negative column frequencies kx = 0 .. W/2 of that row.
-__global__ __launch_bounds__(kDftThreads) void k_dft_rows(int H, int W, const float* __restrict__ img,
-                                                          const double2* __restrict__ tw,
-                                                          double2* __restrict__ rows) {
-  extern __shared__ double2 s_tw[];  // W twiddles, then the row (W doubles)
-  double* s_row = reinterpret_cast<double*>(s_tw + W);
-  const int y = blockIdx.x, c = blockIdx.y;
-  const float* src = img + (size_t(c) * H + y) * W;
-  for (int x = threadIdx.x; x < W; x += kDftThreads) {
-    s_row[x] = double(src[x]);
-    s_tw[x] = tw[x];
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
+  return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
+}
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) {
+  return make_double2(a.x + b.x, a.y + b.y);
+}
+__device__ __forceinline__ double2 csub(double2 a, double2 b) {
+  return make_double2(a.x - b.x, a.y - b.y);
+}
+__device__ __forceinline__ double2 mul_mi(double2 a) { return make_double2(a.y, -a.x); }  // -i a
+
+template <int R>
+struct OddRoots;  // cos and sin of 2 pi k / R, k = 1 .. (R - 1) / 2
+template <>
+struct OddRoots<3> {
+  static constexpr double c[1] = {-0.5}, s[1] = {0.86602540378443864676};
+};
+template <>
+struct OddRoots<5> {
+  static constexpr double c[2] = {0.30901699437494742410, -0.80901699437494742410};
+  static constexpr double s[2] = {0.95105651629515357212, 0.58778525229247312917};
+};
+template <>
+struct OddRoots<7> {
+  static constexpr double c[3] = {0.62348980185873353053, -0.22252093395631440429,
+                                  -0.90096886790241912624};
+  static constexpr double s[3] = {0.78183148246802980871, 0.97492791218182360702,
+                                  0.43388373911755812048};
+};
+
+// y_k = sum_q v_q e^{-2 pi i q k / R} in place
+template <int R>
+__device__ __forceinline__ void dft_small(double2 (&v)[R]) {
+  if constexpr (R == 2) {
+    const double2 a = v[0], b = v[1];
+    v[0] = cadd(a, b);
+    v[1] = csub(a, b);
+  } else if constexpr (R == 4) {
+    const double2 a = cadd(v[0], v[2]), b = csub(v[0], v[2]);
+    const double2 c = cadd(v[1], v[3]), d = mul_mi(csub(v[1], v[3]));
+    v[0] = cadd(a, c);
+    v[1] = cadd(b, d);
+    v[2] = csub(a, c);
+    v[3] = csub(b, d);
+  } else if constexpr (R == 8) {
+    double2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    dft_small<4>(e);
+    dft_small<4>(o);
+    constexpr double h = 0.70710678118654752440;
+    o[1] = make_double2(h * (o[1].x + o[1].y), h * (o[1].y - o[1].x));
+    o[2] = mul_mi(o[2]);
+    o[3] = make_double2(h * (o[3].y - o[3].x), -h * (o[3].x + o[3].y));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = cadd(e[k], o[k]);
+      v[k + 4] = csub(e[k], o[k]);
+    }
+  } else {  // odd prime: pairs q, R - q share their cosine and sine sums
+    constexpr int H = (R - 1) / 2;
+    double2 p[H], m[H];
+    double2 sum = v[0];
+#pragma unroll
+    for (int q = 1; q <= H; ++q) {
+      p[q - 1] = cadd(v[q], v[R - q]);
+      m[q - 1] = csub(v[q], v[R - q]);
+      sum = cadd(sum, p[q - 1]);
+    }
+    double2 out[R];
+    out[0] = sum;
+#pragma unroll
+    for (int k = 1; k <= H; ++k) {
+      double2 re = v[0], im = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int q = 1; q <= H; ++q) {
+        const int r = (q * k) % R, f = r <= H ? r : R - r;
+        const double c = OddRoots<R>::c[f - 1], s = r <= H ? OddRoots<R>::s[f - 1]
+                                                           : -OddRoots<R>::s[f - 1];
+        re = make_double2(fma(c, p[q - 1].x, re.x), fma(c, p[q - 1].y, re.y));
+        im = make_double2(fma(s, m[q - 1].x, im.x), fma(s, m[q - 1].y, im.y));
+      }
+      const double2 t = mul_mi(im);
+      out[k] = cadd(re, t);
+      out[R - k] = csub(re, t);
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) v[k] = out[k];
+  }
+}
+
+// One Stockham stage of radix R over nseq sequences of P.len values in s
+// (sequence after sequence), ns the product of the radices before it.
+template <int T, int E, int R>
+__device__ __forceinline__ void fft_stage(double2* s, const FftPlan& P, int st, uint32_t ns,
+                                          uint32_t nseq, const double2* __restrict__ tw) {
+  constexpr int B = (E + R - 1) / R;  // butterflies per thread
+  const uint32_t len = uint32_t(P.len), m = len / R, total = m * nseq, tstep = m / ns;
+  double2 v[B][R];
+  uint32_t to[B];
+#pragma unroll
+  for (int u = 0; u < B; ++u) {
+    const uint32_t b = threadIdx.x + uint32_t(u * T);
+    if (b < total) {
+      const uint32_t seq = div_magic(b, P.magic_m[st]), j = b - seq * m;
+      const uint32_t d = div_magic(j, P.magic_ns[st]), k = j - d * ns;
+      const double2* src = s + seq * len + j;
+#pragma unroll
+      for (int q = 0; q < R; ++q) v[u][q] = src[q * m];
+      if (ns > 1u) {
+#pragma unroll
+        for (int q = 1; q < R; ++q) v[u][q] = cmul(v[u][q], tw[uint32_t(q) * k * tstep]);
+      }
+      dft_small<R>(v[u]);
+      to[u] = seq * len + d * ns * R + k;
+    }
   }
   __syncthreads();
-  const int nk = W / 2 + 1;
-  double2* dst = rows + (size_t(c) * H + y) * nk;
-  for (int k = threadIdx.x; k < nk; k += kDftThreads) {
-    double re = 0.0, im = 0.0;
-    int idx = 0;  // (x * k) mod W
-    for (int x = 0; x < W; ++x) {
-      const double2 w = s_tw[idx];
-      re = fma(s_row[x], w.x, re);
-      im = fma(s_row[x], w.y, im);
-      idx += k;
-      if (idx >= W) idx -= W;
+#pragma unroll
+  for (int u = 0; u < B; ++u) {
+    if (threadIdx.x + uint32_t(u * T) < total) {
+#pragma unroll
+      for (int q = 0; q < R; ++q) s[to[u] + uint32_t(q) * ns] = v[u][q];
     }
-    dst[k] = make_double2(re, im);
+  }
+  __syncthreads();
+}
+
+// The same for a prime radix p: one output value at a time, p terms each.
+template <int T, int E>
+__device__ __forceinline__ void fft_stage_prime(double2* s, const FftPlan& P, int st, uint32_t ns,
+                                                uint32_t nseq, const double2* __restrict__ tw) {
+  const uint32_t len = uint32_t(P.len), p = uint32_t(P.radix[st]), m = len / p,
+                 total = len * nseq, tstep = m / ns;
+  double2 v[E];
+  uint32_t to[E];
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const uint32_t o = threadIdx.x + uint32_t(u * T);
+    if (o < total) {
+      const uint32_t seq = div_magic(o, P.magic_len), r = o - seq * len;
+      const uint32_t y = div_magic(r, P.magic_m[st]), j = r - y * m;
+      const uint32_t d = div_magic(j, P.magic_ns[st]), k = j - d * ns;
+      uint32_t step = k * tstep + y * m, at = 0;
+      if (step >= len) step -= len;
+      const double2* src = s + seq * len + j;
+      double2 acc = make_double2(0.0, 0.0);
+      for (uint32_t q = 0; q < p; ++q) {
+        const double2 a = src[q * m], w = tw[at];
+        acc.x = fma(a.x, w.x, fma(-a.y, w.y, acc.x));
+        acc.y = fma(a.x, w.y, fma(a.y, w.x, acc.y));
+        at += step;
+        if (at >= len) at -= len;
+      }
+      v[u] = acc;
+      to[u] = seq * len + d * ns * p + k + y * ns;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < E; ++u)
+    if (threadIdx.x + uint32_t(u * T) < total) s[to[u]] = v[u];
+  __syncthreads();
+}
+
+// The transform of nseq sequences in s (P.len values each, at most E T in
+// all); every thread of the block calls it, with a barrier on either side.
+// Plain lengths: s holds the values, then the spectra.  Bluestein: s holds
+// x_k chirp_k padded with zeros to P.len; afterwards conj(s[k]) chirp_k is the
+// spectrum at k < n.  `convolve` false: the stages alone.
+template <int T, int E>
+__device__ __forceinline__ void fft_block(double2* s, const FftPlan& P, uint32_t nseq,
+                                          const double2* __restrict__ tab, bool convolve) {
+  for (int pass = 0;; ++pass) {
+    uint32_t ns = 1;
+    for (int st = 0; st < P.stages; ++st) {
+      switch (P.radix[st]) {
+        case 2: fft_stage<T, E, 2>(s, P, st, ns, nseq, tab); break;
+        case 3: fft_stage<T, E, 3>(s, P, st, ns, nseq, tab); break;
+        case 4: fft_stage<T, E, 4>(s, P, st, ns, nseq, tab); break;
+        case 5: fft_stage<T, E, 5>(s, P, st, ns, nseq, tab); break;
+        case 7: fft_stage<T, E, 7>(s, P, st, ns, nseq, tab); break;
+        case 8: fft_stage<T, E, 8>(s, P, st, ns, nseq, tab); break;
+        default: fft_stage_prime<T, E>(s, P, st, ns, nseq, tab); break;
+      }
+      ns *= uint32_t(P.radix[st]);
+    }
+    if (!convolve || pass) return;
+    const double2* filter = tab + P.len + P.n;
+    const uint32_t len = uint32_t(P.len);
+    for (uint32_t i = threadIdx.x; i < len * nseq; i += T) {
+      const uint32_t seq = div_magic(i, P.magic_len);
+      const double2 a = cmul(s[i], filter[i - seq * len]);
+      s[i] = make_double2(a.x, -a.y);  // the inverse transform as a conjugated forward one
+    }
+    __syncthreads();
   }
 }
 
-// Column pass: one block per column frequency kx in 0 .. W/2; for each channel
-// the column of row spectra goes through LDS and every thread forms its output
-// rows ky, summing |F_c|^2 over the channels.  Writes M(ky, kx) and, by
-// conjugate symmetry, M(-ky, -kx); the image's norm is added to the running
-// mean (first image: overwrite).
-constexpr int kColOut = 16;  // outputs per thread: H <= kDftThreads * kColOut
+// The tables of the row plan (block 0) and the column plan (block 1): roots
+// e^{-2 pi i k / len}; for Bluestein the chirps e^{-pi i k^2 / n} and the
+// transform of the filter conj(chirp_|k|), |k| < n, scaled by 1 / len.
+constexpr int kTabThreads = 1024;
+__global__ __launch_bounds__(kTabThreads) void k_fft_tables(FftPlan row, FftPlan col,
+                                                            double2* __restrict__ row_tab,
+                                                            double2* __restrict__ col_tab) {
+  extern __shared__ double2 s_fft[];
+  const FftPlan& P = blockIdx.x == 0 ? row : col;
+  double2* tab = blockIdx.x == 0 ? row_tab : col_tab;
+  for (int k = threadIdx.x; k < P.len; k += kTabThreads) {
+    double s, c;
+    sincospi(2.0 * double(k) / double(P.len), &s, &c);
+    tab[k] = make_double2(c, -s);
+  }
+  if (!P.blue()) return;  // block-uniform
+  for (int k = threadIdx.x; k < P.len; k += kTabThreads) s_fft[k] = make_double2(0.0, 0.0);
+  __syncthreads();  // also orders the roots' writes before the block reads them
+  double2* chirp = tab + P.len;
+  for (int k = threadIdx.x; k < P.n; k += kTabThreads) {
+    double s, c;
+    sincospi(double((k * k) % (2 * P.n)) / double(P.n), &s, &c);
+    chirp[k] = make_double2(c, -s);
+    s_fft[k] = make_double2(c, s);
+    if (k > 0) s_fft[P.len - k] = make_double2(c, s);
+  }
+  __syncthreads();
+  fft_block<kTabThreads, 8>(s_fft, P, 1u, tab, false);
+  const double scale = 1.0 / double(P.len);
+  double2* filter = chirp + P.n;
+  for (int k = threadIdx.x; k < P.len; k += kTabThreads)
+    filter[k] = make_double2(s_fft[k].x * scale, s_fft[k].y * scale);
+}
 
-__global__ __launch_bounds__(kDftThreads) void k_dft_cols(int H, int W, const double2* __restrict__ rows,
-                                                          const double2* __restrict__ tw,
-                                                          double inv_n, int first,
-                                                          double* __restrict__ mag) {
-  extern __shared__ double2 s_tw[];  // H twiddles, then the column (H values)
-  double2* s_col = s_tw + H;
-  const int kx = blockIdx.x, nk = W / 2 + 1;
-  for (int y = threadIdx.x; y < H; y += kDftThreads) s_tw[y] = tw[y];
-  double acc[kColOut];
+// Row pass: one block per two rows of a channel, transformed together as the
+// real and imaginary part of one sequence; outputs the non-negative column
+// frequencies kx = 0 .. W/2 of both rows.
+template <int T, int E>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T < 1024 ? 5 : 4))) void k_fft_rows(FftPlan P, int H, int W,
+                                                const float* __restrict__ img,
+                                                const double2* __restrict__ tab,
+                                                double2* __restrict__ rows) {
+  extern __shared__ double2 s_fft[];
+  const int y = 2 * int(blockIdx.x), c = blockIdx.y;
+  const bool two = y + 1 < H;
+  const float* src = img + (size_t(c) * H + y) * W;
+  const double2* chirp = tab + P.len;
+  for (int x = threadIdx.x; x < P.len; x += T) {
+    double2 a = make_double2(0.0, 0.0);
+    if (x < W) {
+      a = make_double2(double(src[x]), two ? double(src[x + W]) : 0.0);
+      if (P.blue()) a = cmul(a, chirp[x]);
+    }
+    s_fft[x] = a;
+  }
+  __syncthreads();
+  fft_block<T, E>(s_fft, P, 1u, tab, P.blue());
+  const int nk = W / 2 + 1;
+  double2* dst = rows + (size_t(c) * H + y) * nk;
+  for (int k = threadIdx.x; k < nk; k += T) {
+    const int j = k == 0 ? 0 : W - k;
+    double2 a = s_fft[k], b = s_fft[j];
+    if (P.blue()) {
+      a = cmul(make_double2(a.x, -a.y), chirp[k]);
+      b = cmul(make_double2(b.x, -b.y), chirp[j]);
+    }
+    dst[k] = make_double2(0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
+    if (two) dst[k + nk] = make_double2(0.5 * (a.y + b.y), 0.5 * (b.x - a.x));
+  }
+}
+
+// Column pass: one block per C column frequencies, CH channels of them at a
+// time, summing |F_c|^2 over the channels (a chirp of modulus 1 changes no
+// norm).  Writes M(ky, kx) and, by conjugate symmetry, M(-ky, -kx); the image's
+// norm is added to the running mean (first image: overwrite).  Blocks are
+// dealt so that an XCD's columns are neighbours: their 16-byte pieces of the
+// row spectra and the map then meet in one L2.
+template <int T, int E, int CH>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_fft_cols(FftPlan P, int H, int W, int C,
+                                                const double2* __restrict__ rows,
+                                                const double2* __restrict__ tab, double inv_n,
+                                                int first, double* __restrict__ mag) {
+  extern __shared__ double2 s_fft[];
+  const int nk = W / 2 + 1, groups = (nk + C - 1) / C;
+  const int per = (groups + kXcds - 1) / kXcds;
+  const int grp = int(blockIdx.x % kXcds) * per + int(blockIdx.x / kXcds);
+  if (int(blockIdx.x / kXcds) >= per || grp >= groups) return;  // block-uniform
+  const int kx0 = grp * C, cols = min(C, nk - kx0);
+  const double2* chirp = tab + P.len;
+  // consecutive threads take the C columns (a power of two) of one row, then the next row
+  const int cc = int(threadIdx.x) & (C - 1), yt = int(threadIdx.x) / C, dy = T / C;
+  const bool in = cc < cols;
+  const int kx = kx0 + cc, mx = (W - kx) % W;
+  const bool mirror = in && mx != kx && mx >= nk;  // (-ky, -kx) is another column
+  double acc[E];
 #pragma unroll
-  for (int j = 0; j < kColOut; ++j) acc[j] = 0.0;
-  for (int c = 0; c < 3; ++c) {
-    __syncthreads();  // the previous channel's column is consumed
-    for (int y = threadIdx.x; y < H; y += kDftThreads)
-      s_col[y] = rows[(size_t(c) * H + y) * nk + kx];
-    __syncthreads();
+  for (int e = 0; e < E; ++e) acc[e] = 0.0;
+  for (int c0 = 0; c0 < 3; c0 += CH) {
+    if (c0 > 0) __syncthreads();  // the previous channel's spectra are consumed
 #pragma unroll
-    for (int j = 0; j < kColOut; ++j) {
-      const int ky = threadIdx.x + j * kDftThreads;
-      if (ky < H) {
-        double re = 0.0, im = 0.0;
-        int idx = 0;  // (y * ky) mod H
-        for (int y = 0; y < H; ++y) {
-          const double2 a = s_col[y], w = s_tw[idx];
-          re = fma(a.x, w.x, fma(-a.y, w.y, re));
-          im = fma(a.x, w.y, fma(a.y, w.x, im));
-          idx += ky;
-          if (idx >= H) idx -= H;
+    for (int ch = 0; ch < CH; ++ch) {
+      const double2* src = rows + size_t(c0 + ch) * H * nk + kx;
+      double2* col = s_fft + (ch * C + cc) * P.len;
+      for (int y = yt; y < P.len; y += dy) {
+        double2 a = make_double2(0.0, 0.0);
+        if (y < H && in) {
+          a = src[size_t(y) * nk];
+          if (P.blue()) a = cmul(a, chirp[y]);
         }
-        acc[j] = fma(re, re, fma(im, im, acc[j]));
+        col[y] = a;
+      }
+    }
+    __syncthreads();
+    fft_block<T, E>(s_fft, P, uint32_t(C * CH), tab, P.blue());
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int ky = yt + e * dy;
+      if (ky < H) {
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+          const double2 f = s_fft[(ch * C + cc) * P.len + ky];
+          acc[e] = fma(f.x, f.x, fma(f.y, f.y, acc[e]));
+        }
       }
     }
   }
 #pragma unroll
-  for (int j = 0; j < kColOut; ++j) {
-    const int ky = threadIdx.x + j * kDftThreads;
-    if (ky < H) {
-      const double v = sqrt(acc[j]) * inv_n;
-      const size_t o = size_t(ky) * W + kx;
+  for (int e = 0; e < E; ++e) {
+    const int ky = yt + e * dy;
+    if (ky < H && in) {
+      const double v = sqrt(acc[e]) * inv_n;
+      const size_t o = size_t(ky) * W + kx, om = size_t(ky ? H - ky : 0) * W + mx;
       mag[o] = first ? v : mag[o] + v;
-      // the mirrored frequency (-ky, -kx), when it is a different column
-      const int mx = (W - kx) % W;
-      if (mx != kx && mx >= nk) {
-        const size_t om = size_t((H - ky) % H) * W + mx;
-        mag[om] = first ? v : mag[om] + v;
-      }
+      if (mirror) mag[om] = first ? v : mag[om] + v;
     }
   }
 }
@@ -164,29 +433,97 @@ __global__ __launch_bounds__(256) void k_downsample(int64_t total, int H, int W,
 
 }  // namespace
 
+namespace {
+
+// appends n's factors to P (false when a prime factor exceeds kMaxPrime)
+bool plan_stages(FftPlan& P, int n) {
+  P.stages = 0;
+  auto add = [&](int r) { P.radix[P.stages++] = r; };
+  int twos = 0;
+  while (n % 2 == 0) n /= 2, ++twos;
+  for (; twos >= 5 || twos == 3; twos -= 3) add(8);  // 2^4 as 4 x 4
+  for (; twos >= 2; twos -= 2) add(4);
+  if (twos) add(2);
+  for (int p = 3; p <= kMaxPrime && n > 1; p += 2)
+    while (n % p == 0) add(p), n /= p;
+  return n == 1;
+}
+
+FftPlan make_plan(int n) {
+  FftPlan P{};
+  P.n = P.len = n;
+  if (!plan_stages(P, n)) {
+    auto smooth = [](int m) {
+      for (int p : {2, 3, 5, 7})
+        while (m % p == 0) m /= p;
+      return m == 1;
+    };
+    P.len = 2 * n - 1;
+    while (!smooth(P.len)) ++P.len;  // at most 8192 for n <= 4096
+    plan_stages(P, P.len);
+  }
+  auto magic = [](uint32_t d) { return d == 1u ? 0u : uint32_t(((uint64_t(1) << 32) + d - 1) / d); };
+  uint32_t ns = 1;
+  for (int k = 0; k < P.stages; ++k) {
+    P.magic_ns[k] = magic(ns);
+    P.magic_m[k] = magic(uint32_t(P.len / P.radix[k]));
+    ns *= uint32_t(P.radix[k]);
+  }
+  P.magic_len = magic(uint32_t(P.len));
+  return P;
+}
+
+}  // namespace
+
 size_t frequency_map_ws_bytes(int H, int W) {
   return align256(size_t(3) * H * (W / 2 + 1) * sizeof(double2)) +
-         align256(size_t(W) * sizeof(double2)) + align256(size_t(H) * sizeof(double2));
+         align256(make_plan(W).table() * sizeof(double2)) +
+         align256(make_plan(H).table() * sizeof(double2));
 }
 
 hipError_t launch_frequency_map(int n_images, int H, int W, const float* images, double* mag,
                                 void* ws, hipStream_t st) {
+  const FftPlan row = make_plan(W), col = make_plan(H);
   char* p = static_cast<char*>(ws);
   double2* rows = reinterpret_cast<double2*>(p);
   p += align256(size_t(3) * H * (W / 2 + 1) * sizeof(double2));
-  double2* tw_w = reinterpret_cast<double2*>(p);
-  p += align256(size_t(W) * sizeof(double2));
-  double2* tw_h = reinterpret_cast<double2*>(p);
-  GS_LAUNCH("k_twiddles", k_twiddles, dim3(unsigned((W + 255) / 256)), dim3(256), 0, st, W, tw_w);
-  GS_LAUNCH("k_twiddles", k_twiddles, dim3(unsigned((H + 255) / 256)), dim3(256), 0, st, H, tw_h);
+  double2* row_tab = reinterpret_cast<double2*>(p);
+  p += align256(row.table() * sizeof(double2));
+  double2* col_tab = reinterpret_cast<double2*>(p);
+  const int tab_lds = std::max(row.blue() ? row.len : 0, col.blue() ? col.len : 0);
+  GS_LAUNCH("k_fft_tables", k_fft_tables, dim3(2), dim3(kTabThreads), tab_lds * sizeof(double2),
+            st, row, col, row_tab, col_tab);
+  // columns per block: up to 4 (64-byte pieces of the row spectra) while the
+  // three channels' columns fit the register budget and 512 blocks remain, two
+  // per CU (four 1200x800 views: 216 us with one column per block, 601 blocks,
+  // against 222 with two); longer columns take one channel after the other
+  int C = 4, CH = 3;
+  while (C > 1 && (col.len * C * CH > 1024 * 5 || (W / 2 + C) / C < 512)) C /= 2;
+  if (col.len * C * CH > 1024 * 5) CH = 1;
+  const int nc = col.len * C * CH, groups = (W / 2 + C) / C;
+  const dim3 rgrid(unsigned((H + 1) / 2), 3u);
+  const dim3 cgrid(unsigned((groups + kXcds - 1) / kXcds * kXcds));
+  const size_t rlds = size_t(row.len) * sizeof(double2), clds = size_t(nc) * sizeof(double2);
   const double inv_n = 1.0 / double(n_images);
+#define GS_FFT_ROWS(T, E)                                                                      \
+  GS_LAUNCH("k_fft_rows", HIP_KERNEL_NAME(k_fft_rows<T, E>), rgrid, dim3(T), rlds, st, row, H, W, img, row_tab, \
+            rows)
+#define GS_FFT_COLS(T, E, CH)                                                                         \
+  GS_LAUNCH("k_fft_cols", HIP_KERNEL_NAME(k_fft_cols<T, E, CH>), cgrid, dim3(T), clds, st, col, H, W, C, rows,         \
+            col_tab, inv_n, k == 0 ? 1 : 0, mag)
   for (int k = 0; k < n_images; ++k) {
     const float* img = images + size_t(k) * 3 * H * W;
-    GS_LAUNCH("k_dft_rows", k_dft_rows, dim3(unsigned(H), 3u), dim3(kDftThreads),
-              size_t(W) * (sizeof(double2) + sizeof(double)), st, H, W, img, tw_w, rows);
-    GS_LAUNCH("k_dft_cols", k_dft_cols, dim3(unsigned(W / 2 + 1)), dim3(kDftThreads),
-              size_t(H) * 2 * sizeof(double2), st, H, W, rows, tw_h, inv_n, k == 0 ? 1 : 0, mag);
+    if (row.len <= 64 * 5) GS_FFT_ROWS(64, 5);
+    else if (row.len <= 256 * 5) GS_FFT_ROWS(256, 5);
+    else if (row.len <= 512 * 5) GS_FFT_ROWS(512, 5);
+    else GS_FFT_ROWS(1024, 8);
+    if (CH == 3 && nc <= 256 * 5) GS_FFT_COLS(256, 5, 3);
+    else if (CH == 3 && nc <= 512 * 5) GS_FFT_COLS(512, 5, 3);
+    else if (CH == 3) GS_FFT_COLS(1024, 5, 3);
+    else GS_FFT_COLS(1024, 8, 1);
   }
+#undef GS_FFT_ROWS
+#undef GS_FFT_COLS
   return hipGetLastError();
 }
 
