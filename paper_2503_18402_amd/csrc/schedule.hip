@@ -397,10 +397,169 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_f
   }
 }
 
-// Anti-aliased downsampling of [n][C][H][W] to [n][C][h][w], one thread per
-// output value, both axes' triangle weights formed on the fly.  Coordinates,
-// weights and sums are FP64: in FP32 the tap centre (i + 0.5) H / h carries an
-// error of 1e-4 px near H = 1000, which moves non-integer-factor weights.
+// Anti-aliased downsampling of [n][C][H][W] to [n][C][h][w].  Output sample i
+// weighs the inputs of its window with a triangle around (i + 0.5) in / out.
+// Coordinates, weights and sums are FP64: in FP32 the tap centre
+// (i + 0.5) H / h carries an error of 1e-4 px near H = 1000, which moves
+// non-integer-factor weights.
+
+// Downsampling by factors of 1 or more on both axes.  A block streams down a
+// strip of input rows for up to kDsRows output rows: with its centres at least
+// one input apart, an input row y weighs on two output rows only, the last one
+// centred at or before it and the next, so every thread keeps two running sums
+// per input column and each input is loaded once (plus one window per strip).
+// When an output row is complete its column sums go through LDS and the threads
+// sum their output columns' windows.  Row weights sit in LDS, formed once per
+// block; a thread holds four input columns (one 16-byte load per row when the
+// rows are 16-byte aligned) and the next kDsBatch rows are in flight while the
+// current ones are summed.  64 views of 1200x800 to 300x200: 231 us, 3.4 TB/s of
+// the 783 MB in and out, against 882 us for one thread per output, which loads
+// each input for the 4 outputs around it and forms every weight again.
+constexpr int kDsRows = 8;       // output rows per block
+constexpr int kDsTable = 256;    // input rows a block may walk
+constexpr int kDsBatch = 4;
+constexpr int kDsThreads = 512;  // at most; 4 input columns per thread
+
+template <bool VEC>
+__global__ __launch_bounds__(kDsThreads) void k_downsample_strip(
+    int H, int W, int h, int w, int rows_out, int tile_w, int tiles_x, int groups_y,
+    const float* __restrict__ src, float* __restrict__ dst) {
+  extern __shared__ double s_col[];  // two buffers of 4 x blockDim.x column sums
+  __shared__ double2 s_wy[kDsTable];
+  __shared__ int s_low[kDsTable];
+  __shared__ double s_ry[kDsRows];
+  const int T = blockDim.x, tid = threadIdx.x;
+  const unsigned tx = blockIdx.x % unsigned(tiles_x), r = blockIdx.x / unsigned(tiles_x);
+  const int64_t plane = r / unsigned(groups_y);
+  const int i0 = int(r % unsigned(groups_y)) * rows_out, i1 = min(h, i0 + rows_out);
+  const int j0 = int(tx) * tile_w, j1 = min(w, j0 + tile_w);
+  const double sy = double(H) / double(h), sx = double(W) / double(w);
+  const double iy = 1.0 / sy, ix = 1.0 / sx;
+  auto centre = [](int i, double s) { return (double(i) + 0.5) * s; };
+  // inputs with |(p + 0.5) - c| < s lie in (c - s - 0.5, c + s - 0.5)
+  auto first = [](double c, double s) { return max(0, int(floor(c - s - 0.5))); };
+  auto last = [](double c, double s, int n) { return min(n - 1, int(ceil(c + s - 0.5))); };
+  // exactly zero from one window's half-width on, whatever inv = 1 / half rounds to
+  auto tri = [](double d, double half, double inv) {
+    return fabs(d) < half ? fma(-fabs(d), inv, 1.0) : 0.0;
+  };
+  auto weight = [&](int p, double c, double half, double inv) {
+    return tri(double(p) + 0.5 - c, half, inv);
+  };
+  int y0 = first(centre(i0, sy), sy), y1 = last(centre(i1 - 1, sy), sy, H);
+  // rows of weight zero at the strip's ends are left out (0 x Inf is not 0)
+  while (y0 < y1 && weight(y0, centre(i0, sy), sy, iy) == 0.0) ++y0;
+  while (y0 < y1 && weight(y1, centre(i1 - 1, sy), sy, iy) == 0.0) --y1;
+  const int ny = y1 - y0 + 1;  // at most kDsTable (the host's rows_out)
+  for (int k = tid; k < ny; k += T) {
+    const int y = y0 + k, lo = int(floor((double(y) + 0.5) * iy - 0.5));
+    s_low[k] = lo;
+    s_wy[k] = make_double2(weight(y, centre(lo, sy), sy, iy),
+                           weight(y, centre(lo + 1, sy), sy, iy));
+  }
+  if (tid < i1 - i0) {
+    const double c = centre(i0 + tid, sy);
+    double sum = 0.0;
+    for (int y = first(c, sy); y <= last(c, sy, H); ++y) sum += weight(y, c, sy, iy);
+    s_ry[tid] = 1.0 / sum;
+  }
+  // input columns [x0, x0 + 4 T), the thread's: x0 + 4 tid + u, or x0 + tid + u T
+  const int xa = first(centre(j0, sx), sx), x0 = VEC ? xa & ~3 : xa;
+  const int span = last(centre(j1 - 1, sx), sx, W) - x0 + 1;  // at most 4 T (the host's tile_w)
+  const float* s = src + plane * int64_t(H) * W;
+  int at[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) at[u] = VEC ? 4 * tid + u : tid + u * T;
+  const bool any = at[0] < span;
+  auto load = [&](int k, float (&v)[4]) {
+    const float* row = s + int64_t(y0 + min(k, ny - 1)) * W + x0;
+    if (VEC) {
+      const float4 q = *reinterpret_cast<const float4*>(row + (any ? at[0] : 0));
+      v[0] = q.x, v[1] = q.y, v[2] = q.z, v[3] = q.w;
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = row[at[u] < span ? at[u] : 0];
+    }
+  };
+  // the thread's output columns j0 + tid + u T: window, centre, 1 / weight sum
+  double cx[4], rx[4];
+  int xs[4], xn[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int j = j0 + tid + u * T;
+    xs[u] = xn[u] = 0;
+    cx[u] = rx[u] = 0.0;
+    if (j < j1) {
+      const double c = centre(j, sx);
+      const int a = first(c, sx), b = last(c, sx, W);
+      double sum = 0.0;
+      for (int x = a; x <= b; ++x) sum += weight(x, c, sx, ix);
+      rx[u] = 1.0 / sum;
+      xs[u] = a - x0;
+      xn[u] = b - a + 1;
+      cx[u] = double(a) + 0.5 - c;  // the window's first offset from the centre
+    }
+  }
+  double acc0[4] = {0.0, 0.0, 0.0, 0.0}, acc1[4] = {0.0, 0.0, 0.0, 0.0};
+  float cur[kDsBatch][4], nxt[kDsBatch][4];
+#pragma unroll
+  for (int b = 0; b < kDsBatch; ++b) load(b, cur[b]);
+  __syncthreads();
+  int i_cur = __builtin_amdgcn_readfirstlane(s_low[0]);
+  auto emit = [&]() {  // output row i_cur is complete in acc0
+    if (i_cur >= i0 && i_cur < i1) {
+      double* buf = s_col + (i_cur & 1) * 4 * T;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) buf[at[u]] = acc0[u];
+      __syncthreads();  // the other buffer is rewritten only after the next barrier
+      const double ry = s_ry[i_cur - i0];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = j0 + tid + u * T;
+        if (j < j1) {
+          double row = 0.0, d = cx[u];
+          const double* q = buf + xs[u];
+          for (int k = 0; k < xn[u]; ++k, d += 1.0)
+            row = fma(tri(d, sx, ix), q[k], row);
+          dst[(plane * h + i_cur) * int64_t(w) + j] = float(row * (rx[u] * ry));
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc0[u] = acc1[u], acc1[u] = 0.0;
+    ++i_cur;
+  };
+  for (int k0 = 0; k0 < ny; k0 += kDsBatch) {
+#pragma unroll
+    for (int b = 0; b < kDsBatch; ++b) load(k0 + kDsBatch + b, nxt[b]);
+#pragma unroll
+    for (int b = 0; b < kDsBatch; ++b) {
+      const int k = k0 + b;
+      if (k < ny) {
+        const int lo = __builtin_amdgcn_readfirstlane(s_low[k]);
+        while (i_cur < lo) emit();
+        const double2 wy = s_wy[k];
+        // block-uniform: a row of weight zero is left out (0 x Inf is not 0)
+        if (wy.x != 0.0) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc0[u] = fma(wy.x, double(cur[b][u]), acc0[u]);
+        }
+        if (wy.y != 0.0) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc1[u] = fma(wy.y, double(cur[b][u]), acc1[u]);
+        }
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < kDsBatch; ++b)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cur[b][u] = nxt[b][u];
+  }
+  while (i_cur < i1) emit();
+}
+
+// Enlarging on an axis (two or three taps per output), or windows too long for
+// the strips' tables (factors above about 100): one thread per output.
 __global__ __launch_bounds__(256) void k_downsample(int64_t total, int H, int W, int h, int w,
                                                     const float* __restrict__ src,
                                                     float* __restrict__ dst) {
@@ -531,6 +690,33 @@ hipError_t launch_downsample(int n_planes, int H, int W, int h, int w, const flo
                              hipStream_t st) {
   const int64_t total = int64_t(n_planes) * h * w;
   if (total == 0) return hipSuccess;
+  const double sx = double(W) / double(w), sy = double(H) / double(h);
+  if (sx >= 1.0 && sy >= 1.0) {
+    // rows per strip: (rows + 1) sy + 3 input rows at most; columns per block:
+    // (tile_w + 1) sx + 6 input columns at most, four per thread
+    const int rows_out = std::min(kDsRows, int((kDsTable - 3) / sy) - 1);
+    const int most = int((4 * kDsThreads - 6) / sx) - 1;
+    if (rows_out >= 1 && most >= 1) {
+      const int tiles_x = (w + most - 1) / most, tile_w = (w + tiles_x - 1) / tiles_x;
+      const int groups_y = (h + rows_out - 1) / rows_out;
+      const int64_t blocks = int64_t(n_planes) * groups_y * tiles_x;
+      const int span = std::min(W + 3, int((tile_w + 1) * sx) + 7);
+      const int T = std::min(kDsThreads, ((span + 3) / 4 + 63) / 64 * 64);
+      const bool vec = W % 4 == 0 && (reinterpret_cast<uintptr_t>(src) & 15u) == 0;
+      const size_t lds = size_t(8) * T * sizeof(double);
+      if (blocks < (int64_t(1) << 31)) {
+        if (vec)
+          GS_LAUNCH("k_downsample_strip", k_downsample_strip<true>, dim3(unsigned(blocks)),
+                    dim3(unsigned(T)), lds, st, H, W, h, w, rows_out, tile_w, tiles_x, groups_y,
+                    src, dst);
+        else
+          GS_LAUNCH("k_downsample_strip", k_downsample_strip<false>, dim3(unsigned(blocks)),
+                    dim3(unsigned(T)), lds, st, H, W, h, w, rows_out, tile_w, tiles_x, groups_y,
+                    src, dst);
+        return hipGetLastError();
+      }
+    }
+  }
   GS_LAUNCH("k_downsample", k_downsample, dim3(unsigned((total + 255) / 256)), dim3(256), 0, st,
             total, H, W, h, w, src, dst);
   return hipGetLastError();
