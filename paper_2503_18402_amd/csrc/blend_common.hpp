@@ -35,28 +35,56 @@ __device__ __forceinline__ bool box_overlaps(uint32_t lo, uint32_t hi, int x0, i
   return box_x(lo) <= x1 && box_x(hi) >= x0 && box_y(lo) <= y1 && box_y(hi) >= y0;
 }
 
-// alpha of a record at pixel centre (px, py): the record holds the base-2
-// conic (A, B, C) and lo = log2 of the opacity, so o G2D = 2^(p2 + lo) with
-// p2 = A dx^2 + B dx dy + C dy^2.  The pixel takes the Gaussian iff `ok`:
-// p2 <= 0 and o G2D >= 1/255, decided on the exponent, so callers that branch
-// on `ok` before using `a` evaluate the exponential only where it is used.
+// A record at pixel centre (px, py): it holds the base-2 conic (A, B, C) and
+// lo = log2 of the opacity, so o G2D = 2^q with q = p2 + lo and
+// p2 = A dx^2 + B dx dy + C dy^2.  The pixel takes the Gaussian iff p2 <= 0
+// and o G2D >= 1/255, both decided on the exponent, so the exponential is
+// evaluated only where it is used.
+struct Exponent {
+  float dx, dy, p2, q;
+};
+__device__ __forceinline__ Exponent exponent_at(const float4 r0, const float C, const float lo,
+                                                const float px, const float py) {
+  Exponent e;
+  e.dx = px - r0.x;
+  e.dy = py - r0.y;
+  const float t0 = r0.w * e.dy;
+  const float t1 = fmaf(r0.z, e.dx, t0);
+  const float t2 = C * e.dy;
+  const float t3 = t2 * e.dy;
+  e.p2 = fmaf(e.dx, t1, t3);
+  e.q = e.p2 + lo;
+  return e;
+}
+
+// Whether a record is plain: its alpha stays below the clamp at every pixel
+// (alpha <= o: log2 o below log2 0.99 by more than the exponential's rounding)
+// and its conic is definite by more than the rounding of p2, so that p2 <= 0
+// everywhere: |p2| is at least half the margin times |A| dx^2 + |C| dy^2, whose
+// rounding is 1e-6 of it.  Plain records skip the clamp and the sign test, two to
+// four of the instructions that take 4.4 cycles per SIMD here (compares,
+// selects, minima; adds and multiplies take 2.6).  Where a chunk of a list holds
+// only plain ones, nearly always, its walk is compiled without them: 1M Gaussians
+// at 1600x1064 forward 188 to 180 us, backward 387 to 363.
+__device__ __forceinline__ bool plain_record(const float4 r0, const float C, const float lo) {
+  const float d = 4.0f * r0.z * C;
+  return (lo < kLog2AlphaMax - 1.0e-4f) & (r0.z < 0.0f) & (C < 0.0f) &
+         (d - r0.w * r0.w > 1.0e-4f * d);
+}
+
+// The same with the alpha where the pixel takes the Gaussian (`ok`).
 struct Alpha {
   float dx, dy, raw, a;
   bool ok;
 };
 __device__ __forceinline__ Alpha alpha_at(const float4 r0, const float C, const float lo,
                                           const float px, const float py) {
+  const Exponent e = exponent_at(r0, C, lo, px, py);
   Alpha r;
-  r.dx = px - r0.x;
-  r.dy = py - r0.y;
-  const float t0 = r0.w * r.dy;
-  const float t1 = fmaf(r0.z, r.dx, t0);
-  const float t2 = C * r.dy;
-  const float t3 = t2 * r.dy;
-  const float p2 = fmaf(r.dx, t1, t3);
-  const float q = p2 + lo;
-  r.ok = (p2 <= 0.0f) & (q >= kLog2AlphaMin);
-  r.raw = __builtin_amdgcn_exp2f(q);
+  r.dx = e.dx;
+  r.dy = e.dy;
+  r.ok = (e.p2 <= 0.0f) & (e.q >= kLog2AlphaMin);
+  r.raw = __builtin_amdgcn_exp2f(e.q);
   r.a = fminf(kAlphaMax, r.raw);
   return r;
 }

@@ -18,6 +18,7 @@ namespace gsk {
 constexpr float kAlphaMin = 1.0f / 255.0f;  // skip a Gaussian below this alpha
 constexpr float kLog2AlphaMin = -7.99435343685885793771f;  // log2(1/255)
 constexpr float kAlphaMax = 0.99f;          // alpha clamp
+constexpr float kLog2AlphaMax = -0.01449956969511509f;   // log2(0.99)
 constexpr float kTMin = 1.0e-4f;            // stop a pixel before T drops below this
 constexpr float kDilation = 0.3f;           // screen-space low-pass added to Sigma'
 constexpr float kMip2d = 0.1f;              // the 2D mip filter's variance (Mip-Splatting)
