@@ -65,7 +65,7 @@ typedef struct {
 } gs_camera;
 
 /* Raster configuration.  tile in {8, 16, 32} pixels; lds_batch in
- * {128, 256, 512} Gaussians staged in LDS per step of the blend kernels;
+ * {128, 256, 512} Gaussians staged in LDS per step of the forward blend;
  * bg is the background colour added as T_final * bg.  Binning is
  * result-neutral: the image does not depend on lds_batch, and across tile
  * sizes, or between a launch of fewer than 2048 tiles (which splits lists

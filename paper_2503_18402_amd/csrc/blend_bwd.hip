@@ -1,12 +1,12 @@
 // Backward of Eq. 1 and the chain rule to the Gaussian parameters.
 //
-// k_blend_bwd: one workgroup per tile replays the tile's list back to front
-// in LDS-staged batches.  Each pixel starts at its own last contributor with
+// k_blend_bwd: one wave per tile replays the tile's list back to front
+// in LDS-staged chunks.  Each pixel starts at its own last contributor with
 // T = final_T and recovers T_i = T_{i+1} / (1 - alpha_i); the colour behind a
 // Gaussian is carried as its dot product with dL/dC.  Per (tile, Gaussian) nine
 // 2D terms (the two offset sums sum dL/dpower * (dx, dy), whose product with
 // the conic is the mean2D gradient, then conic a/b/c, opacity, rgb) are summed
-// over the tile's pixels in a fixed order (wave butterfly, then waves in order)
+// over the tile's pixels in a fixed order
 // and written to that pair's own slot: the pair slots of a Gaussian are
 // contiguous (ordered by Gaussian index, then by tile inside its footprint),
 // so no float atomics are needed and gradients are bit-reproducible.
@@ -15,6 +15,8 @@
 // 2D gradients through the EWA projection, the covariance, the quaternion,
 // the sigmoid and the SH colour back to the parameters, accumulating over
 // views in registers before one read-modify-write of the outputs.
+#include <type_traits>
+
 #include "blend_common.hpp"
 
 namespace gsk {
@@ -220,10 +222,175 @@ __device__ __forceinline__ void bwd_step(BwdPix<TILE>& P, const BwdStage& S, int
 
 
 
-// One 64-lane wave per tile walks the list back to front in LDS-staged batches.
-// With `skip_long`, tiles whose list is longer than their view's threshold are
-// left to k_blend_bwd_long.
-template <int TILE, int BATCH>
+// ---- sums over the wave's pixels.  Nine values per list entry have to be added
+// over 64 lanes, in a fixed order.  Lane swaps cost 8 cycles per SIMD here and
+// DPP adds 4.6 (a plain add 2.6), so only the first two halvings run in
+// registers: DPP adds with bank masks put two values' sums into one register
+// (lanes l and l ^ 8 of a row, then the mirrored half rows), 14 instructions for
+// all nine, which leaves four partial sums per 16-lane row and value.  Those go
+// to LDS, written and not waited for; after kSumEnts entries lane 16 e + c adds
+// the 16 partial sums of entry e's value c and writes it to the pair's slot: one
+// store for kSumEnts entries.
+constexpr int kSumEnts = 4;
+constexpr int kPartStride = 20;  // 16 partial sums, padded against bank conflicts
+constexpr int kPartEnt = kG * kPartStride;
+
+// v0, v4, v8: per row of 16 lanes, four partial sums per value; bank b (four
+// lanes) of v0 holds value kBank[b], of v4 value kBank[b] + 4, every bank of v8
+// value 8.  (A DPP read of a register needs two instructions after its write.)
+__device__ __forceinline__ void row_sums9(float (&v)[kG]) {
+#define GS_DPP(d, s, ctrl, bank) \
+  "v_add_f32_dpp %" #d ", %" #s ", %" #s " " ctrl " row_mask:0xf bank_mask:" bank "\n\t"
+  asm("s_nop 1\n\t"
+      GS_DPP(0, 0, "row_ror:8", "0x3") GS_DPP(2, 2, "row_ror:8", "0x3")
+      GS_DPP(4, 4, "row_ror:8", "0x3") GS_DPP(6, 6, "row_ror:8", "0x3")
+      GS_DPP(8, 8, "row_ror:8", "0xf")
+      GS_DPP(0, 1, "row_ror:8", "0xc") GS_DPP(2, 3, "row_ror:8", "0xc")
+      GS_DPP(4, 5, "row_ror:8", "0xc") GS_DPP(6, 7, "row_ror:8", "0xc")
+      GS_DPP(0, 0, "row_half_mirror", "0x5") GS_DPP(4, 4, "row_half_mirror", "0x5")
+      GS_DPP(8, 8, "row_half_mirror", "0xf")
+      GS_DPP(0, 2, "row_half_mirror", "0xa") GS_DPP(4, 6, "row_half_mirror", "0xa")
+      : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
+        "+v"(v[7]), "+v"(v[8]));
+#undef GS_DPP
+}
+
+// scale of value c in the pair's slot: the conic's natural-unit gradients from
+// the base-2 sums; the offset sums (0, 1), opacity and colour as they are
+__device__ __forceinline__ float slot_scale(int c) {
+  return (c == 2 || c == 4) ? -0.5f : (c == 3 ? -1.0f : 1.0f);
+}
+
+// One wave's sums on their way to the pair slots.  (What the flush needs beside
+// the lane's places is formed there: registers are what holds the waves per SIMD.)
+struct WaveSum {
+  float* part;           // [kSumEnts][kPartEnt] floats of LDS, this wave's
+  uint32_t* slots;       // [kSumEnts] pair slots
+  float* pair_grad;
+  uint32_t cap;
+  uint32_t put, put8;    // this lane's places for v0 (v4 follows) and v8
+  int cnt;               // entries waiting
+
+  __device__ __forceinline__ WaveSum(float* part_, uint32_t* slots_, int lane, float* pair_grad_,
+                                     int64_t cap_)
+      : part(part_), slots(slots_), pair_grad(pair_grad_), cnt(0) {
+    const int row = lane >> 4, bank = (lane >> 2) & 3, i = lane & 3;
+    const int c0 = ((bank & 1) << 1) | (bank >> 1);  // 0, 2, 1, 3
+    put = uint32_t(c0 * kPartStride + 4 * row + i);
+    // every bank holds value 8's four sums, the odd ones mirrored
+    put8 = uint32_t(8 * kPartStride + 4 * row + ((bank & 1) ? 3 - i : i));
+    cap = uint32_t(cap_ < 0xffffffffll ? cap_ : 0xffffffffll);
+  }
+  __device__ __forceinline__ void flush() {
+    __builtin_amdgcn_wave_barrier();
+    const int lane = threadIdx.x & 63, e = lane >> 4, c = lane & 15;
+    if (e < cnt && c < kG) {
+      const float4* q = reinterpret_cast<const float4*>(part + (e * kG + c) * kPartStride);
+      const float4 a = q[0], b = q[1], d = q[2], f = q[3];
+      const float s = (((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w))) +
+                      (((d.x + d.y) + (d.z + d.w)) + ((f.x + f.y) + (f.z + f.w)));
+      const uint32_t idx = slots[e];
+      if (idx < cap) pair_grad[size_t(idx) * kG + c] = slot_scale(c) * s;
+    }
+    __builtin_amdgcn_wave_barrier();
+    cnt = 0;
+  }
+  __device__ __forceinline__ void add(float (&acc)[kG], uint32_t slot) {
+    row_sums9(acc);
+    float* p = part + cnt * kPartEnt;
+    p[put] = acc[0];
+    p[put + 4 * kPartStride] = acc[4];
+    p[put8] = acc[8];
+    slots[cnt] = slot;
+    if (++cnt == kSumEnts) flush();
+  }
+};
+
+// a list entry staged in LDS: the record in the tile's frame
+struct BwdRec {
+  float4 r0;       // mean, A, B
+  float4 r1;       // C, log2 opacity, r, g
+  float b;
+  uint32_t mask;   // bit q: the box touches group q
+  uint32_t slot;   // the pair's gradient slot
+  uint32_t pad;
+};
+
+// The backward step of an entry at list position pos (1-based) for every pixel
+// of the wave whose group is in m: recover T_i and accumulate the nine 2D
+// gradients under the mask of the pixels that took it.  Returns whether any did
+// (wave-uniform).  PLAIN: the entry is a plain_record.
+template <int TILE, bool PLAIN>
+__device__ __forceinline__ bool bwd_entry(BwdPix<TILE>& P, const BwdRec& e, uint32_t m,
+                                          uint32_t pos, float px0, float py0, float (&acc)[kG]) {
+  constexpr int GX = TileShape<TILE>::kGroupsX, Q = TileShape<TILE>::kGroups;
+  const float4 r0 = e.r0, r1 = e.r1;
+  const float cb = e.b;
+#pragma unroll
+  for (int c = 0; c < kG; ++c) acc[c] = 0.0f;
+  uint64_t hit = 0ull;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if ((m >> q) & 1u) {
+      const Exponent x = exponent_at(r0, r1.x, r1.y, px0 + float((q % GX) * 8),
+                                     py0 + float((q / GX) * 8));
+      // each compare's lane mask on its own: ANDed on the scalar unit
+      const bool ok0 = PLAIN || x.p2 <= 0.0f, ok1 = x.q >= kLog2AlphaMin, ok2 = pos <= P.last[q];
+      hit |= (PLAIN ? ~0ull : __ballot(ok0)) & __ballot(ok1) & __ballot(ok2);
+      if (__builtin_expect(ok0 & ok1 & ok2, 1)) {
+        const float raw = __builtin_amdgcn_exp2f(x.q);
+        const float a = PLAIN ? raw : fminf(kAlphaMax, raw);
+        const float inv = __builtin_amdgcn_rcpf(1.0f - a);
+        const float Ti = P.T[q] * inv;
+        const float wgt = a * Ti;
+        const float cg = fmaf(r1.z, P.g0[q], fmaf(r1.w, P.g1[q], cb * P.g2[q]));
+        // dL/dalpha = (T cg - SdL) / (1 - a); the 0.99 clamp passes no gradient
+        float dLda = fmaf(P.T[q], cg, -P.SdL[q]) * inv;
+        if (!PLAIN) dLda = raw <= kAlphaMax ? dLda : 0.0f;
+        P.SdL[q] = fmaf(wgt, cg, P.SdL[q]);
+        P.T[q] = Ti;
+        acc[6] = fmaf(wgt, P.g0[q], acc[6]);
+        acc[7] = fmaf(wgt, P.g1[q], acc[7]);
+        acc[8] = fmaf(wgt, P.g2[q], acc[8]);
+        const float dpow = dLda * raw;
+        acc[5] += dpow;  // dL/do times o: the chain rule divides by the opacity
+        const float dpx = dpow * x.dx, dpy = dpow * x.dy;
+        acc[2] = fmaf(dpx, x.dx, acc[2]);
+        acc[3] = fmaf(dpx, x.dy, acc[3]);
+        acc[4] = fmaf(dpy, x.dy, acc[4]);
+        // the offsets weighted by dpow; the mean gradient is these two sums
+        // times the Gaussian's conic, applied once in the chain rule
+        acc[0] += dpx;
+        acc[1] += dpy;
+      }
+    }
+  }
+  return hit != 0ull;
+}
+
+// the groups of mask whose pixels may have blended the entry at list position pos
+template <int TILE>
+__device__ __forceinline__ uint32_t live_groups(const BwdPix<TILE>& P, uint32_t mask, uint32_t pos) {
+  uint32_t m = __builtin_amdgcn_readfirstlane(mask);
+#pragma unroll
+  for (int q = 0; q < TileShape<TILE>::kGroups; ++q)
+    if (pos > P.glast[q]) m &= ~(1u << q);
+  return m;
+}
+
+// One 64-lane wave per tile walks the list back to front in chunks staged in
+// LDS, the next chunk's indices read ahead.  With `skip_long`, tiles whose list is
+// longer than their view's threshold are left to k_blend_bwd_long.
+// Bound by instruction issue (38 vector instructions per pixel and entry reached)
+// and, at the ends, by the longest lists.  1M Gaussians at 1600x1064, 16-pixel
+// tiles: 490 us with every lane selecting its updates and all nine sums finished
+// in registers per entry, 365 so (16 views of mixed sizes 2740 to 2035; tiles of
+// 8: 608 to 450, of 32: 953 to 754).  Measured and not taken there: chunks of 32
+// and 48 entries 375 to 400, the sums through LDS alone 486, through the f32
+// matrix instruction (which shares the vector units) 548.
+constexpr int kBwdChunk = 64;
+
+template <int TILE>
 __global__ __launch_bounds__(64) void k_blend_bwd(
     RViews RV, int n, const char* __restrict__ proj, size_t stride,
     const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
@@ -231,12 +398,9 @@ __global__ __launch_bounds__(64) void k_blend_bwd(
     const float* __restrict__ dL_dimage, size_t goff_off,
     float* __restrict__ pair_grad, int64_t cap, float bg0, float bg1, float bg2, int skip_long,
     const uint32_t* __restrict__ order) {
-  __shared__ float4 s_r0[BATCH];
-  __shared__ float4 s_r1[BATCH];
-  __shared__ float s_b[BATCH];
-  __shared__ uint32_t s_mask[BATCH];
-  __shared__ uint32_t s_pidx[BATCH];
-  const BwdStage S{s_r0, s_r1, s_b, s_mask, s_pidx};
+  __shared__ BwdRec s_rec[kBwdChunk];
+  __shared__ __align__(16) float s_part[kSumEnts * kPartEnt];
+  __shared__ uint32_t s_slot[kSumEnts];
 
   const int t = order ? int(order[blockIdx.x]) : xcd_tile(blockIdx.x, RV);
   const uint32_t start = ranges[2 * t], end = ranges[2 * t + 1];
@@ -253,16 +417,51 @@ __global__ __launch_bounds__(64) void k_blend_bwd(
   const uint32_t* goff = reinterpret_cast<const uint32_t*>(proj + size_t(v) * stride + goff_off);
   const float px0 = float(lane & 7) + 0.5f, py0 = float(lane >> 3) + 0.5f;
 
-  for (uint32_t bend = stop; bend > start;) {
-    const uint32_t bstart = (bend - start > uint32_t(BATCH)) ? bend - BATCH : start;
-    const int nb = int(bend - bstart);
-    __syncthreads();  // the previous batch is consumed
-    bwd_stage<TILE>(S, bstart, nb, lane, vals, rec, goff, tx, ty);
-    __syncthreads();
-    for (int k = nb - 1; k >= 0; --k)
-      bwd_step<TILE>(P, S, k, bstart - start + uint32_t(k) + 1u, lane, px0, py0, pair_grad, cap);
-    bend = bstart;
+  auto first_of = [&](uint32_t c1) {
+    return c1 - start > uint32_t(kBwdChunk) ? c1 - uint32_t(kBwdChunk) : start;
+  };
+  uint32_t c1 = stop, c0 = first_of(c1), g = 0;
+  if (c0 + uint32_t(lane) < c1) g = vals[c0 + uint32_t(lane)];
+  WaveSum S(s_part, s_slot, lane, pair_grad, cap);
+  while (c1 > start) {
+    __builtin_amdgcn_wave_barrier();  // the previous chunk is consumed
+    bool plain = true;
+    if (lane < kBwdChunk && c0 + uint32_t(lane) < c1) {
+      const float4 r0 = rec[3 * size_t(g)];
+      const float4 r1 = rec[3 * size_t(g) + 1];
+      const float4 r2 = rec[3 * size_t(g) + 2];
+      const uint32_t first = goff[g];
+      const uint32_t lo = __float_as_uint(r2.z), hi = __float_as_uint(r2.w);
+      plain = plain_record(r0, r1.x, r1.y);
+      BwdRec& e = s_rec[lane];
+      e.r0 = to_tile_frame<TILE>(r0, lo, tx, ty);
+      e.r1 = r1;
+      e.b = r2.x;
+      e.mask = group_mask<TILE>(lo, hi, tx, ty);
+      const int tx0 = box_x(lo) / TILE, ty0 = box_y(lo) / TILE, tx1 = box_x(hi) / TILE;
+      e.slot = first + uint32_t((ty - ty0) * (tx1 - tx0 + 1) + (tx - tx0));
+    }
+    __builtin_amdgcn_wave_barrier();
+    const bool all_plain = __ballot(!plain) == 0ull;
+    const uint32_t m1 = c0, m0 = first_of(m1);
+    if (m0 + uint32_t(lane) < m1) g = vals[m0 + uint32_t(lane)];
+    auto walk = [&](auto is_plain) {
+      for (int k = int(c1 - c0) - 1; k >= 0; --k) {
+        const BwdRec& e = s_rec[k];
+        const uint32_t pos = c0 - start + uint32_t(k) + 1u;
+        const uint32_t m = live_groups<TILE>(P, e.mask, pos);
+        if (m == 0u) continue;
+        float acc[kG];
+        if (bwd_entry<TILE, decltype(is_plain)::value>(P, e, m, pos, px0, py0, acc))
+          S.add(acc, e.slot);
+      }
+    };
+    if (all_plain) walk(std::true_type{});
+    else walk(std::false_type{});
+    c1 = m1;
+    c0 = m0;
   }
+  if (S.cnt) S.flush();
 }
 
 // ---- long lists (low resolutions: few tiles, thousands of entries each): one
@@ -1171,24 +1370,17 @@ __global__ __launch_bounds__(1024) void k_zero_pairs(float* __restrict__ p,
 }
 
 template <int TILE>
-void launch_bwd_tile(int batch, dim3 grid, const RViews& RV, int n, const char* proj,
+void launch_bwd_tile(dim3 grid, const RViews& RV, int n, const char* proj,
                      size_t stride, const uint32_t* ranges, const uint32_t* vals,
                      const float* final_T, const uint32_t* last_contrib, const float* dL,
                      size_t goff, float* pairs, int64_t cap, const float* bg,
                      const uint32_t* order, hipStream_t st) {
-  const dim3 block(64);
   // launches with few tiles hand long lists to the list-parallel kernel
   const int split = split_long_lists(RV, TILE) ? 1 : 0;
-#define GS_BWD_LAUNCH(B)                                                                       \
-  GS_LAUNCH("k_blend_bwd", HIP_KERNEL_NAME(k_blend_bwd<TILE, B>), grid, block, 0, st, RV, n, proj,   \
-                     stride, ranges, vals, final_T, last_contrib, dL, goff, pairs, cap, bg[0], \
-                     bg[1], bg[2], split, split ? nullptr : order)
-  switch (batch) {
-    case 128: GS_BWD_LAUNCH(128); break;
-    case 256: GS_BWD_LAUNCH(256); break;
-    default: GS_BWD_LAUNCH(512); break;
-  }
-#undef GS_BWD_LAUNCH
+  GS_LAUNCH("k_blend_bwd", HIP_KERNEL_NAME(k_blend_bwd<TILE>), grid,
+            dim3(64), 0, st, RV, n, proj, stride, ranges, vals, final_T,
+            last_contrib, dL, goff, pairs, cap, bg[0], bg[1], bg[2], split,
+            split ? nullptr : order);
   if (split) {
     const unsigned nb = unsigned(RV.total_tiles < kLongBlocks ? RV.total_tiles : kLongBlocks);
     GS_LAUNCH("k_blend_bwd_long", HIP_KERNEL_NAME(k_blend_bwd_long<TILE <= 16 ? TILE : 16>),
@@ -1231,15 +1423,15 @@ hipError_t bwd_to_planes(const Views& V, int n, const gs_raster_cfg& cfg, const 
     const dim3 grid(unsigned(V.total_tiles));
     switch (cfg.tile) {
       case 8:
-        launch_bwd_tile<8>(cfg.lds_batch, grid, RV, n, proj, L.stride, ranges, vals, final_T,
+        launch_bwd_tile<8>(grid, RV, n, proj, L.stride, ranges, vals, final_T,
                            last_contrib, dL_dimage, goff, pairs, cap, cfg.bg, order, st);
         break;
       case 16:
-        launch_bwd_tile<16>(cfg.lds_batch, grid, RV, n, proj, L.stride, ranges, vals, final_T,
+        launch_bwd_tile<16>(grid, RV, n, proj, L.stride, ranges, vals, final_T,
                             last_contrib, dL_dimage, goff, pairs, cap, cfg.bg, order, st);
         break;
       default:
-        launch_bwd_tile<32>(cfg.lds_batch, grid, RV, n, proj, L.stride, ranges, vals, final_T,
+        launch_bwd_tile<32>(grid, RV, n, proj, L.stride, ranges, vals, final_T,
                             last_contrib, dL_dimage, goff, pairs, cap, cfg.bg, order, st);
         break;
     }
