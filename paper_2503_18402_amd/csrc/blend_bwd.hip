@@ -115,123 +115,15 @@ __device__ __forceinline__ void bwd_load_pixels(BwdPix<TILE>& P, const RViews& R
   }
 }
 
-// one wave's LDS staging of list entries: record in the tile frame, box mask,
-// and the entry's per-pair gradient slot
-struct BwdStage {
-  float4* r0;
-  float4* r1;
-  float* b;
-  uint32_t* mask;
-  uint32_t* pidx;
-};
-
-template <int TILE>
-__device__ __forceinline__ void bwd_stage(const BwdStage& S, uint32_t bstart, int nb, int lane,
-                                          const uint32_t* __restrict__ vals, const float4* rec,
-                                          const uint32_t* goff, int tx, int ty) {
-  for (int k = lane; k < nb; k += 64) {
-    const uint32_t g = vals[bstart + k];
-    const float4 r0 = rec[3 * size_t(g)];
-    const float4 r1 = rec[3 * size_t(g) + 1];
-    const float4 r2 = rec[3 * size_t(g) + 2];
-    const uint32_t lo = __float_as_uint(r2.z), hi = __float_as_uint(r2.w);
-    S.r0[k] = to_tile_frame<TILE>(r0, lo, tx, ty);
-    S.r1[k] = r1;
-    S.b[k] = r2.x;
-    S.mask[k] = group_mask<TILE>(lo, hi, tx, ty);
-    const int tx0 = box_x(lo) / TILE, ty0 = box_y(lo) / TILE, tx1 = box_x(hi) / TILE;
-    S.pidx[k] = goff[g] + uint32_t((ty - ty0) * (tx1 - tx0 + 1) + (tx - tx0));
-  }
-}
-
-// The backward step of staged entry k at list position pos (1-based) for every
-// pixel of the wave: recover T_i, accumulate the nine 2D gradients, reduce
-// them over the wave and write the pair's slot.
-template <int TILE>
-__device__ __forceinline__ void bwd_step(BwdPix<TILE>& P, const BwdStage& S, int k, uint32_t pos,
-                                         int lane, float px0, float py0,
-                                         float* __restrict__ pair_grad, int64_t cap) {
-  constexpr int GX = TileShape<TILE>::kGroupsX, Q = TileShape<TILE>::kGroups;
-  uint32_t m = __builtin_amdgcn_readfirstlane(S.mask[k]);
-#pragma unroll
-  for (int q = 0; q < Q; ++q)
-    if (pos > P.glast[q]) m &= ~(1u << q);
-  if (m == 0u) return;
-  const float4 r0 = S.r0[k];
-  const float4 r1 = S.r1[k];
-  const float cb = S.b[k];
-  const float lo = r1.y;  // log2 of the blending opacity
-  // -0 is the identity of float addition (+0 is not: +0 + -0 = +0), so the
-  // first group's products need no add
-  float acc[kG];
-#pragma unroll
-  for (int c = 0; c < kG; ++c) acc[c] = -0.0f;
-  bool hit = false;
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    if ((m >> q) & 1u) {
-      // branch-free: every lane computes, the decisions select the updates
-      const float px = px0 + float((q % GX) * 8), py = py0 + float((q / GX) * 8);
-      const Alpha e = alpha_at(r0, r1.x, lo, px, py);
-      const bool ok = e.ok & (pos <= P.last[q]);
-      // footprint boxes are conservative: often no pixel of the group is reached
-      if (__ballot(ok) == 0ull) continue;
-      const bool grad = ok & (e.raw <= kAlphaMax);  // the 0.99 clamp passes no gradient
-      hit = true;
-      const float inv = __builtin_amdgcn_rcpf(1.0f - e.a);
-      const float Ti = P.T[q] * inv;
-      const float wgt = ok ? e.a * Ti : 0.0f;
-      const float cg = fmaf(r1.z, P.g0[q], fmaf(r1.w, P.g1[q], cb * P.g2[q]));
-      const float dLda = grad ? fmaf(P.T[q], cg, -P.SdL[q]) * inv : 0.0f;  // (T cg - SdL) / (1 - a)
-      P.SdL[q] = fmaf(wgt, cg, P.SdL[q]);
-      P.T[q] = ok ? Ti : P.T[q];
-      acc[6] = fmaf(wgt, P.g0[q], acc[6]);
-      acc[7] = fmaf(wgt, P.g1[q], acc[7]);
-      acc[8] = fmaf(wgt, P.g2[q], acc[8]);
-      const float dpow = dLda * e.raw;
-      acc[5] += dpow;  // dL/do times o: the chain rule divides by the opacity
-      const float dpx = dpow * e.dx, dpy = dpow * e.dy;
-      acc[2] = fmaf(dpx, e.dx, acc[2]);
-      acc[3] = fmaf(dpx, e.dy, acc[3]);
-      acc[4] = fmaf(dpy, e.dy, acc[4]);
-      // the offsets weighted by dpow; the mean gradient is these two sums
-      // times the Gaussian's conic, applied once in the chain rule
-      acc[0] += dpx;
-      acc[1] += dpy;
-    }
-  }
-  if (hit) {  // wave-uniform
-    float qv[3];
-    wave_sum9(acc, qv);
-    const uint32_t idx = S.pidx[k];
-    if ((lane & 15) == 15 && int64_t(idx) < cap) {
-      // natural-unit conic gradients from the base-2 accumulators; the offset
-      // sums (0, 1) are stored as they are
-      // scales of components (0..3) and (4..7): 1, 1, -1/2, -1 and -1/2, 1, 1, 1
-      const int row = lane >> 4;
-      const int c0 = ((row & 1) << 1) | (row >> 1);  // 0, 2, 1, 3
-      const float s0 = c0 < 2 ? 1.0f : (c0 == 2 ? -0.5f : -1.0f);
-      const float s1 = c0 == 0 ? -0.5f : 1.0f;
-      float* dst = pair_grad + size_t(idx) * kG;
-      dst[c0] = s0 * qv[0];
-      dst[c0 + 4] = s1 * qv[1];
-      if (row == 0) dst[8] = qv[2];
-    }
-  }
-}
-
-
-
 // ---- sums over the wave's pixels.  Nine values per list entry have to be added
 // over 64 lanes, in a fixed order.  Lane swaps cost 8 cycles per SIMD here and
 // DPP adds 4.6 (a plain add 2.6), so only the first two halvings run in
 // registers: DPP adds with bank masks put two values' sums into one register
 // (lanes l and l ^ 8 of a row, then the mirrored half rows), 14 instructions for
 // all nine, which leaves four partial sums per 16-lane row and value.  Those go
-// to LDS, written and not waited for; after kSumEnts entries lane 16 e + c adds
-// the 16 partial sums of entry e's value c and writes it to the pair's slot: one
-// store for kSumEnts entries.
-constexpr int kSumEnts = 4;
+// to LDS, written and not waited for; after ENTS (at most 4) entries lane 16 e + c
+// adds the 16 partial sums of entry e's value c and writes it to the pair's slot:
+// one store for them all.
 constexpr int kPartStride = 20;  // 16 partial sums, padded against bank conflicts
 constexpr int kPartEnt = kG * kPartStride;
 
@@ -263,9 +155,10 @@ __device__ __forceinline__ float slot_scale(int c) {
 
 // One wave's sums on their way to the pair slots.  (What the flush needs beside
 // the lane's places is formed there: registers are what holds the waves per SIMD.)
+template <int ENTS>
 struct WaveSum {
-  float* part;           // [kSumEnts][kPartEnt] floats of LDS, this wave's
-  uint32_t* slots;       // [kSumEnts] pair slots
+  float* part;           // [ENTS][kPartEnt] floats of LDS, this wave's
+  uint32_t* slots;       // [ENTS] pair slots
   float* pair_grad;
   uint32_t cap;
   uint32_t put, put8;    // this lane's places for v0 (v4 follows) and v8
@@ -302,7 +195,7 @@ struct WaveSum {
     p[put + 4 * kPartStride] = acc[4];
     p[put8] = acc[8];
     slots[cnt] = slot;
-    if (++cnt == kSumEnts) flush();
+    if (++cnt == ENTS) flush();
   }
 };
 
@@ -315,6 +208,24 @@ struct BwdRec {
   uint32_t slot;   // the pair's gradient slot
   uint32_t pad;
 };
+
+// stages list entry g of tile (tx, ty); returns whether it is a plain_record
+template <int TILE>
+__device__ __forceinline__ bool bwd_stage(BwdRec& e, uint32_t g, const float4* rec,
+                                          const uint32_t* goff, int tx, int ty) {
+  const float4 r0 = rec[3 * size_t(g)];
+  const float4 r1 = rec[3 * size_t(g) + 1];
+  const float4 r2 = rec[3 * size_t(g) + 2];
+  const uint32_t first = goff[g];
+  const uint32_t lo = __float_as_uint(r2.z), hi = __float_as_uint(r2.w);
+  e.r0 = to_tile_frame<TILE>(r0, lo, tx, ty);
+  e.r1 = r1;
+  e.b = r2.x;
+  e.mask = group_mask<TILE>(lo, hi, tx, ty);
+  const int tx0 = box_x(lo) / TILE, ty0 = box_y(lo) / TILE, tx1 = box_x(hi) / TILE;
+  e.slot = first + uint32_t((ty - ty0) * (tx1 - tx0 + 1) + (tx - tx0));
+  return plain_record(r0, r1.x, r1.y);
+}
 
 // The backward step of an entry at list position pos (1-based) for every pixel
 // of the wave whose group is in m: recover T_i and accumulate the nine 2D
@@ -378,9 +289,27 @@ __device__ __forceinline__ uint32_t live_groups(const BwdPix<TILE>& P, uint32_t 
   return m;
 }
 
+// walks the nb staged entries at list positions first + 1.. back to front
+template <int TILE, int ENTS>
+__device__ __forceinline__ void bwd_walk(BwdPix<TILE>& P, WaveSum<ENTS>& S, const BwdRec* rec, int nb,
+                                         uint32_t first, bool all_plain, float px0, float py0) {
+  auto walk = [&](auto is_plain) {
+    for (int k = nb - 1; k >= 0; --k) {
+      const BwdRec& e = rec[k];
+      const uint32_t pos = first + uint32_t(k) + 1u;
+      const uint32_t m = live_groups<TILE>(P, e.mask, pos);
+      if (m == 0u) continue;
+      float acc[kG];
+      if (bwd_entry<TILE, decltype(is_plain)::value>(P, e, m, pos, px0, py0, acc))
+        S.add(acc, e.slot);
+    }
+  };
+  if (all_plain) walk(std::true_type{});
+  else walk(std::false_type{});
+}
+
 // One 64-lane wave per tile walks the list back to front in chunks staged in
-// LDS, the next chunk's indices read ahead.  With `skip_long`, tiles whose list is
-// longer than their view's threshold are left to k_blend_bwd_long.
+// LDS, the next chunk's indices read ahead.
 // Bound by instruction issue (38 vector instructions per pixel and entry reached)
 // and, at the ends, by the longest lists.  1M Gaussians at 1600x1064, 16-pixel
 // tiles: 490 us with every lane selecting its updates and all nine sums finished
@@ -396,16 +325,15 @@ __global__ __launch_bounds__(64) void k_blend_bwd(
     const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
     const float* __restrict__ final_T, const uint32_t* __restrict__ last_contrib,
     const float* __restrict__ dL_dimage, size_t goff_off,
-    float* __restrict__ pair_grad, int64_t cap, float bg0, float bg1, float bg2, int skip_long,
+    float* __restrict__ pair_grad, int64_t cap, float bg0, float bg1, float bg2,
     const uint32_t* __restrict__ order) {
   __shared__ BwdRec s_rec[kBwdChunk];
-  __shared__ __align__(16) float s_part[kSumEnts * kPartEnt];
-  __shared__ uint32_t s_slot[kSumEnts];
+  __shared__ __align__(16) float s_part[4 * kPartEnt];
+  __shared__ uint32_t s_slot[4];
 
   const int t = order ? int(order[blockIdx.x]) : xcd_tile(blockIdx.x, RV);
   const uint32_t start = ranges[2 * t], end = ranges[2 * t + 1];
   const int v = view_of_tile(RV, t);
-  if (skip_long && end - start > long_list_threshold<TILE>(RV, v)) return;
   const int lt = t - RV.tile_base[v];
   const int gw = RV.gw[v];
   const int tx = lt % gw, ty = lt / gw;
@@ -422,185 +350,148 @@ __global__ __launch_bounds__(64) void k_blend_bwd(
   };
   uint32_t c1 = stop, c0 = first_of(c1), g = 0;
   if (c0 + uint32_t(lane) < c1) g = vals[c0 + uint32_t(lane)];
-  WaveSum S(s_part, s_slot, lane, pair_grad, cap);
+  WaveSum<4> S(s_part, s_slot, lane, pair_grad, cap);
   while (c1 > start) {
     __builtin_amdgcn_wave_barrier();  // the previous chunk is consumed
     bool plain = true;
-    if (lane < kBwdChunk && c0 + uint32_t(lane) < c1) {
-      const float4 r0 = rec[3 * size_t(g)];
-      const float4 r1 = rec[3 * size_t(g) + 1];
-      const float4 r2 = rec[3 * size_t(g) + 2];
-      const uint32_t first = goff[g];
-      const uint32_t lo = __float_as_uint(r2.z), hi = __float_as_uint(r2.w);
-      plain = plain_record(r0, r1.x, r1.y);
-      BwdRec& e = s_rec[lane];
-      e.r0 = to_tile_frame<TILE>(r0, lo, tx, ty);
-      e.r1 = r1;
-      e.b = r2.x;
-      e.mask = group_mask<TILE>(lo, hi, tx, ty);
-      const int tx0 = box_x(lo) / TILE, ty0 = box_y(lo) / TILE, tx1 = box_x(hi) / TILE;
-      e.slot = first + uint32_t((ty - ty0) * (tx1 - tx0 + 1) + (tx - tx0));
-    }
+    if (c0 + uint32_t(lane) < c1) plain = bwd_stage<TILE>(s_rec[lane], g, rec, goff, tx, ty);
     __builtin_amdgcn_wave_barrier();
     const bool all_plain = __ballot(!plain) == 0ull;
     const uint32_t m1 = c0, m0 = first_of(m1);
     if (m0 + uint32_t(lane) < m1) g = vals[m0 + uint32_t(lane)];
-    auto walk = [&](auto is_plain) {
-      for (int k = int(c1 - c0) - 1; k >= 0; --k) {
-        const BwdRec& e = s_rec[k];
-        const uint32_t pos = c0 - start + uint32_t(k) + 1u;
-        const uint32_t m = live_groups<TILE>(P, e.mask, pos);
-        if (m == 0u) continue;
-        float acc[kG];
-        if (bwd_entry<TILE, decltype(is_plain)::value>(P, e, m, pos, px0, py0, acc))
-          S.add(acc, e.slot);
-      }
-    };
-    if (all_plain) walk(std::true_type{});
-    else walk(std::false_type{});
+    bwd_walk(P, S, s_rec, int(c1 - c0), c0 - start, all_plain, px0, py0);
     c1 = m1;
     c0 = m0;
   }
   if (S.cnt) S.flush();
 }
 
-// ---- long lists (low resolutions: few tiles, thousands of entries each): one
-// block of kLongWaves waves per tile, the list cut into nch <= kMaxChunks
-// chunks dealt to the waves.  Which entries a pixel blends is fixed by the
+// ---- launches with few tiles (low resolutions: up to thousands of entries per
+// list): one block of NW waves per tile, the list cut into up to NW chunks, one per
+// wave.  Which entries a pixel blends is fixed by the
 // forward's last_contrib and the alpha test alone, so the chunks are
 // independent:
-//   A. each chunk's transmittance product and colour (front to back, T = 1 at
-//      its start) per pixel;
-//   B. per pixel, the transmittance after each chunk (prefix of the products)
-//      and the colour behind it dotted with dL/dC (suffix of the chunk
-//      colours, weighted by their incoming T, plus T_final (bg . dL/dC));
-//   C. each chunk's backward walk from that state, as in k_blend_bwd.
+//   A. each chunk's transmittance product and its colour dotted with dL/dC (front
+//      to back, T = 1 at its start) per pixel;
+//   B. in every wave, per pixel: the transmittance after its chunk (the product of
+//      the chunks up to it) and the colour behind it dotted with dL/dC (the
+//      background's and, back to front, the later chunks');
+//   C. the chunk's backward walk from that state, as in k_blend_bwd.
 // The T recovery by division therefore runs over at most one chunk.
-constexpr int kLongWaves = 8;
-constexpr int kMaxChunks = 16;
+// Bound by the longest wave: staging, two walks of a chunk, one wave's issue rate.
+// 16 waves per tile while two such blocks per CU hold every tile (a launch of up to
+// 512 tiles: 48 tiles 37 us against 46 with 8 waves, 425 tiles 74 against 101); above
+// that, where blocks queue, 8 (950 tiles: 44 against 49).  4 waves: 49 to 161.  With 8
+// waves of several chunks for the lists above 48 entries and k_blend_bwd for the others
+// these launches took 96, 119 and 64 us.
 constexpr uint32_t kMinChunk = 32;
-constexpr int kLongBatch = 64;
-constexpr int kLongBlocks = 1024;
+constexpr int kWideTiles = 512;
 
-template <int TILE>
-__global__ __launch_bounds__(64 * kLongWaves) void k_blend_bwd_long(
+template <int TILE, int NW>
+__global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
     RViews RV, int n, const char* __restrict__ proj, size_t stride,
     const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
     const float* __restrict__ final_T, const uint32_t* __restrict__ last_contrib,
     const float* __restrict__ dL_dimage, size_t goff_off,
     float* __restrict__ pair_grad, int64_t cap, float bg0, float bg1, float bg2) {
   constexpr int GX = TileShape<TILE>::kGroupsX, Q = TileShape<TILE>::kGroups;
-  __shared__ float4 s_r0[kLongWaves][kLongBatch];
-  __shared__ float4 s_r1[kLongWaves][kLongBatch];
-  __shared__ float s_b[kLongWaves][kLongBatch];
-  __shared__ uint32_t s_mask[kLongWaves][kLongBatch];
-  __shared__ uint32_t s_pidx[kLongWaves][kLongBatch];
-  // per chunk and pixel: (product, colour) after pass A, (T after, SdL after) after B
-  __shared__ float4 s_ch[kMaxChunks][Q][64];
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const BwdStage S{s_r0[wv], s_r1[wv], s_b[wv], s_mask[wv], s_pidx[wv]};
+  __shared__ BwdRec s_rec[NW][kBwdChunk];
+  constexpr int ENTS = 2;  // 80 KB with 16 waves at tiles of 8: two blocks per CU
+  __shared__ __align__(16) float s_part[NW][ENTS * kPartEnt];
+  __shared__ uint32_t s_slot[NW][ENTS];
+  __shared__ float2 s_ch[NW][Q][64];  // A: (product, colour . dL/dC)
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int t = xcd_tile(blockIdx.x, RV);
+  const uint32_t start = ranges[2 * t], end = ranges[2 * t + 1];
+  if (start == end) return;
+  const int v = view_of_tile(RV, t);
+  const int lt = t - RV.tile_base[v];
+  const int gw = RV.gw[v];
+  const int tx = lt % gw, ty = lt / gw;
+  BwdPix<TILE> P;
+  bwd_load_pixels<TILE>(P, RV, v, tx, ty, lane, final_T, last_contrib, dL_dimage, bg0, bg1, bg2);
+  const uint32_t len = min(P.mylast, end - start);  // entries anyone blends
+  if (len == 0u) return;                            // block-uniform
+  const int nch = int(min((len + kMinChunk - 1u) / kMinChunk, uint32_t(NW)));
+  const uint32_t ch = (len + uint32_t(nch) - 1u) / uint32_t(nch);
+  const uint32_t c0 = min(uint32_t(wv) * ch, len), c1 = min(c0 + ch, len);
+  const float4* rec = reinterpret_cast<const float4*>(proj + size_t(v) * stride);
+  const uint32_t* goff = reinterpret_cast<const uint32_t*>(proj + size_t(v) * stride + goff_off);
   const float px0 = float(lane & 7) + 0.5f, py0 = float(lane >> 3) + 0.5f;
+  BwdRec* const my = s_rec[wv];
 
-  for (int t = blockIdx.x; t < RV.total_tiles; t += gridDim.x) {
-    const uint32_t start = ranges[2 * t], end = ranges[2 * t + 1];
-    const int v = view_of_tile(RV, t);
-    if (end - start <= long_list_threshold<TILE>(RV, v)) continue;  // block-uniform
-    const int lt = t - RV.tile_base[v];
-    const int gw = RV.gw[v];
-    const int tx = lt % gw, ty = lt / gw;
-    BwdPix<TILE> P;
-    bwd_load_pixels<TILE>(P, RV, v, tx, ty, lane, final_T, last_contrib, dL_dimage, bg0, bg1,
-                          bg2);
-    const uint32_t len = min(P.mylast, end - start);  // entries anyone blends
-    const uint32_t want = (len + kMinChunk - 1) / kMinChunk;
-    const int nch = int(want < uint32_t(kMaxChunks) ? want : uint32_t(kMaxChunks));
-    const uint32_t ch = nch > 0 ? (len + uint32_t(nch) - 1) / uint32_t(nch) : 0u;
-    const float4* rec = reinterpret_cast<const float4*>(proj + size_t(v) * stride);
-    const uint32_t* goff =
-        reinterpret_cast<const uint32_t*>(proj + size_t(v) * stride + goff_off);
+  bool all_plain = true;
+  auto stage = [&](uint32_t i0, uint32_t i1) {  // at most kBwdChunk entries
+    __builtin_amdgcn_wave_barrier();
+    bool plain = true;
+    if (i0 + uint32_t(lane) < i1)
+      plain = bwd_stage<TILE>(my[lane], vals[start + i0 + uint32_t(lane)], rec, goff, tx, ty);
+    all_plain = __ballot(!plain) == 0ull;
+    __builtin_amdgcn_wave_barrier();
+  };
 
-    // A. per chunk: product of (1 - alpha) and colour over the blended entries
-    for (int c = wv; c < nch; c += kLongWaves) {
-      const uint32_t c0 = uint32_t(c) * ch, c1 = min(c0 + ch, len);
-      float Pr[Q], C0[Q], C1[Q], C2[Q];
+  // A (its last batch stays staged for C)
+  {
+    float Pr[Q], Sc[Q];
 #pragma unroll
-      for (int q = 0; q < Q; ++q) Pr[q] = 1.0f, C0[q] = C1[q] = C2[q] = 0.0f;
-      for (uint32_t b0 = c0; b0 < c1; b0 += kLongBatch) {
-        const int nb = int(min(c1 - b0, uint32_t(kLongBatch)));
-        bwd_stage<TILE>(S, start + b0, nb, lane, vals, rec, goff, tx, ty);
-        __builtin_amdgcn_wave_barrier();
-        for (int k = 0; k < nb; ++k) {
-          const uint32_t pos = b0 + uint32_t(k) + 1u;
-          const uint32_t m = __builtin_amdgcn_readfirstlane(S.mask[k]);
-          const float4 r0 = S.r0[k], r1 = S.r1[k];
-          const float cb = S.b[k];
+    for (int q = 0; q < Q; ++q) Pr[q] = 1.0f, Sc[q] = 0.0f;
+    for (uint32_t b0 = c0; b0 < c1; b0 += kBwdChunk) {
+      const int nb = int(min(c1 - b0, uint32_t(kBwdChunk)));
+      stage(b0, c1);
+      if (nch == 1) continue;
+      for (int k = 0; k < nb; ++k) {
+        const BwdRec& e = my[k];
+        const uint32_t pos = b0 + uint32_t(k) + 1u;
+        const uint32_t m = live_groups<TILE>(P, e.mask, pos);
+        if (m == 0u) continue;
+        const float4 r0 = e.r0, r1 = e.r1;
+        const float cb = e.b;
 #pragma unroll
-          for (int q = 0; q < Q; ++q) {
-            if (((m >> q) & 1u) == 0u || pos > P.glast[q]) continue;  // wave-uniform
-            const float px = px0 + float((q % GX) * 8), py = py0 + float((q / GX) * 8);
-            const Alpha e = alpha_at(r0, r1.x, r1.y, px, py);
-            const bool ok = e.ok & (pos <= P.last[q]);
-            const float w = ok ? e.a * Pr[q] : 0.0f;
-            C0[q] = fmaf(w, r1.z, C0[q]);
-            C1[q] = fmaf(w, r1.w, C1[q]);
-            C2[q] = fmaf(w, cb, C2[q]);
-            Pr[q] = ok ? Pr[q] * (1.0f - e.a) : Pr[q];
+        for (int q = 0; q < Q; ++q) {
+          if (((m >> q) & 1u) == 0u) continue;  // wave-uniform
+          const Exponent x = exponent_at(r0, r1.x, r1.y, px0 + float((q % GX) * 8),
+                                         py0 + float((q / GX) * 8));
+          if (__builtin_expect((x.p2 <= 0.0f) & (x.q >= kLog2AlphaMin) & (pos <= P.last[q]), 1)) {
+            const float a = fminf(kAlphaMax, __builtin_amdgcn_exp2f(x.q));
+            const float cg = fmaf(r1.z, P.g0[q], fmaf(r1.w, P.g1[q], cb * P.g2[q]));
+            Sc[q] = fmaf(a * Pr[q], cg, Sc[q]);
+            Pr[q] *= 1.0f - a;
           }
         }
-        __builtin_amdgcn_wave_barrier();  // the staging is rewritten next
-      }
-#pragma unroll
-      for (int q = 0; q < Q; ++q) s_ch[c][q][lane] = make_float4(Pr[q], C0[q], C1[q], C2[q]);
-    }
-    __syncthreads();
-    // B. wave q handles pixel group q: T after each chunk and the colour behind it
-    if (wv < Q) {
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        if (q != wv) continue;
-        // prefix: the transmittance entering each chunk replaces its product
-        float T = 1.0f;
-        for (int c = 0; c < nch; ++c) {
-          const float pr = s_ch[c][q][lane].x;
-          s_ch[c][q][lane].x = T;
-          T *= pr;
-        }
-        // suffix: P.SdL holds T_final (bg . dL/dC); the forward's T_final is the
-        // transmittance after the last chunk
-        float behind = P.SdL[q];
-        float Tafter = P.T[q];
-        for (int c = nch - 1; c >= 0; --c) {
-          const float4 pc = s_ch[c][q][lane];  // (T entering, colour)
-          s_ch[c][q][lane] = make_float4(Tafter, behind, 0.0f, 0.0f);
-          const float cg = fmaf(pc.y, P.g0[q], fmaf(pc.z, P.g1[q], pc.w * P.g2[q]));
-          behind = fmaf(pc.x, cg, behind);
-          Tafter = pc.x;
-        }
       }
     }
-    __syncthreads();
-    // C. backward walk of each chunk from its end state
-    for (int c = wv; c < nch; c += kLongWaves) {
-      const uint32_t c0 = uint32_t(c) * ch, c1 = min(c0 + ch, len);
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const float4 st = s_ch[c][q][lane];
-        P.T[q] = st.x;
-        P.SdL[q] = st.y;
-      }
-      for (uint32_t bend = c1; bend > c0;) {
-        const uint32_t bstart = (bend - c0 > uint32_t(kLongBatch)) ? bend - kLongBatch : c0;
-        const int nb = int(bend - bstart);
-        bwd_stage<TILE>(S, start + bstart, nb, lane, vals, rec, goff, tx, ty);
-        __builtin_amdgcn_wave_barrier();
-        for (int k = nb - 1; k >= 0; --k)
-          bwd_step<TILE>(P, S, k, bstart + uint32_t(k) + 1u, lane, px0, py0, pair_grad, cap);
-        __builtin_amdgcn_wave_barrier();
-        bend = bstart;
-      }
-    }
-    __syncthreads();  // s_ch is rewritten for the block's next tile
+    for (int q = 0; q < Q; ++q) s_ch[wv][q][lane] = make_float2(Pr[q], Sc[q]);
   }
+  __syncthreads();
+  if (c0 == c1) return;
+  // B
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    float T = 1.0f;
+    for (int j = 0; j <= wv; ++j) T *= s_ch[j][q][lane].x;
+    // the forward's T_final is the transmittance after the last chunk
+    if (wv == nch - 1) continue;
+    P.T[q] = T;
+    // (in units of the transmittance entering what lies behind)
+    float b = fmaf(bg0, P.g0[q], fmaf(bg1, P.g1[q], bg2 * P.g2[q]));
+    for (int j = nch - 1; j > wv; --j) {
+      const float2 pc = s_ch[j][q][lane];
+      b = fmaf(pc.x, b, pc.y);
+    }
+    P.SdL[q] = T * b;
+  }
+  // C
+  WaveSum<ENTS> S(s_part[wv], s_slot[wv], lane, pair_grad, cap);
+  uint32_t b0 = c0 + (c1 - c0 - 1u) / kBwdChunk * kBwdChunk, b1 = c1;
+  while (true) {
+    bwd_walk(P, S, my, int(b1 - b0), b0, all_plain, px0, py0);
+    if (b0 == c0) break;
+    b1 = b0;
+    b0 -= kBwdChunk;
+    stage(b0, b1);
+  }
+  if (S.cnt) S.flush();
 }
 
 // -------------------------------------------------------------- chain rule
@@ -1375,18 +1266,17 @@ void launch_bwd_tile(dim3 grid, const RViews& RV, int n, const char* proj,
                      const float* final_T, const uint32_t* last_contrib, const float* dL,
                      size_t goff, float* pairs, int64_t cap, const float* bg,
                      const uint32_t* order, hipStream_t st) {
-  // launches with few tiles hand long lists to the list-parallel kernel
-  const int split = split_long_lists(RV, TILE) ? 1 : 0;
+  if (few_tiles(RV, TILE)) {
+    constexpr int T = TILE <= 16 ? TILE : 16;
+    const bool wide = RV.total_tiles <= kWideTiles;
+    GS_LAUNCH("k_blend_bwd_long", (wide ? k_blend_bwd_long<T, 16> : k_blend_bwd_long<T, 8>), grid,
+              dim3(wide ? 1024 : 512), 0, st, RV, n, proj, stride, ranges, vals, final_T,
+              last_contrib, dL, goff, pairs, cap, bg[0], bg[1], bg[2]);
+    return;
+  }
   GS_LAUNCH("k_blend_bwd", HIP_KERNEL_NAME(k_blend_bwd<TILE>), grid,
             dim3(64), 0, st, RV, n, proj, stride, ranges, vals, final_T,
-            last_contrib, dL, goff, pairs, cap, bg[0], bg[1], bg[2], split,
-            split ? nullptr : order);
-  if (split) {
-    const unsigned nb = unsigned(RV.total_tiles < kLongBlocks ? RV.total_tiles : kLongBlocks);
-    GS_LAUNCH("k_blend_bwd_long", HIP_KERNEL_NAME(k_blend_bwd_long<TILE <= 16 ? TILE : 16>),
-              dim3(nb), dim3(64 * kLongWaves), 0, st, RV, n, proj, stride, ranges, vals, final_T,
-              last_contrib, dL, goff, pairs, cap, bg[0], bg[1], bg[2]);
-  }
+            last_contrib, dL, goff, pairs, cap, bg[0], bg[1], bg[2], order);
 }
 
 }  // namespace
@@ -1415,7 +1305,7 @@ hipError_t bwd_to_planes(const Views& V, int n, const gs_raster_cfg& cfg, const 
   const RViews RV = make_rviews(V);
   const size_t T = size_t(V.total_tiles);
   uint32_t* order = nullptr;
-  if (T > 0 && !split_long_lists(RV, cfg.tile) && size_t(4) * kG * size_t(M) >= 4 * T)
+  if (T > 0 && !few_tiles(RV, cfg.tile) && size_t(4) * kG * size_t(M) >= 4 * T)
     order = reinterpret_cast<uint32_t*>(ws + B.g2d);
   GS_LAUNCH("k_zero_pairs", k_zero_pairs, dim3(kXcds + kZeroBlocks), dim3(1024), 0, st, pairs,
             total, cap, RV, ranges, order, step_dev);

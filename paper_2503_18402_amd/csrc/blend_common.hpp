@@ -135,26 +135,17 @@ __host__ __device__ __forceinline__ int order_block(int r, int n, int round_len 
   return (round < full && (round & 1)) ? round * round_len + (round_len - 1 - j) : r;
 }
 
-// List-parallel blending, for launches with few tiles: when the whole launch
-// has fewer than kFewTiles tiles (a low-resolution view on its own), lists
-// longer than kLongList go to the list-parallel kernels (tiles of 8 and 16
-// pixels; the forward and the backward use the same rule, so both take the
-// same path for a tile).  A wave walking a list alone on its SIMD costs about
-// 0.4 us per entry, and with few tiles nothing else runs meanwhile.  A launch
+// List-parallel blending, for launches with few tiles (a low-resolution view on
+// its own, tiles of 8 and 16 pixels): with fewer than kFewTiles tiles one wave per
+// tile or square leaves SIMDs idle and its list's length is waited for, so
+// the list is cut into chunks for several waves.  A launch
 // with more tiles (a full-resolution view, or a batch of views) fills the chip
 // with tiles alone; its longest lists start first (views are walked fewest
-// tiles first), and splitting them only adds the list-parallel passes' extra
-// work, so such launches skip the long-list kernels altogether.
-constexpr uint32_t kLongList = 48;
+// tiles first), and splitting them would only add the chunks' extra work.
 constexpr int kFewTiles = 2048;
 
-__host__ __device__ inline bool split_long_lists(const RViews& RV, int tile) {
+__host__ __device__ inline bool few_tiles(const RViews& RV, int tile) {
   return tile <= 16 && RV.total_tiles < kFewTiles;
-}
-
-template <int TILE>
-__device__ __forceinline__ uint32_t long_list_threshold(const RViews&, int) {
-  return kLongList;
 }
 
 // global tile id -> view (views are few; the loop runs on the scalar unit)

@@ -80,8 +80,8 @@ struct FwdPix {
 };
 
 // Blends an entry into a pixel, under the mask of the pixels reached.  PLAIN:
-// the entry is a plain_record.
-template <bool PLAIN>
+// the entry is a plain_record.  STOP: the pixel stops at kTMin.
+template <bool PLAIN, bool STOP>
 __device__ __forceinline__ void fwd_blend(FwdPix& P, const FwdEnt& e, float px, float py) {
   const Exponent x = exponent_at(e.r0, e.r1.x, e.r1.y, px, py);
   if (__builtin_expect((PLAIN || x.p2 <= 0.0f) & (x.q >= P.thr), 1)) {
@@ -89,7 +89,7 @@ __device__ __forceinline__ void fwd_blend(FwdPix& P, const FwdEnt& e, float px, 
     const float a = PLAIN ? raw : fminf(kAlphaMax, raw);
     const float aT = a * P.T;
     const float Tn = P.T - aT;  // T (1 - alpha), reusing the weight's product
-    const bool stop = Tn < kTMin;  // stops without blending the entry
+    const bool stop = STOP && Tn < kTMin;  // stops without blending the entry
     const float w = stop ? 0.0f : aT;
     P.C0 = fmaf(w, e.r1.z, P.C0);
     P.C1 = fmaf(w, e.r1.w, P.C1);
@@ -100,19 +100,45 @@ __device__ __forceinline__ void fwd_blend(FwdPix& P, const FwdEnt& e, float px, 
   }
 }
 
+// Walks the entries of `todo` among the 64 at rec, on the scalar unit: the next
+// entry's record is read while the current one is blended (past the last one: any
+// record, not used).
+template <class Blend>
+__device__ __forceinline__ void fwd_walk(const FwdRec* rec, uint64_t todo, Blend&& blend) {
+  auto fetch = [&](FwdEnt& e) {
+    const FwdRec& r = rec[__builtin_ctzll(todo | (1ull << 63))];
+    todo &= todo - 1ull;
+    e.r0 = r.r0;
+    e.r1 = r.r1;
+    e.b = r.b;
+    e.pos = r.pos;
+  };
+  int left = __builtin_popcountll(todo);
+  if (left == 0) return;
+  FwdEnt ea, eb;
+  fetch(ea);
+  while (true) {
+    fetch(eb);
+    blend(ea);
+    if (left == 1) break;
+    fetch(ea);
+    blend(eb);
+    if (left == 2) break;
+    left -= 2;
+  }
+}
+
 template <int TILE, int BATCH>
 __global__ __launch_bounds__(WaveShape<TILE>::kThreads) void k_blend_fwd(
     RViews RV, const char* __restrict__ proj, size_t stride, const uint32_t* __restrict__ ranges,
     const uint32_t* __restrict__ vals, float* __restrict__ image, float* __restrict__ final_T,
-    uint32_t* __restrict__ last_contrib, float bg0, float bg1, float bg2, int skip_long,
-    L1Fuse l1) {
+    uint32_t* __restrict__ last_contrib, float bg0, float bg1, float bg2, L1Fuse l1) {
   using S = WaveShape<TILE>;
   constexpr int NT = S::kThreads, NW = S::kWaves, R = S::kRegion, SUB = S::kSub, P = S::kPix;
   __shared__ FwdRec s_rec[BATCH];
 
   const int t = xcd_tile(blockIdx.x, RV);
   const int v = view_of_tile(RV, t);
-  if (skip_long && ranges[2 * t + 1] - ranges[2 * t] > long_list_threshold<TILE>(RV, v)) return;
   const int lt = t - RV.tile_base[v];
   const int gw = RV.gw[v], W = RV.W[v], H = RV.H[v];
   const int tx = lt % gw, ty = lt / gw;
@@ -170,36 +196,13 @@ __global__ __launch_bounds__(WaveShape<TILE>::kThreads) void k_blend_fwd(
       // the entries of these 64 whose box touches this wave's square, walked on the scalar unit
       const uint32_t msk = c + lane < nb ? s_rec[(c + lane) % BATCH].mask : 0u;
       uint64_t todo = __ballot((msk >> w) & 1u);
-      // the next entry's record is read while the current one is blended
-      // (past the last one: any record, not used)
-      auto fetch = [&](FwdEnt& e) {
-        const FwdRec& r = s_rec[c + __builtin_ctzll(todo | (1ull << 63))];
-        todo &= todo - 1ull;
-        e.r0 = r.r0;
-        e.r1 = r.r1;
-        e.b = r.b;
-        e.pos = r.pos;
-      };
-      auto blend = [&](auto is_plain, const FwdEnt& e) {
-#pragma unroll
-        for (int p = 0; p < P; ++p)
-          fwd_blend<decltype(is_plain)::value>(X[p], e, px0 + float((p % SUB) * 8),
-                                               py0 + float((p / SUB) * 8));
-      };
       auto walk = [&](auto is_plain) {
-        int left = __builtin_popcountll(todo);
-        if (left == 0) return;
-        FwdEnt ea, eb;
-        fetch(ea);
-        while (true) {
-          fetch(eb);
-          blend(is_plain, ea);
-          if (left == 1) break;
-          fetch(ea);
-          blend(is_plain, eb);
-          if (left == 2) break;
-          left -= 2;
-        }
+        fwd_walk(s_rec + c, todo, [&](const FwdEnt& e) {
+#pragma unroll
+          for (int p = 0; p < P; ++p)
+            fwd_blend<decltype(is_plain)::value, true>(X[p], e, px0 + float((p % SUB) * 8),
+                                                       py0 + float((p / SUB) * 8));
+        });
       };
       if ((__ballot((msk & kNotPlain) != 0u) & todo) == 0ull) walk(std::true_type{});
       else walk(std::false_type{});
@@ -230,41 +233,25 @@ __global__ __launch_bounds__(WaveShape<TILE>::kThreads) void k_blend_fwd(
   if (l1.loss) l1_block_add<NW>(l1, l1_abs);
 }
 
-// ---- long lists (low resolutions: few tiles, thousands of entries each): one
-// block of kFWaves waves per tile, the list cut into nch <= kFMaxChunks chunks
-// dealt to the waves; lane l owns pixel (l % 8, l / 8) of every 8x8 group.
-// Transmittance only decreases along the list, so a pixel stops inside chunk
-// k exactly when T entering k times the product of (1 - alpha) over k's
-// entries falls below 1e-4:
-//   A. per chunk and pixel, with no stopping: the product, the colour (T = 1
-//      at the chunk start) and the last entry with alpha >= 1/255;
-//   B. per pixel: the first chunk whose product takes T below 1e-4, and T and
-//      colour entering it (or, if none, the final T, colour and last entry);
-//   C. from that chunk on, the sequential front-to-back walk of the short
-//      kernel until the pixel stops.
+// ---- launches with few tiles (low resolutions: up to thousands of entries per
+// list): one block of kFWaves waves per 8x8 group of a tile, lane l at pixel
+// (l % 8, l / 8).  The list is walked in rounds of kFWaves chunks, one per wave,
+// until no pixel is left.  Transmittance only decreases along the list, so a pixel
+// stops inside a chunk exactly when T entering it times the product of (1 - alpha)
+// over its entries falls below 1e-4:
+//   A. per chunk, with no stopping: the product, the colour (T = 1 at the
+//      chunk's start) and the last entry with alpha >= 1/255;
+//   B. in every wave, from all chunks: the chunk where the pixel stops, and T and
+//      colour entering it (or, if none, after the round);
+//   C. from that chunk on, its wave walks the pixel's list until it stops.
+// Bound by one wave's issue rate and by the rounds, each a gather, a walk and a
+// barrier.  A 128x96 view of 48 tiles of 16: 15 us, against 51 with one block per tile
+// and a second launch for its short lists; 425 tiles of up to 3152 entries, where no
+// pixel needs more than 1205 and half the pixels 530: 58 against 139 with the whole list
+// evaluated; 950 tiles of 180: 22 against 38.  4 waves 18, 76 and 20; 16 waves 16,
+// 68 and 40; chunks of 32 or 64 the same within 1 us.
 constexpr int kFWaves = 8;
-constexpr int kFMaxChunks = 16;
-constexpr uint32_t kFMinChunk = 32;
-constexpr int kFBatch = 64;
-constexpr int kFLongBlocks = 1024;
-
-template <int TILE>
-__device__ __forceinline__ void fwd_stage(float4* r0s, float4* r1s, float* bs, uint32_t* ms,
-                                          uint32_t bstart, int nb, int lane,
-                                          const uint32_t* __restrict__ vals, const float4* rec,
-                                          int tx, int ty) {
-  for (int k = lane; k < nb; k += 64) {
-    const uint32_t g = vals[bstart + k];
-    const float4 r0 = rec[3 * size_t(g)];
-    const float4 r1 = rec[3 * size_t(g) + 1];
-    const float4 r2 = rec[3 * size_t(g) + 2];
-    const uint32_t lo = __float_as_uint(r2.z), hi = __float_as_uint(r2.w);
-    r0s[k] = to_tile_frame<TILE>(r0, lo, tx, ty);
-    r1s[k] = r1;
-    bs[k] = r2.x;
-    ms[k] = group_mask<TILE>(lo, hi, tx, ty);
-  }
-}
+constexpr uint32_t kFChunk = 48;  // most entries of a chunk; a list of one is only walked (C)
 
 template <int TILE>
 __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
@@ -272,184 +259,135 @@ __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
     const uint32_t* __restrict__ vals, float* __restrict__ image, float* __restrict__ final_T,
     uint32_t* __restrict__ last_contrib, float bg0, float bg1, float bg2, L1Fuse l1) {
   constexpr int GX = TileShape<TILE>::kGroupsX, Q = TileShape<TILE>::kGroups;
-  __shared__ float4 s_r0[kFWaves][kFBatch];
-  __shared__ float4 s_r1[kFWaves][kFBatch];
-  __shared__ float s_b[kFWaves][kFBatch];
-  __shared__ uint32_t s_mask[kFWaves][kFBatch];
-  __shared__ float4 s_ch[kFMaxChunks][Q][64];    // A: (product, colour)
-  __shared__ uint32_t s_lp[kFMaxChunks][Q][64];  // A: last entry with alpha >= 1/255
-  __shared__ float4 s_st[Q][64];                 // B/C: (T, colour) of the pixel
-  __shared__ uint32_t s_stop[Q][64];             // B: stop chunk + 1, 0 if none
-  __shared__ uint32_t s_last[Q][64];             // B/C: last blended entry
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int lx = lane & 7, ly = lane >> 3;
-  const float px0 = float(lx) + 0.5f, py0 = float(ly) + 0.5f;
-  float4* r0s = s_r0[wv];
-  float4* r1s = s_r1[wv];
-  float* bs = s_b[wv];
-  uint32_t* ms = s_mask[wv];
-  float l1_abs = 0.0f;  // over the block's tiles
+  __shared__ FwdRec s_rec[kFWaves][64];
+  __shared__ float4 s_ch[2][kFWaves][64];    // A: (product, colour); rounds alternate
+  __shared__ uint32_t s_lp[2][kFWaves][64];  // A: last entry with alpha >= 1/255
+  // the groups of a tile run on one XCD
+  const int xcd = blockIdx.x % kXcds, q = (blockIdx.x / kXcds) % Q;
+  const int block = int(blockIdx.x / (kXcds * Q)) * kXcds + xcd;
+  if (block >= RV.total_tiles) return;
+  const int t = xcd_tile(block, RV);
+  const int v = view_of_tile(RV, t);
+  const int lt = t - RV.tile_base[v];
+  const int gw = RV.gw[v], W = RV.W[v], H = RV.H[v];
+  const int tx = lt % gw, ty = lt / gw;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int gx0 = tx * TILE + (q % GX) * 8, gy0 = ty * TILE + (q / GX) * 8;
+  const int x = gx0 + (lane & 7), y = gy0 + (lane >> 3);
+  // pixel centre in the tile's frame
+  const float px = float((q % GX) * 8 + (lane & 7)) + 0.5f;
+  const float py = float((q / GX) * 8 + (lane >> 3)) + 0.5f;
+  const uint32_t start = ranges[2 * t], len = ranges[2 * t + 1] - start;
+  const float4* rec = reinterpret_cast<const float4*>(proj + size_t(v) * stride);
+  FwdRec* const my = s_rec[wv];
 
-  for (int t = blockIdx.x; t < RV.total_tiles; t += gridDim.x) {
-    const uint32_t start = ranges[2 * t], end = ranges[2 * t + 1];
-    const int v = view_of_tile(RV, t);
-    if (end - start <= long_list_threshold<TILE>(RV, v)) continue;  // block-uniform
-    const int lt = t - RV.tile_base[v];
-    const int gw = RV.gw[v], W = RV.W[v], H = RV.H[v];
-    const int tx = lt % gw, ty = lt / gw;
-    const uint32_t len = end - start;
-    const uint32_t want = (len + kFMinChunk - 1) / kFMinChunk;
-    const int nch = int(want < uint32_t(kFMaxChunks) ? want : uint32_t(kFMaxChunks));
-    const uint32_t ch = (len + uint32_t(nch) - 1) / uint32_t(nch);
-    const float4* rec = reinterpret_cast<const float4*>(proj + size_t(v) * stride);
+  const int64_t pb = RV.pix_base[v];
+  const int64_t plane = int64_t(W) * H;
+  float l1_abs = 0.0f;
+  auto write = [&](float T, float C0, float C1, float C2, uint32_t last) {
+    const int64_t o = int64_t(y) * W + x;
+    const float c0 = fmaf(T, bg0, C0), c1 = fmaf(T, bg1, C1), c2 = fmaf(T, bg2, C2);
+    image[3 * pb + o] = c0;
+    image[3 * pb + plane + o] = c1;
+    image[3 * pb + 2 * plane + o] = c2;
+    final_T[pb + o] = T;
+    last_contrib[pb + o] = last;
+    if (l1.target) l1_abs += l1_pixel(l1, 3 * pb + o, plane, c0, c1, c2);
+  };
 
-    // A. per chunk, no stopping
-    for (int c = wv; c < nch; c += kFWaves) {
-      const uint32_t c0 = uint32_t(c) * ch, c1 = min(c0 + ch, len);
-      float Pr[Q], C0[Q], C1[Q], C2[Q];
-      uint32_t lp[Q];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) Pr[q] = 1.0f, C0[q] = C1[q] = C2[q] = 0.0f, lp[q] = 0u;
-      for (uint32_t b0 = c0; b0 < c1; b0 += kFBatch) {
-        const int nb = int(min(c1 - b0, uint32_t(kFBatch)));
-        fwd_stage<TILE>(r0s, r1s, bs, ms, start + b0, nb, lane, vals, rec, tx, ty);
-        __builtin_amdgcn_wave_barrier();
-        for (int k = 0; k < nb; ++k) {
-          const uint32_t m = __builtin_amdgcn_readfirstlane(ms[k]);
-          const float4 r0 = r0s[k], r1 = r1s[k];
-          const float cb = bs[k];
-          const uint32_t pos = b0 + uint32_t(k) + 1u;
-#pragma unroll
-          for (int q = 0; q < Q; ++q) {
-            if (((m >> q) & 1u) == 0u) continue;  // wave-uniform: the box misses the group
-            const Alpha e = alpha_at(r0, r1.x, r1.y, px0 + float((q % GX) * 8),
-                                     py0 + float((q / GX) * 8));
-            const float w = e.ok ? e.a * Pr[q] : 0.0f;
-            C0[q] = fmaf(w, r1.z, C0[q]);
-            C1[q] = fmaf(w, r1.w, C1[q]);
-            C2[q] = fmaf(w, cb, C2[q]);
-            Pr[q] = e.ok ? Pr[q] * (1.0f - e.a) : Pr[q];
-            lp[q] = e.ok ? pos : lp[q];
-          }
-        }
-        __builtin_amdgcn_wave_barrier();  // the staging is rewritten next
-      }
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        s_ch[c][q][lane] = make_float4(Pr[q], C0[q], C1[q], C2[q]);
-        s_lp[c][q][lane] = lp[q];
-      }
+  // entries [i0, min(i0 + 64, i1)) into this wave's LDS: those that touch the group
+  uint64_t todo = 0ull, general = 0ull;
+  auto index = [&](uint32_t i0, uint32_t i1) {
+    return i0 + uint32_t(lane) < i1 ? vals[start + i0 + uint32_t(lane)] : 0u;
+  };
+  auto stage = [&](uint32_t i0, uint32_t i1, uint32_t g) {
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t i = i0 + uint32_t(lane);
+    bool touch = false, plain = true;
+    if (i < i1) {
+      const float4 r0 = rec[3 * size_t(g)];
+      const float4 r1 = rec[3 * size_t(g) + 1];
+      const float4 r2 = rec[3 * size_t(g) + 2];
+      const uint32_t lo = __float_as_uint(r2.z), hi = __float_as_uint(r2.w);
+      touch = box_overlaps(lo, hi, gx0, gy0, gx0 + 7, gy0 + 7);
+      plain = plain_record(r0, r1.x, r1.y);
+      my[lane].r0 = to_tile_frame<TILE>(r0, lo, tx, ty);
+      my[lane].r1 = r1;
+      my[lane].b = r2.x;
+      my[lane].pos = i + 1u;
     }
-    __syncthreads();
-    // B. wave q handles pixel group q
-    if (wv < Q) {
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        if (q != wv) continue;
-        float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
-        uint32_t last = 0u, stop = 0u;
-        for (int c = 0; c < nch; ++c) {
-          const float4 pc = s_ch[c][q][lane];
-          if (T * pc.x < kTMin) {
-            stop = uint32_t(c) + 1u;
-            break;
-          }
+    todo = __ballot(touch);
+    general = todo & __ballot(!plain);
+    __builtin_amdgcn_wave_barrier();
+  };
+  FwdPix X;
+  auto walk = [&](auto stops) {
+    if (general == 0ull)
+      fwd_walk(my, todo,
+               [&](const FwdEnt& e) { fwd_blend<true, decltype(stops)::value>(X, e, px, py); });
+    else
+      fwd_walk(my, todo,
+               [&](const FwdEnt& e) { fwd_blend<false, decltype(stops)::value>(X, e, px, py); });
+  };
+
+  const bool in = (x < W) & (y < H);
+  bool alive = in;
+  float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
+  uint32_t last = 0u;
+  const uint32_t rounds = (len + kFWaves * kFChunk - 1u) / (kFWaves * kFChunk);
+  const uint32_t ch = len <= kFChunk ? kFChunk : (len + kFWaves * rounds - 1u) / (kFWaves * rounds);
+  // (the next round's indices are read ahead)
+  uint32_t g = index(uint32_t(wv) * ch, min(uint32_t(wv + 1) * ch, len));
+  int par = 0;
+  for (uint32_t r0 = 0; r0 < len && __ballot(alive) != 0ull; r0 += kFWaves * ch, par ^= 1) {
+    const uint32_t c0 = r0 + uint32_t(wv) * ch, c1 = min(c0 + ch, len);
+    const int nch = int(min((len - r0 + ch - 1u) / ch, uint32_t(kFWaves)));
+    bool mine = false;
+    if (wv < nch) stage(c0, c1, g);
+    g = index(c0 + kFWaves * ch, min(c0 + (kFWaves + 1u) * ch, len));
+    if (len <= kFChunk) {
+      mine = alive & (wv == 0);
+      alive = false;
+    } else {
+      // A
+      if (wv < nch) {
+        X = FwdPix{1.0f, 0.0f, 0.0f, 0.0f, alive ? kLog2AlphaMin : INFINITY, 0u};
+        walk(std::false_type{});
+        s_ch[par][wv][lane] = make_float4(X.T, X.C0, X.C1, X.C2);
+        s_lp[par][wv][lane] = X.last;
+      }
+      __syncthreads();
+      // B
+      for (int c = 0; c < nch; ++c) {
+        const float4 pc = s_ch[par][c][lane];
+        const uint32_t lp = s_lp[par][c][lane];
+        const float Tn = T * pc.x;
+        const bool stop = alive & (Tn < kTMin);
+        mine |= stop & (c == wv);
+        alive &= !stop;
+        if (alive) {
           C0 = fmaf(T, pc.y, C0);
           C1 = fmaf(T, pc.z, C1);
           C2 = fmaf(T, pc.w, C2);
-          T *= pc.x;
-          const uint32_t l = s_lp[c][q][lane];
-          last = l ? l : last;
-        }
-        s_st[q][lane] = make_float4(T, C0, C1, C2);
-        s_stop[q][lane] = stop;
-        s_last[q][lane] = last;
-      }
-    }
-    __syncthreads();
-    // C. sequential walk from each pixel's stop chunk until it stops
-    for (int c = wv; c < nch; c += kFWaves) {
-      float T[Q], C0[Q], C1[Q], C2[Q];
-      uint32_t last[Q];
-      bool done[Q], mine[Q];
-      bool any = false;
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        mine[q] = s_stop[q][lane] == uint32_t(c) + 1u;
-        const float4 st = s_st[q][lane];
-        T[q] = st.x, C0[q] = st.y, C1[q] = st.z, C2[q] = st.w;
-        last[q] = s_last[q][lane];
-        done[q] = !mine[q];
-        any |= mine[q];
-      }
-      if (__ballot(any) == 0ull) continue;
-      for (uint32_t b0 = uint32_t(c) * ch; b0 < len; b0 += kFBatch) {
-        bool alive = false;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) alive |= !done[q];
-        if (__ballot(alive) == 0ull) break;
-        const int nb = int(min(len - b0, uint32_t(kFBatch)));
-        fwd_stage<TILE>(r0s, r1s, bs, ms, start + b0, nb, lane, vals, rec, tx, ty);
-        __builtin_amdgcn_wave_barrier();
-        for (int k = 0; k < nb; ++k) {
-          const uint32_t m = __builtin_amdgcn_readfirstlane(ms[k]);
-          const float4 r0 = r0s[k], r1 = r1s[k];
-          const float cb = bs[k];
-          const uint32_t pos = b0 + uint32_t(k) + 1u;
-#pragma unroll
-          for (int q = 0; q < Q; ++q) {
-            if (((m >> q) & 1u) == 0u) continue;
-            const Alpha e = alpha_at(r0, r1.x, r1.y, px0 + float((q % GX) * 8),
-                                     py0 + float((q / GX) * 8));
-            const bool ok = e.ok & !done[q];
-            const float aT = e.a * T[q];
-            const float Tn = T[q] - aT;
-            const bool stop = ok & (Tn < kTMin);
-            const bool blend = ok & !stop;
-            const float wgt = blend ? aT : 0.0f;
-            C0[q] = fmaf(wgt, r1.z, C0[q]);
-            C1[q] = fmaf(wgt, r1.w, C1[q]);
-            C2[q] = fmaf(wgt, cb, C2[q]);
-            T[q] = blend ? Tn : T[q];
-            last[q] = blend ? pos : last[q];
-            done[q] = done[q] | stop;
-          }
-        }
-        __builtin_amdgcn_wave_barrier();
-      }
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        if (mine[q]) {
-          s_st[q][lane] = make_float4(T[q], C0[q], C1[q], C2[q]);
-          s_last[q][lane] = last[q];
+          T = Tn;
+          last = lp ? lp : last;
         }
       }
     }
-    __syncthreads();
-    // outputs: wave q writes pixel group q
-    if (wv < Q) {
-      const int64_t pb = RV.pix_base[v];
-      const int64_t plane = int64_t(W) * H;
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        if (q != wv) continue;
-        const int x = tx * TILE + (q % GX) * 8 + lx, y = ty * TILE + (q / GX) * 8 + ly;
-        if (x < W && y < H) {
-          const float4 st = s_st[q][lane];
-          const int64_t o = int64_t(y) * W + x;
-          const float c0 = fmaf(st.x, bg0, st.y), c1 = fmaf(st.x, bg1, st.z),
-                      c2 = fmaf(st.x, bg2, st.w);
-          image[3 * pb + o] = c0;
-          image[3 * pb + plane + o] = c1;
-          image[3 * pb + 2 * plane + o] = c2;
-          final_T[pb + o] = st.x;
-          last_contrib[pb + o] = s_last[q][lane];
-          if (l1.target) l1_abs += l1_pixel(l1, 3 * pb + o, plane, c0, c1, c2);
-        }
+    // C
+    if (__ballot(mine) != 0ull) {
+      X = FwdPix{T, C0, C1, C2, mine ? kLog2AlphaMin : INFINITY, last};
+      for (uint32_t i = c0;;) {
+        walk(std::true_type{});
+        i += (i == c0) ? c1 - c0 : 64u;
+        // (a product rounded below kTMin where the walk stays above: on it goes)
+        if (i >= len || __ballot(X.thr < INFINITY) == 0ull) break;
+        stage(i, len, index(i, len));
       }
+      if (mine) write(X.T, X.C0, X.C1, X.C2, X.last);
     }
-    __syncthreads();  // the block's next tile rewrites the LDS
   }
+  if (wv == 0 && alive) write(T, C0, C1, C2, last);  // the pixels that never stopped
   if (l1.loss) l1_block_add<kFWaves>(l1, l1_abs);
 }
 
@@ -458,30 +396,29 @@ hipError_t launch_tile(int batch, const RViews& RV, const char* proj, size_t str
                        const uint32_t* ranges, const uint32_t* vals, float* image,
                        float* final_T, uint32_t* last_contrib, const float* bg, const L1Fuse& l1,
                        hipStream_t st) {
-  const dim3 grid(unsigned(RV.total_tiles)), block(WaveShape<TILE>::kThreads);
-  // launches with few tiles hand long lists to the list-parallel kernel
-  const int skip_long = split_long_lists(RV, TILE) ? 1 : 0;
-  if (skip_long) {
-    const unsigned nb = unsigned(RV.total_tiles < kFLongBlocks ? RV.total_tiles : kFLongBlocks);
-    GS_LAUNCH("k_blend_fwd_long", HIP_KERNEL_NAME(k_blend_fwd_long<TILE <= 16 ? TILE : 16>),
-              dim3(nb), dim3(64 * kFWaves), 0, st, RV, proj, stride, ranges, vals, image, final_T,
-              last_contrib, bg[0], bg[1], bg[2], l1);
+  if (few_tiles(RV, TILE)) {
+    constexpr int T = TILE <= 16 ? TILE : 16;
+    const unsigned nb = unsigned((RV.total_tiles + kXcds - 1) / kXcds * kXcds) * TileShape<T>::kGroups;
+    GS_LAUNCH("k_blend_fwd_long", k_blend_fwd_long<T>, dim3(nb), dim3(64 * kFWaves), 0, st, RV,
+              proj, stride, ranges, vals, image, final_T, last_contrib, bg[0], bg[1], bg[2], l1);
+    return hipGetLastError();
   }
+  const dim3 grid(unsigned(RV.total_tiles)), block(WaveShape<TILE>::kThreads);
   switch (batch) {
     case 128:
       GS_LAUNCH("k_blend_fwd", HIP_KERNEL_NAME(k_blend_fwd<TILE, 128>), grid, block, 0, st, RV, proj,
                          stride, ranges, vals, image, final_T, last_contrib, bg[0], bg[1], bg[2],
-                         skip_long, l1);
+                         l1);
       break;
     case 256:
       GS_LAUNCH("k_blend_fwd", HIP_KERNEL_NAME(k_blend_fwd<TILE, 256>), grid, block, 0, st, RV, proj,
                          stride, ranges, vals, image, final_T, last_contrib, bg[0], bg[1], bg[2],
-                         skip_long, l1);
+                         l1);
       break;
     default:
       GS_LAUNCH("k_blend_fwd", HIP_KERNEL_NAME(k_blend_fwd<TILE, 512>), grid, block, 0, st, RV, proj,
                          stride, ranges, vals, image, final_T, last_contrib, bg[0], bg[1], bg[2],
-                         skip_long, l1);
+                         l1);
       break;
   }
   return hipGetLastError();

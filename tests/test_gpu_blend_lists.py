@@ -2,12 +2,16 @@
 one entry, of the 64 a chunk holds and one to either side of one and two chunks,
 and what is left for the last flush of the backward's sums; records that may
 reach the opacity clamp among plain ones; tiles of 8, 16 and 32 pixels, ragged views.  The views have more tiles than the list-parallel
-kernels take, so every list is walked by the ordinary ones.
+kernels take, so every list is walked by the ordinary ones.  Then the list-parallel
+kernels on a small view: one chunk, chunks of the least size, the last of one round
+and the first of the next, a wave's second batch, with pixels that stop and that do not.
 
 Tolerances: an image value sums at most 129 weighted colours in float32 (below
 129 * 2^-24 = 8e-6); T is recovered over at most 129 divisions, each within 2^-22,
 so a term of a gradient carries about 129^0.5 * 2^-22 = 2.7e-6 of itself: below the
-1e-5 of the terms' scale that check_grads allows beside 1e-3 of the result."""
+1e-5 of the terms' scale that check_grads allows beside 1e-3 of the result.  (The
+small view: at most 1025 entries, whose roundings of T add up to 1025^0.5 * 2^-24 =
+2e-6, and at most 1025 / 8 divisions.)"""
 import numpy as np
 import pytest
 import torch
@@ -30,6 +34,10 @@ def _stack(count, kind, seed):
     s = rng.normal(-3.6, 0.2, (count, 3))
     q = rng.normal(size=(count, 4))
     o = rng.uniform(-3.6, -2.6, count)
+    if kind == "faint":  # no pixel stops
+        o = rng.uniform(-5.0, -4.5, count)
+    if kind == "dense":  # every box holds the centre
+        m[:, :2] *= 0.25
     front = np.argsort(m[:, 2])
     if kind == "clamped":  # the last and the one at two thirds may reach 0.99
         o[front[[-1, (2 * count) // 3]]] = 7.0
@@ -44,22 +52,36 @@ def _stack(count, kind, seed):
                                         (65, "plain"), (66, "plain"), (128, "plain"),
                                         (129, "clamped")])
 def test_lists_at_chunk_edges_match_oracle(tile, count, kind):
-    w, h = SIZES[tile]
+    _compare(*SIZES[tile], tile, count, kind, least=0.9)
+
+
+@pytest.mark.parametrize("tile", [8, 16])
+@pytest.mark.parametrize("count,kind", [(1, "plain"), (24, "plain"), (25, "clamped"),
+                                        (48, "plain"), (49, "plain"), (384, "faint"),
+                                        (385, "clamped"), (769, "faint"), (1025, "faint"),
+                                        (384, "dense"), (385, "dense")])
+def test_lists_of_few_tiles_match_oracle(tile, count, kind):
+    _compare(61, 45, tile, count, kind, least=0.5)
+
+
+def _compare(w, h, tile, count, kind, least):
     cam = scenes.look_at((0, 0, -3.0), (0, 0, 0), w, h, 300.0)
     sc = _stack(count, kind, seed=count)
     P = project.project(sc, cam, tile=tile)
-    if kind == "plain":
+    if kind in ("plain", "dense"):
         assert max(map(len, render.tile_candidates(P))) == count
     ys, xs = np.mgrid[h // 2 - 22:h // 2 + 23, w // 2 - 22:w // 2 + 23]
     pix = (ys * w + xs).ravel()
     F = render.render_fwd(P, pixels=pix)
+    if kind == "faint":
+        assert F["final_T"].min() > 2e-4
     up = U.zero_flagged(np.random.default_rng(9).uniform(-1, 1, (3, len(pix))), F)
     full = np.zeros((3, w * h), np.float32)
     full[:, pix] = up
     _, frame, g = U.run(sc, [cam], tile=tile, lds_batch=128, upstream=[full], want_keys=False)
     img = frame.image.view(3, -1).cpu().numpy()[:, pix]
     ok = ~F["flag"]
-    assert ok.mean() > 0.9
+    assert ok.mean() > least
     assert np.abs(img - F["image"])[:, ok].max() < 1e-5
     B = render.render_bwd(sc, P, up, pixels=pix, with_bound=True)
     keep = ~U.gaussian_flags(P)
