@@ -80,7 +80,7 @@ struct FwdPix {
 };
 
 // Blends an entry into a pixel, under the mask of the pixels reached.  PLAIN:
-// the entry is a plain_record.  STOP: the pixel stops at kTMin.
+// the entry is a plain_record.  STOP: the pixel stops at kTMin (else T is a product).
 template <bool PLAIN, bool STOP>
 __device__ __forceinline__ void fwd_blend(FwdPix& P, const FwdEnt& e, float px, float py) {
   const Exponent x = exponent_at(e.r0, e.r1.x, e.r1.y, px, py);
@@ -88,7 +88,8 @@ __device__ __forceinline__ void fwd_blend(FwdPix& P, const FwdEnt& e, float px, 
     const float raw = __builtin_amdgcn_exp2f(x.q);
     const float a = PLAIN ? raw : fminf(kAlphaMax, raw);
     const float aT = a * P.T;
-    const float Tn = P.T - aT;  // T (1 - alpha), reusing the weight's product
+    // T (1 - alpha), reusing the weight's product where the pixel may stop
+    const float Tn = STOP ? P.T - aT : P.T * (1.0f - a);
     const bool stop = STOP && Tn < kTMin;  // stops without blending the entry
     const float w = stop ? 0.0f : aT;
     P.C0 = fmaf(w, e.r1.z, P.C0);
@@ -235,8 +236,8 @@ __global__ __launch_bounds__(WaveShape<TILE>::kThreads) void k_blend_fwd(
 
 // ---- launches with few tiles (low resolutions: up to thousands of entries per
 // list): one block of kFWaves waves per 8x8 group of a tile, lane l at pixel
-// (l % 8, l / 8).  The list is walked in rounds of kFWaves chunks, one per wave,
-// until no pixel is left.  Transmittance only decreases along the list, so a pixel
+// (l % 8, l / 8).  The list is cut into up to kFMaxChunks chunks and walked in rounds
+// of kFWaves, one per wave, until no pixel is left.  Transmittance only decreases along the list, so a pixel
 // stops inside a chunk exactly when T entering it times the product of (1 - alpha)
 // over its entries falls below 1e-4:
 //   A. per chunk, with no stopping: the product, the colour (T = 1 at the
@@ -245,13 +246,18 @@ __global__ __launch_bounds__(WaveShape<TILE>::kThreads) void k_blend_fwd(
 //      colour entering it (or, if none, after the round);
 //   C. from that chunk on, its wave walks the pixel's list until it stops.
 // Bound by one wave's issue rate and by the rounds, each a gather, a walk and a
-// barrier.  A 128x96 view of 48 tiles of 16: 15 us, against 51 with one block per tile
+// barrier.  A 128x96 view of 48 tiles of 16: 17 us, against 51 with one block per tile
 // and a second launch for its short lists; 425 tiles of up to 3152 entries, where no
-// pixel needs more than 1205 and half the pixels 530: 58 against 139 with the whole list
-// evaluated; 950 tiles of 180: 22 against 38.  4 waves 18, 76 and 20; 16 waves 16,
-// 68 and 40; chunks of 32 or 64 the same within 1 us.
+// pixel needs more than 1205 and half the pixels 530: 66 against 139 with the whole list
+// evaluated; 950 tiles of 180: 23 against 38.  (With chunks of up to 48 entries in rounds
+// of their own, 4 waves took 18, 76 and 20 us, 8 waves 15, 58 and 22, 16 waves 16, 68
+// and 40: but the chunks' bounds decide how T is rounded, an image that differs in its
+// last bits flips the sign of an L1 gradient now and then, and with it a Gaussian's
+// step, so the chunks stay where they were.)
 constexpr int kFWaves = 8;
-constexpr uint32_t kFChunk = 48;  // most entries of a chunk; a list of one is only walked (C)
+constexpr int kFMaxChunks = 16;
+constexpr uint32_t kFMinChunk = 32;
+constexpr uint32_t kFWalk = 48;  // up to this length a list is only walked (C)
 
 template <int TILE>
 __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
@@ -334,8 +340,8 @@ __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
   bool alive = in;
   float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
   uint32_t last = 0u;
-  const uint32_t rounds = (len + kFWaves * kFChunk - 1u) / (kFWaves * kFChunk);
-  const uint32_t ch = len <= kFChunk ? kFChunk : (len + kFWaves * rounds - 1u) / (kFWaves * rounds);
+  const uint32_t chunks = min((len + kFMinChunk - 1u) / kFMinChunk, uint32_t(kFMaxChunks));
+  const uint32_t ch = len <= kFWalk ? kFWalk : (len + chunks - 1u) / chunks;
   // (the next round's indices are read ahead)
   uint32_t g = index(uint32_t(wv) * ch, min(uint32_t(wv + 1) * ch, len));
   int par = 0;
@@ -345,7 +351,8 @@ __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
     bool mine = false;
     if (wv < nch) stage(c0, c1, g);
     g = index(c0 + kFWaves * ch, min(c0 + (kFWaves + 1u) * ch, len));
-    if (len <= kFChunk) {
+    uint32_t at = c0;  // the staged entries
+    if (len <= kFWalk) {
       mine = alive & (wv == 0);
       alive = false;
     } else {
@@ -353,6 +360,11 @@ __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
       if (wv < nch) {
         X = FwdPix{1.0f, 0.0f, 0.0f, 0.0f, alive ? kLog2AlphaMin : INFINITY, 0u};
         walk(std::false_type{});
+        while (at + 64u < c1) {
+          at += 64u;
+          stage(at, c1, index(at, c1));
+          walk(std::false_type{});
+        }
         s_ch[par][wv][lane] = make_float4(X.T, X.C0, X.C1, X.C2);
         s_lp[par][wv][lane] = X.last;
       }
@@ -377,12 +389,14 @@ __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
     // C
     if (__ballot(mine) != 0ull) {
       X = FwdPix{T, C0, C1, C2, mine ? kLog2AlphaMin : INFINITY, last};
-      for (uint32_t i = c0;;) {
+      if (at != c0) stage(c0, c1, index(c0, c1));
+      for (uint32_t i = c0, end = c1;;) {
         walk(std::true_type{});
-        i += (i == c0) ? c1 - c0 : 64u;
-        // (a product rounded below kTMin where the walk stays above: on it goes)
+        i = min(i + 64u, end);
+        // (a product rounded below kTMin where the walk stays above: on past the chunk)
         if (i >= len || __ballot(X.thr < INFINITY) == 0ull) break;
-        stage(i, len, index(i, len));
+        if (i >= end) end = len;
+        stage(i, end, index(i, end));
       }
       if (mine) write(X.T, X.C0, X.C1, X.C2, X.last);
     }
