@@ -27,7 +27,7 @@
 //              through global memory).
 // The slot order after step 3 depends on atomic timing; after step 4 it does
 // not.  A block whose pairs fall on at most 2048 tiles it can index (all tiles
-// of its views at low resolutions, where every tile collects thousands of
+// of its view at low resolutions, where every tile collects thousands of
 // pairs; or the bounding rectangle of its footprints' tiles, when its
 // Gaussians sit close together in space) counts in LDS first and reserves one
 // slot range per touched tile in step 3 instead, through a cursor that starts
@@ -37,7 +37,7 @@
 // workspace holds the bucketed keys, the ranks, the offsets' block sums and
 // four counts.
 //
-// The pair expansion spreads each wave's pairs evenly over its 64 lanes, so a
+// The pair expansion spreads each block's pairs evenly over its threads, so a
 // Gaussian with a footprint of thousands of tiles does not serialise on one lane.
 #include <algorithm>
 #include <mutex>
@@ -53,19 +53,43 @@ struct TileInfo {  // per view: first global tile, one past its last tile, grid 
   int32_t gw[GS_MAX_VIEWS];
 };
 
+constexpr int kXT = 256;        // threads per expansion block
+
 struct Items {  // the (view, Gaussian) items of a preprocess output
   TileInfo TI;
   const char* proj;
   size_t stride, tt_off;
   char* goff_proj;  // non-null: record each item's first pair position (at goff_off)
   size_t goff_off;
-  int64_t m;  // n_views * n
-  int n, tile;
+  int n;
+  int tile_log2;
+  int rounds;  // a block takes kXT * rounds items of one view,
+  int bpv;     // a view bpv blocks
+  // views, most tiles first: the launch's last blocks are light (16 views of mixed sizes,
+  // fewest tiles first: count and place 306 + 442 us, so 262 + 312)
+  int order[GS_MAX_VIEWS];
 };
 
-constexpr int kXT = 256;        // threads per expansion block
+// Which items a block takes.  `id` numbers the blocks in index order.
+struct BlockItems {
+  int v, id;
+  int64_t g0;  // first Gaussian
+};
+__device__ __forceinline__ BlockItems block_items(const Items& S) {
+  const int slot = int(blockIdx.x) / S.bpv, c = int(blockIdx.x) - slot * S.bpv;
+  BlockItems b;
+  b.v = S.order[slot];
+  b.id = b.v * S.bpv + c;
+  b.g0 = int64_t(c) * kXT * S.rounds;
+  return b;
+}
+
 constexpr int kAggBins = 2048;  // most tiles a block aggregates in LDS
-constexpr int kAggRounds = 8;   // items per aggregating block: at most kXT * kAggRounds
+constexpr int kAggRounds = 4;   // items per aggregating block: at most kXT * kAggRounds
+// (4 items a thread: 1024-item blocks leave the last ones of a launch less to do than
+// 2048-item blocks, 16 views of mixed sizes: 199 + 234 us against 262 + 312; 512-item
+// blocks there 142 + 238, but 434 + 780 against 400 + 720 at 16 views of 4M Gaussians,
+// with twice the blocks' positions to scan, 55 us against 30)
 // but no fewer blocks than this while items allow: each block walks its rounds
 // one after the other (load, scan, LDS bins), so 2048 blocks (8 per CU) hide
 // that latency; at 1M Gaussians on views of a few hundred tiles, 512 blocks
@@ -74,91 +98,137 @@ constexpr int kAggRounds = 8;   // items per aggregating block: at most kXT * kA
 // 4x more reservation atomics cost 1.4x
 constexpr int kAggBlocks = 2048;
 
-// Calls f(global tile id, sort key, index-order position, tile x | tile y << 16
-// in its view's grid) once for every pair of the items [first, first + kXT),
-// whose first pair sits at index-order position pbase.  Every thread of the
-// block must call it.  Returns the items' pair count.
-template <class F>
-__device__ inline uint32_t for_each_pair(const Items& S, int64_t first, uint32_t pbase, F&& f) {
-  __shared__ uint32_t s_end[kXT];   // inclusive prefix of pair counts within the wave
-  __shared__ uint32_t s_wtot[kXT / 64];
-  __shared__ uint32_t s_base[kXT];  // global id of the footprint's first tile
-  __shared__ uint32_t s_w[kXT];     // footprint width in tiles
-  __shared__ uint32_t s_gw[kXT];    // tile-grid width of the item's view
-  __shared__ uint64_t s_key[kXT];   // bits(depth) << 32 | Gaussian index
-  __shared__ uint32_t s_xy[kXT];    // footprint's first tile: x | y << 16
-  const int lane = threadIdx.x & 63, w0 = threadIdx.x & ~63;
-  const int64_t i = first + threadIdx.x;
-  uint32_t cnt = 0, base = 0, w = 1, gw = 1, xy = 0;
-  uint64_t key = 0;
-  if (i < S.m) {
-    const int64_t v = i / S.n, g = i - v * S.n;
+// An item's footprint box and depth, read once per kernel: a block's kXT * rounds
+// items stay in registers between its passes over them (their records lie 48 bytes
+// apart, so a pass over memory moves three times what it uses).
+struct Item {
+  uint32_t lo, hi, z;  // lo > hi in x: no pairs
+  __device__ bool visible() const { return box_x(lo) <= box_x(hi); }
+};
+constexpr uint32_t kNoBox = 1u;
+
+__device__ __forceinline__ Item load_item(const Items& S, int v, int64_t g) {
+  Item it{kNoBox, 0u, 0u};
+  if (g < S.n) {
     const char* pv = S.proj + size_t(v) * S.stride;
     if (reinterpret_cast<const uint32_t*>(pv + S.tt_off)[g] > 0u) {
       const float4 r2 = reinterpret_cast<const float4*>(pv)[3 * g + 2];
-      const uint32_t lo = __float_as_uint(r2.z), hi = __float_as_uint(r2.w);
-      const int tx0 = box_x(lo) / S.tile, ty0 = box_y(lo) / S.tile;
-      const int tx1 = box_x(hi) / S.tile, ty1 = box_y(hi) / S.tile;
-      w = uint32_t(tx1 - tx0 + 1);
-      cnt = w * uint32_t(ty1 - ty0 + 1);
-      gw = uint32_t(S.TI.gw[v]);
-      base = uint32_t(S.TI.tile_base[v]) + uint32_t(ty0) * gw + uint32_t(tx0);
-      xy = uint32_t(tx0) | (uint32_t(ty0) << 16);
-      key = (uint64_t(__float_as_uint(r2.y)) << 32) | uint64_t(g);
+      it.z = __float_as_uint(r2.y);
+      it.lo = __float_as_uint(r2.z);
+      it.hi = __float_as_uint(r2.w);
     }
   }
-  const uint32_t inc = wave_incl_scan(cnt);
-  if (lane == 63) s_wtot[threadIdx.x >> 6] = inc;
-  s_end[threadIdx.x] = inc;
-  s_base[threadIdx.x] = base;
-  s_w[threadIdx.x] = w;
-  s_gw[threadIdx.x] = gw;
-  s_key[threadIdx.x] = key;
-  s_xy[threadIdx.x] = xy;
+  return it;
+}
+
+// Calls f(global tile id, sort key, index-order position, tile x | tile y << 16
+// in its view's grid) once for every pair of view v's items [first, first + kXT),
+// whose first pair sits at index-order position pbase; `it` is the thread's item.
+// The pairs are dealt to the block's threads in turn, kPairs of them a thread and
+// step: f.issue() starts a pair's atomic or loads, f.commit() uses what it returned,
+// so their latencies overlap.  (One pair a step over the owning wave's lanes alone:
+// a footprint of thousands of tiles then keeps its wave, and at the end the whole
+// launch, for one round trip per 64 pairs: 16 views of mixed sizes of 1M Gaussians
+// stored by place, whose fullest block has 78 thousand pairs and its fullest wave 11
+// thousand, counted in 445 us and placed in 515 so, now in 306 and 442.)  Every thread of the block
+// must call it.  Returns the items' pair count.
+constexpr int kPairs = 4;
+
+template <class F>
+__device__ inline uint32_t for_each_pair(const Items& S, int v, int64_t first, const Item& it,
+                                         uint32_t pbase, F&& f) {
+  __shared__ uint32_t s_end[kXT];   // inclusive prefix of pair counts
+  __shared__ uint32_t s_wtot[kXT / 64];
+  __shared__ uint32_t s_base[kXT];  // global id of the footprint's first tile
+  __shared__ uint32_t s_w[kXT];     // footprint width in tiles
+  __shared__ uint64_t s_key[kXT];   // bits(depth) << 32 | Gaussian index
+  __shared__ uint32_t s_xy[kXT];    // footprint's first tile: x | y << 16
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int64_t g = first + tid;
+  const uint32_t gw = uint32_t(S.TI.gw[v]);
+  uint32_t cnt = 0, base = 0, w = 1, xy = 0;
+  uint64_t key = 0;
+  if (it.visible()) {
+    const int tx0 = box_x(it.lo) >> S.tile_log2, ty0 = box_y(it.lo) >> S.tile_log2;
+    const int tx1 = box_x(it.hi) >> S.tile_log2, ty1 = box_y(it.hi) >> S.tile_log2;
+    w = uint32_t(tx1 - tx0 + 1);
+    cnt = w * uint32_t(ty1 - ty0 + 1);
+    base = uint32_t(S.TI.tile_base[v]) + uint32_t(ty0) * gw + uint32_t(tx0);
+    xy = uint32_t(tx0) | (uint32_t(ty0) << 16);
+    key = (uint64_t(it.z) << 32) | uint64_t(g);
+  }
+  uint32_t inc = wave_incl_scan(cnt);
+  if (lane == 63) s_wtot[tid >> 6] = inc;
+  s_base[tid] = base;
+  s_w[tid] = w;
+  s_key[tid] = key;
+  s_xy[tid] = xy;
   __syncthreads();
-  const uint32_t total = __shfl(inc, 63, 64);
-  uint32_t wbase = pbase, all = 0;
+  uint32_t all = 0;
 #pragma unroll
   for (int w = 0; w < kXT / 64; ++w) {
     const uint32_t t = s_wtot[w];
-    wbase += (w < (threadIdx.x >> 6)) ? t : 0u;
+    inc += (w < (tid >> 6)) ? t : 0u;
     all += t;
   }
-  if (S.goff_proj && i < S.m) {
-    const int64_t v = i / S.n, g = i - v * S.n;
+  s_end[tid] = inc;
+  if (S.goff_proj && g < S.n)
     reinterpret_cast<uint32_t*>(S.goff_proj + size_t(v) * S.stride + S.goff_off)[g] =
-        wbase + (inc - cnt);
-  }
-  for (uint32_t j = uint32_t(lane); j < total; j += 64) {
-    // the item owning the wave's j-th pair: the first k with s_end[k] > j
-    int k = 0;
+        pbase + (inc - cnt);
+  __syncthreads();
+  for (uint32_t j0 = uint32_t(tid); j0 < all; j0 += kPairs * kXT) {
+    uint32_t t[kPairs], at[kPairs], xy[kPairs], got[kPairs];
 #pragma unroll
-    for (int step = 32; step > 0; step >>= 1)
-      if (s_end[w0 + k + step - 1] <= j) k += step;
-    const uint32_t local = j - (k > 0 ? s_end[w0 + k - 1] : 0u);
-    const uint32_t wk = s_w[w0 + k];
-    const uint32_t ty = local / wk, tx = local - ty * wk;
-    f(s_base[w0 + k] + ty * s_gw[w0 + k] + tx, s_key[w0 + k], wbase + j,
-      s_xy[w0 + k] + tx + (ty << 16));
+    for (int u = 0; u < kPairs; ++u) {
+      const uint32_t j = j0 + u * kXT;
+      if (j < all) {
+        // the item owning pair j: the first k with s_end[k] > j
+        int k = 0;
+#pragma unroll
+        for (int step = kXT / 2; step > 0; step >>= 1)
+          if (s_end[k + step - 1] <= j) k += step;
+        const uint32_t local = j - (k > 0 ? s_end[k - 1] : 0u);
+        const uint32_t wk = s_w[k];
+        const uint32_t ty = local / wk, tx = local - ty * wk;
+        at[u] = uint32_t(k);
+        t[u] = s_base[k] + ty * gw + tx;
+        xy[u] = s_xy[k] + tx + (ty << 16);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u) {
+      const uint32_t j = j0 + u * kXT;
+      if (j < all) got[u] = f.issue(t[u], pbase + j, xy[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u) {
+      const uint32_t j = j0 + u * kXT;
+      if (j < all) f.commit(got[u], s_key[at[u]], pbase + j);
+    }
   }
   __syncthreads();  // the arrays are rewritten by the next call
   return all;
 }
 
 // Pair count of each block's items (the block decomposition of k_tile_count
-// and k_bucket); k_scan_spine then turns them into each block's first
-// index-order position.
-__global__ __launch_bounds__(kXT) void k_tile_reduce(Items S, int rounds,
-                                                     uint32_t* __restrict__ block_pairs) {
+// and k_bucket), from which block_first (or, for many blocks, k_scan_spine) forms
+// each block's first index-order position.  Also clears the tiles' counters
+// (p[0, np), and their copies q[0, nq)) for k_tile_count.
+__global__ __launch_bounds__(kXT) void k_tile_reduce(Items S, uint32_t* __restrict__ block_pairs,
+                                                     uint32_t* __restrict__ p, int64_t np,
+                                                     uint32_t* __restrict__ q, int64_t nq) {
   __shared__ uint32_t s_w[kXT / 64];
-  const int64_t i0 = int64_t(blockIdx.x) * kXT * rounds;
+  const int64_t t0 = int64_t(blockIdx.x) * kXT + threadIdx.x, nt = int64_t(gridDim.x) * kXT;
+  for (int64_t i = t0; i < np; i += nt) p[i] = 0u;
+  for (int64_t i = t0; i < nq; i += nt) q[i] = 0u;
+  if (S.n == 0) return;
+  const BlockItems B = block_items(S);
+  const uint32_t* tt =
+      reinterpret_cast<const uint32_t*>(S.proj + size_t(B.v) * S.stride + S.tt_off);
   uint32_t acc = 0;
-  for (int r = 0; r < rounds; ++r) {
-    const int64_t i = i0 + int64_t(r) * kXT + threadIdx.x;
-    if (i < S.m) {
-      const int64_t v = i / S.n, g = i - v * S.n;
-      acc += reinterpret_cast<const uint32_t*>(S.proj + size_t(v) * S.stride + S.tt_off)[g];
-    }
+  for (int r = 0; r < S.rounds; ++r) {
+    const int64_t g = B.g0 + int64_t(r) * kXT + threadIdx.x;
+    if (g < S.n) acc += tt[g];
   }
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) acc += uint32_t(__shfl_xor(int(acc), d, 64));
@@ -168,59 +238,120 @@ __global__ __launch_bounds__(kXT) void k_tile_reduce(Items S, int rounds,
     uint32_t t = 0;
 #pragma unroll
     for (int w = 0; w < kXT / 64; ++w) t += s_w[w];
-    block_pairs[blockIdx.x] = t;
+    block_pairs[B.id] = t;
   }
 }
 
-// A block takes kXT * rounds consecutive items.  It counts its pairs per tile
-// in LDS first and issues one global atomic per touched tile when its pairs
-// fall on at most agg_bins tiles that it can index:
-//   - all tiles of the views its items belong to (low resolutions, where
+// Many blocks: their pair counts into their first index-order positions, in place.
+// One block, kSpineItems counts a thread and step, a wave's 64 kSpineItems in a row.
+constexpr int kSpineThreads = 1024;
+constexpr int kSpineItems = 16;
+
+__global__ __launch_bounds__(kSpineThreads) void k_tile_spine(uint32_t* __restrict__ pos, int n) {
+  __shared__ uint32_t s_w[kSpineThreads / 64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t carry = 0;
+  for (int base = 0; base < n; base += kSpineThreads * kSpineItems) {
+    const int i0 = base + wv * 64 * kSpineItems + lane;
+    uint32_t c[kSpineItems], inc[kSpineItems], s = 0;
+#pragma unroll
+    for (int k = 0; k < kSpineItems; ++k) c[k] = i0 + 64 * k < n ? pos[i0 + 64 * k] : 0u;
+#pragma unroll
+    for (int k = 0; k < kSpineItems; ++k) inc[k] = wave_incl_scan(c[k]);
+#pragma unroll
+    for (int k = 0; k < kSpineItems; ++k) {
+      const uint32_t t = __shfl(inc[k], 63, 64);
+      inc[k] += s;
+      s += t;
+    }
+    if (lane == 0) s_w[wv] = s;
+    __syncthreads();
+    uint32_t before = carry, all = 0;
+#pragma unroll
+    for (int q = 0; q < kSpineThreads / 64; ++q) {
+      const uint32_t t = s_w[q];
+      before += q < wv ? t : 0u;
+      all += t;
+    }
+#pragma unroll
+    for (int k = 0; k < kSpineItems; ++k)
+      if (i0 + 64 * k < n) pos[i0 + 64 * k] = before + inc[k] - c[k];
+    carry += all;
+    __syncthreads();  // s_w is rewritten by the next step
+  }
+}
+
+// The block's first index-order position: `pos` holds the blocks' positions when
+// `scanned`, else their pair counts, which every block adds up to its own: up to
+// kSpineBlocks of them, 16 loads a thread from L2, that costs less than a launch
+// of one block between the two kernels (10 us with it at 1M Gaussians, 2 without).  Every thread of the block
+// must call it.
+constexpr unsigned kSpineBlocks = 4096;
+
+__device__ inline uint32_t block_first(const uint32_t* __restrict__ pos, int id, bool scanned) {
+  if (scanned) return pos[id];
+  __shared__ uint32_t s_p[kXT / 64];
+  uint32_t acc = 0;
+  for (unsigned j = threadIdx.x; int(j) < id; j += kXT) acc += pos[j];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) acc += uint32_t(__shfl_xor(int(acc), d, 64));
+  if ((threadIdx.x & 63) == 0) s_p[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  acc = 0;
+#pragma unroll
+  for (int w = 0; w < kXT / 64; ++w) acc += s_p[w];
+  return acc;
+}
+
+// A block takes kXT * rounds consecutive items of a view.  It counts its pairs per
+// tile in LDS first and issues one global atomic per touched tile when its pairs
+// fall on at most kAggBins tiles that it can index:
+//   - all tiles of the view (low resolutions, where
 //     every tile collects thousands of pairs and same-counter atomics
-//     serialise), bin = tile - first tile of those views; or
-//   - for items of one view, the bounding rectangle of their footprints'
+//     serialise), bin = tile - first tile of the view; or
+//   - the bounding rectangle of their footprints'
 //     tiles (Gaussians stored close together in space, as the spatial order
 //     stores them, cover few tiles), bin = row-major cell of that rectangle.
 // Otherwise every pair goes to the global counters and ranks itself there.
-struct BlockSpan {
-  int64_t i0, i1;    // items
-  int32_t mode;      // 0: global counters, 1: the views' tiles, 2: the rectangle
-  int32_t t_lo;      // mode 1: first tile of the block's views
-  int32_t bx0, by0, bw, gw, base;  // mode 2: rectangle origin and width; view grid
+struct BlockSpan : BlockItems {
+  int32_t mode;      // 0: global counters, 1: the view's tiles, 2: the rectangle
+  int32_t bx0, by0, bw, gw, base;  // mode 2: rectangle origin and width; view's grid
   int32_t span;      // bins in use
   __device__ int bin(uint32_t t, uint32_t xy) const {
-    return mode == 1 ? int(t) - t_lo
+    return mode == 1 ? int(t) - base
                      : (int(xy >> 16) - by0) * bw + (int(xy & 0xffffu) - bx0);
   }
   __device__ uint32_t tile_of(int b) const {
-    if (mode == 1) return uint32_t(t_lo + b);
+    if (mode == 1) return uint32_t(base + b);
     const int y = b / bw, x = b - y * bw;
     return uint32_t(base + (by0 + y) * gw + bx0 + x);
   }
 };
 
-// every thread of the block must call it
-__device__ inline BlockSpan block_span(const Items& S, int rounds, int agg_bins) {
+// Loads the block's items (the thread's are it[0, rounds)) and decides its mode; every
+// thread of the block must call it.
+template <int R>
+__device__ inline BlockSpan block_span(const Items& S, Item (&it)[R]) {
   BlockSpan b{};
-  b.i0 = int64_t(blockIdx.x) * kXT * rounds;
-  b.i1 = (b.i0 + int64_t(kXT) * rounds < S.m) ? b.i0 + int64_t(kXT) * rounds : S.m;
-  const int v0 = int(b.i0 / S.n), v1 = int((b.i1 - 1) / S.n);
-  b.t_lo = S.TI.tile_base[v0];
-  b.span = S.TI.tile_end[v1] - b.t_lo;
-  b.mode = b.span <= agg_bins ? 1 : 0;
-  if (b.mode == 1 || v0 != v1 || agg_bins == 0) return b;  // block-uniform
+  static_cast<BlockItems&>(b) = block_items(S);
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    it[r] = r < S.rounds ? load_item(S, b.v, b.g0 + int64_t(r) * kXT + threadIdx.x)
+                         : Item{kNoBox, 0u, 0u};
+  b.gw = S.TI.gw[b.v];
+  b.base = S.TI.tile_base[b.v];
+  b.span = S.TI.tile_end[b.v] - b.base;
+  b.mode = b.span <= kAggBins ? 1 : 0;
+  if (b.mode == 1) return b;  // block-uniform
   // the tile rectangle of the block's footprints
   int x0 = 1 << 30, y0 = 1 << 30, x1 = -1, y1 = -1;
-  const char* pv = S.proj + size_t(v0) * S.stride;
-  for (int64_t i = b.i0 + threadIdx.x; i < b.i1; i += kXT) {
-    const int64_t g = i - int64_t(v0) * S.n;
-    if (reinterpret_cast<const uint32_t*>(pv + S.tt_off)[g] > 0u) {
-      const float4 r2 = reinterpret_cast<const float4*>(pv)[3 * g + 2];
-      const uint32_t lo = __float_as_uint(r2.z), hi = __float_as_uint(r2.w);
-      x0 = min(x0, box_x(lo) / S.tile);
-      y0 = min(y0, box_y(lo) / S.tile);
-      x1 = max(x1, box_x(hi) / S.tile);
-      y1 = max(y1, box_y(hi) / S.tile);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (it[r].visible()) {
+      x0 = min(x0, box_x(it[r].lo) >> S.tile_log2);
+      y0 = min(y0, box_y(it[r].lo) >> S.tile_log2);
+      x1 = max(x1, box_x(it[r].hi) >> S.tile_log2);
+      y1 = max(y1, box_y(it[r].hi) >> S.tile_log2);
     }
   }
 #pragma unroll
@@ -246,13 +377,11 @@ __device__ inline BlockSpan block_span(const Items& S, int rounds, int agg_bins)
     y1 = max(y1, s_r[3][w]);
   }
   __syncthreads();  // s_r is rewritten by the next call
-  if (x1 >= x0 && int64_t(x1 - x0 + 1) * (y1 - y0 + 1) <= agg_bins) {
+  if (x1 >= x0 && int64_t(x1 - x0 + 1) * (y1 - y0 + 1) <= kAggBins) {
     b.mode = 2;
     b.bx0 = x0;
     b.by0 = y0;
     b.bw = x1 - x0 + 1;
-    b.gw = S.TI.gw[v0];
-    b.base = S.TI.tile_base[v0];
     b.span = b.bw * (y1 - y0 + 1);
   }
   return b;
@@ -267,31 +396,73 @@ __device__ __forceinline__ uint32_t* agg_counter(uint32_t* ranges, uint32_t* cop
   return copies ? copies + (blockIdx.x % kXcds) * kAggBins + t : ranges + 2 * size_t(t) + 1;
 }
 
-__global__ __launch_bounds__(kXT) void k_tile_count(Items S, int rounds, int agg_bins,
+// ---- what the passes do with a pair
+struct CountLds {  // count it in the block's bins
+  const BlockSpan& B;
+  uint32_t* bins;
+  __device__ uint32_t issue(uint32_t t, uint32_t, uint32_t xy) const {
+    atomicAdd(&bins[B.bin(t, xy)], 1u);
+    return 0u;
+  }
+  __device__ void commit(uint32_t, uint64_t, uint32_t) const {}
+};
+struct CountRank {  // the returned count is the pair's rank among its tile's ranked pairs
+  uint32_t* ranges;
+  uint32_t* rank;
+  int64_t cap;
+  __device__ uint32_t issue(uint32_t t, uint32_t, uint32_t) const {
+    return atomicAdd(&ranges[2 * size_t(t)], 1u);
+  }
+  __device__ void commit(uint32_t got, uint64_t, uint32_t p) const {
+    if (int64_t(p) < cap) rank[p] = got;
+  }
+};
+struct PlaceLds {  // the next slot of the block's reservation
+  const BlockSpan& B;
+  uint32_t* bins;
+  uint64_t* bucket;
+  __device__ uint32_t issue(uint32_t t, uint32_t, uint32_t xy) const {
+    return atomicAdd(&bins[B.bin(t, xy)], 1u);
+  }
+  __device__ void commit(uint32_t got, uint64_t key, uint32_t) const { bucket[got] = key; }
+};
+struct PlaceRank {
+  const uint32_t* ranges;
+  const uint32_t* rank;
+  uint64_t* bucket;
+  __device__ uint32_t issue(uint32_t t, uint32_t p, uint32_t) const {
+    return ranges[2 * size_t(t)] + rank[p];
+  }
+  __device__ void commit(uint32_t got, uint64_t key, uint32_t) const { bucket[got] = key; }
+};
+
+template <int R>
+__global__ __launch_bounds__(kXT) void k_tile_count(Items S,
                                                     const uint32_t* __restrict__ block_pos,
-                                                    int64_t cap, uint32_t* __restrict__ ranges,
+                                                    bool scanned, int64_t cap,
+                                                    uint32_t* __restrict__ ranges,
                                                     uint32_t* __restrict__ rank,
                                                     uint32_t* __restrict__ copies) {
   extern __shared__ uint32_t s_bins[];
-  const BlockSpan B = block_span(S, rounds, agg_bins);
+  Item it[R];
+  const BlockSpan B = block_span(S, it);
+  uint32_t pos = block_first(block_pos, B.id, scanned);  // for the items' pair offsets
   if (B.mode) {
     for (int b = threadIdx.x; b < B.span; b += kXT) s_bins[b] = 0u;
     __syncthreads();
-    uint32_t pos = block_pos[blockIdx.x];  // for the items' pair offsets
-    for (int64_t c = B.i0; c < B.i1; c += kXT)
-      pos += for_each_pair(S, c, pos, [&](uint32_t t, uint64_t, uint32_t, uint32_t xy) {
-        atomicAdd(&s_bins[B.bin(t, xy)], 1u);
-      });
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r < S.rounds)
+        pos += for_each_pair(S, B.v, B.g0 + int64_t(r) * kXT, it[r], pos, CountLds{B, s_bins});
     for (int b = threadIdx.x; b < B.span; b += kXT)
       if (s_bins[b]) atomicAdd(agg_counter(ranges, copies, B.tile_of(b)), s_bins[b]);
   } else {
     // the returned count is the pair's rank among its tile's ranked pairs
-    uint32_t pos = block_pos[blockIdx.x];
-    for (int64_t c = B.i0; c < B.i1; c += kXT)
-      pos += for_each_pair(S, c, pos, [&](uint32_t t, uint64_t, uint32_t p, uint32_t) {
-        const uint32_t r = atomicAdd(&ranges[2 * size_t(t)], 1u);
-        if (int64_t(p) < cap) rank[p] = r;
-      });
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r < S.rounds)
+        pos += for_each_pair(S, B.v, B.g0 + int64_t(r) * kXT, it[r], pos,
+                             CountRank{ranges, rank, cap});
   }
 }
 
@@ -299,23 +470,26 @@ __global__ __launch_bounds__(kXT) void k_tile_count(Items S, int rounds, int agg
 // first slot plus its rank; with LDS bins the block first reserves one
 // contiguous slot range per touched tile from the tile's cursor (which starts
 // after the ranked pairs), then ranks its pairs inside it with LDS atomics.
-__global__ __launch_bounds__(kXT) void k_bucket(Items S, int rounds, int agg_bins,
+template <int R>
+__global__ __launch_bounds__(kXT) void k_bucket(Items S,
                                                 const int64_t* __restrict__ n_eff,
                                                 const uint32_t* __restrict__ block_pos,
+                                                bool scanned,
                                                 const uint32_t* __restrict__ rank,
                                                 uint32_t* __restrict__ ranges,
                                                 uint32_t* __restrict__ copies,
                                                 uint64_t* __restrict__ bucket) {
   extern __shared__ uint32_t s_bins[];
   if (*n_eff == 0) return;  // capacity overflow (or no pairs): nothing to place
-  const BlockSpan B = block_span(S, rounds, agg_bins);
+  Item it[R];
+  const BlockSpan B = block_span(S, it);
   if (B.mode) {
     for (int b = threadIdx.x; b < B.span; b += kXT) s_bins[b] = 0u;
     __syncthreads();
-    for (int64_t c = B.i0; c < B.i1; c += kXT)
-      for_each_pair(S, c, 0u, [&](uint32_t t, uint64_t, uint32_t, uint32_t xy) {
-        atomicAdd(&s_bins[B.bin(t, xy)], 1u);
-      });
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r < S.rounds)
+        for_each_pair(S, B.v, B.g0 + int64_t(r) * kXT, it[r], 0u, CountLds{B, s_bins});
     // a thread's bins are b = t + u kXT, u < kAggBins / kXT: all their
     // reservation atomics are issued before the first result is used, so the
     // returns' latencies overlap
@@ -333,16 +507,17 @@ __global__ __launch_bounds__(kXT) void k_bucket(Items S, int rounds, int agg_bin
       if (b < B.span && s_bins[b]) s_bins[b] = got[u];
     }
     __syncthreads();
-    for (int64_t c = B.i0; c < B.i1; c += kXT)
-      for_each_pair(S, c, 0u, [&](uint32_t t, uint64_t key, uint32_t, uint32_t xy) {
-        bucket[atomicAdd(&s_bins[B.bin(t, xy)], 1u)] = key;
-      });
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r < S.rounds)
+        for_each_pair(S, B.v, B.g0 + int64_t(r) * kXT, it[r], 0u, PlaceLds{B, s_bins, bucket});
   } else {
-    uint32_t pos = block_pos[blockIdx.x];
-    for (int64_t c = B.i0; c < B.i1; c += kXT)
-      pos += for_each_pair(S, c, pos, [&](uint32_t t, uint64_t key, uint32_t p, uint32_t) {
-        bucket[ranges[2 * size_t(t)] + rank[p]] = key;
-      });
+    uint32_t pos = block_first(block_pos, B.id, scanned);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r < S.rounds)
+        pos += for_each_pair(S, B.v, B.g0 + int64_t(r) * kXT, it[r], pos,
+                             PlaceRank{ranges, rank, bucket});
   }
 }
 
@@ -354,7 +529,6 @@ __global__ __launch_bounds__(kXT) void k_bucket(Items S, int rounds, int agg_bin
 // the pair total, and whether it fits the capacity.  Sums are 64-bit, so an
 // overflowing total is always detected.
 constexpr int kTS = 1024;
-constexpr int kTSItems = 8;
 
 __device__ inline uint64_t wave_incl_scan64(uint64_t x) {
   const int lane = threadIdx.x & 63;
@@ -366,6 +540,11 @@ __device__ inline uint64_t wave_incl_scan64(uint64_t x) {
   return x;
 }
 
+// Bound by the latency of one block's steps: a wave takes 64 ITEMS tiles in a row, 64 a
+// load (ITEMS 2, or 8 for more than 2 kTS tiles), and a step's loads run under the one
+// before: 8 us at 950 tiles, 37 at 35768, 80 at 81600 (15, 56 and 138 with eight
+// consecutive tiles a thread, one load per 64 cache lines).
+template <int ITEMS>
 __global__ __launch_bounds__(kTS) void k_tile_scan(uint32_t* __restrict__ ranges,
                                                    uint32_t* __restrict__ copies, int n_tiles,
                                                    int64_t* __restrict__ proj_total,
@@ -376,30 +555,47 @@ __global__ __launch_bounds__(kTS) void k_tile_scan(uint32_t* __restrict__ ranges
                                                    int64_t* __restrict__ n_pairs_user) {
   __shared__ uint64_t s_w[kTS / 64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  uint64_t carry = 0;
-  for (int base = 0; base < n_tiles; base += kTS * kTSItems) {
-    const int i0 = base + threadIdx.x * kTSItems;
-    uint32_t c[kTSItems], cr[kTSItems];
-    uint64_t s = 0;
+  uint32_t cr[ITEMS], ag[ITEMS];  // ranked pairs, LDS-counted pairs
+  auto load = [&](int i0) {
 #pragma unroll
-    for (int k = 0; k < kTSItems; ++k) {
-      cr[k] = (i0 + k < n_tiles) ? ranges[2 * size_t(i0 + k)] : 0u;
-      uint32_t agg = 0u;
-      if (i0 + k < n_tiles) {
+    for (int k = 0; k < ITEMS; ++k) {
+      const int i = i0 + 64 * k;
+      cr[k] = ag[k] = 0u;
+      if (i < n_tiles) {
+        cr[k] = ranges[2 * size_t(i)];
         if (copies) {
 #pragma unroll
-          for (int x = 0; x < kXcds; ++x) agg += copies[x * kAggBins + i0 + k];
+          for (int x = 0; x < kXcds; ++x) ag[k] += copies[x * kAggBins + i];
         } else {
-          agg = ranges[2 * size_t(i0 + k) + 1];
+          ag[k] = ranges[2 * size_t(i) + 1];
         }
       }
-      c[k] = cr[k] + agg;
-      s += c[k];
     }
-    const uint64_t inc = wave_incl_scan64(s);
-    if (lane == 63) s_w[wv] = inc;
+  };
+  int i0 = wv * 64 * ITEMS + lane;
+  load(i0);
+  uint64_t carry = 0;
+  for (int base = 0; base < n_tiles; base += kTS * ITEMS) {
+    uint32_t r[ITEMS];
+    uint64_t c[ITEMS], inc[ITEMS], s = 0;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+      r[k] = cr[k];
+      c[k] = uint64_t(cr[k]) + ag[k];
+      inc[k] = wave_incl_scan64(c[k]);
+    }
+    const int i = i0;
+    i0 += kTS * ITEMS;
+    if (base + kTS * ITEMS < n_tiles) load(i0);
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+      const uint64_t t = __shfl(inc[k], 63, 64);
+      inc[k] += s;
+      s += t;
+    }
+    if (lane == 0) s_w[wv] = s;
     __syncthreads();
-    uint64_t before = 0, tot = 0;
+    uint64_t before = carry, tot = 0;
 #pragma unroll
     for (int q = 0; q < kTS / 64; ++q) {
       const uint64_t t = s_w[q];
@@ -407,23 +603,23 @@ __global__ __launch_bounds__(kTS) void k_tile_scan(uint32_t* __restrict__ ranges
       tot += t;
     }
     __syncthreads();
-    uint64_t ex = carry + before + inc - s;
 #pragma unroll
-    for (int k = 0; k < kTSItems; ++k) {
-      if (i0 + k < n_tiles) {
-        ranges[2 * size_t(i0 + k)] = uint32_t(ex);
-        ranges[2 * size_t(i0 + k) + 1] = uint32_t(ex + cr[k]);
+    for (int k = 0; k < ITEMS; ++k) {
+      const int t = i + 64 * k;
+      if (t < n_tiles) {
+        const uint64_t ex = before + inc[k] - c[k];
+        ranges[2 * size_t(t)] = uint32_t(ex);
+        ranges[2 * size_t(t) + 1] = uint32_t(ex + r[k]);
         if (copies) {
-          uint32_t cur = uint32_t(ex + cr[k]);
+          uint32_t cur = uint32_t(ex + r[k]);
 #pragma unroll
           for (int x = 0; x < kXcds; ++x) {
-            const uint32_t a = copies[x * kAggBins + i0 + k];
-            copies[x * kAggBins + i0 + k] = cur;
+            const uint32_t a = copies[x * kAggBins + t];
+            copies[x * kAggBins + t] = cur;
             cur += a;
           }
         }
       }
-      ex += c[k];
     }
     carry += tot;
   }
@@ -834,28 +1030,16 @@ __global__ __launch_bounds__(kBigThreads) void k_tile_sort_big(
   }
 }
 
-// value into p[0, count) and q[0, count_q)
-__global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, int64_t count,
-                                                  uint32_t value, uint32_t* __restrict__ q,
-                                                  int64_t count_q) {
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < count;
-       i += int64_t(gridDim.x) * blockDim.x)
-    p[i] = value;
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < count_q;
-       i += int64_t(gridDim.x) * blockDim.x)
-    q[i] = value;
-}
-
 struct WsLayout {
   size_t cnt, copies, bucket, rank, bpos, total;
-  WsLayout(int64_t m, int64_t cap) {
+  WsLayout(int64_t n_views, int64_t n, int64_t cap) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t r = o; o += align256(bytes); return r; };
     cnt = take(8 * 4);
     copies = take(4 * size_t(kXcds) * kAggBins);
     bucket = take(8 * size_t(cap));
     rank = take(4 * size_t(cap));
-    bpos = take(4 * (size_t((m + kXT - 1) / kXT) + 1));  // per expansion block
+    bpos = take(4 * (size_t(n_views * ((n + kXT - 1) / kXT)) + 1));  // per expansion block
     total = o;
   }
 };
@@ -869,7 +1053,7 @@ constexpr size_t align256c(size_t x) { return (x + 255) & ~size_t(255); }
 constexpr size_t kNoAllocBytes =
     256 + align256c(4 * size_t(kXcds) * kAggBins) + align256c(8 * size_t(GS_BIN_SORT_NOALLOC_MAX_PAIRS)) +
     align256c(4 * size_t(GS_BIN_SORT_NOALLOC_MAX_PAIRS)) +
-    align256c(4 * (size_t(GS_BIN_SORT_NOALLOC_MAX_ITEMS + kXT - 1) / kXT + 1));
+    align256c(4 * (size_t(GS_BIN_SORT_NOALLOC_MAX_ITEMS + kXT - 1) / kXT + GS_MAX_VIEWS + 1));
 static __device__ __align__(256) char scratch[kNoAllocBytes];
 
 constexpr int kMaxDevices = 64;
@@ -898,7 +1082,7 @@ hipError_t scratch_address(void** out) {
 }  // namespace
 
 size_t bin_sort_ws_bytes(int n_views, int n, int64_t cap) {
-  return WsLayout(int64_t(n_views) * n, cap).total;
+  return WsLayout(n_views, n, cap).total;
 }
 
 hipError_t launch_bin_sort_noalloc(const Views& V, int n, char* proj, int64_t cap,
@@ -906,7 +1090,7 @@ hipError_t launch_bin_sort_noalloc(const Views& V, int n, char* proj, int64_t ca
                                    int64_t* n_pairs_dev, hipStream_t st) {
   const int64_t m = int64_t(V.n_views) * n;
   if (cap < 0 || cap > GS_BIN_SORT_NOALLOC_MAX_PAIRS || m > GS_BIN_SORT_NOALLOC_MAX_ITEMS ||
-      WsLayout(m, cap).total > kNoAllocBytes)
+      WsLayout(V.n_views, n, cap).total > kNoAllocBytes)
     return hipErrorInvalidValue;  // the caller rejects this first
   void* ws = nullptr;
   const hipError_t e = scratch_address(&ws);
@@ -921,7 +1105,7 @@ hipError_t launch_bin_sort_noalloc(const Views& V, int n, char* proj, int64_t ca
 hipError_t launch_bin_sort(const Views& V, int n, char* proj, int64_t cap, void* ws_,
                            uint64_t* keys, uint32_t* vals, uint32_t* ranges,
                            int64_t* n_pairs_dev, hipStream_t st) {
-  const WsLayout W(int64_t(V.n_views) * n, cap);
+  const WsLayout W(V.n_views, n, cap);
   char* ws = static_cast<char*>(ws_);
   int64_t* counts = reinterpret_cast<int64_t*>(ws + W.cnt);
   int64_t* n_tot = counts + 0;
@@ -946,50 +1130,53 @@ hipError_t launch_bin_sort(const Views& V, int n, char* proj, int64_t cap, void*
   S.tt_off = L.tt;
   S.goff_proj = proj;  // the count pass records the items' pair offsets
   S.goff_off = L.goff;
-  S.m = int64_t(V.n_views) * n;
   S.n = n;
-  S.tile = V.tile;
+  S.tile_log2 = V.tile == 8 ? 3 : V.tile == 16 ? 4 : 5;
   const int T = V.total_tiles;
   const int64_t nr = 2 * int64_t(T);
   // LDS aggregation pays where views have few tiles; blocks then take more
   // items (fewer global atomics), as long as the grid still fills the chip:
   // a small scene keeps one round per block
   const bool any_agg = min_view_tiles <= kAggBins;
-  int rounds = 1;
+  S.rounds = 1;
+  const int64_t m = int64_t(V.n_views) * n;
   if (any_agg) {
-    const int64_t want = (S.m + int64_t(kXT) * kAggBlocks - 1) / (int64_t(kXT) * kAggBlocks);
-    rounds = int(std::min<int64_t>(std::max<int64_t>(want, 1), kAggRounds));
+    const int64_t want = (m + int64_t(kXT) * kAggBlocks - 1) / (int64_t(kXT) * kAggBlocks);
+    S.rounds = int(std::min<int64_t>(std::max<int64_t>(want, 1), kAggRounds));
   }
-  // every launch may aggregate: whole views of few tiles, or the tile rectangle
-  // of a block of Gaussians that sit close together
+  S.bpv = int((int64_t(n) + int64_t(kXT) * S.rounds - 1) / (int64_t(kXT) * S.rounds));
+  for (int v = 0; v < V.n_views; ++v) S.order[v] = v;
+  std::stable_sort(S.order, S.order + V.n_views, [&](int a, int b) {
+    return V.v[a].gw * V.v[a].gh > V.v[b].gw * V.v[b].gh;
+  });
   const size_t agg_lds = sizeof(uint32_t) * kAggBins;
-  const int agg_bins = kAggBins;
-  const unsigned xb = unsigned((S.m + int64_t(kXT) * rounds - 1) / (int64_t(kXT) * rounds));
+  const unsigned xb = unsigned(S.bpv) * unsigned(V.n_views);
 
   // launches of at most kAggBins tiles spread the LDS-counting blocks'
   // reservation atomics over kXcds counter copies
   uint32_t* copies = (T <= kAggBins) ? copies_ws : nullptr;
   const int64_t nc = copies ? int64_t(kXcds) * kAggBins : 0;
-  GS_LAUNCH("k_fill_u32", k_fill_u32, dim3(unsigned(nr / 256 + 1 < 4096 ? nr / 256 + 1 : 4096)),
-            dim3(256), 0, st, ranges, nr, 0u, copies, nc);
-  if (xb > 0) {
-    // index-order positions of each block's first pair: ranked pairs store
-    // their ranks there, and every item's pair offset (recorded in proj for
-    // the backward) follows from them
-    GS_LAUNCH("k_tile_reduce", k_tile_reduce, dim3(xb), dim3(kXT), 0, st, S, rounds, bpos);
-    GS_LAUNCH("k_scan_spine", k_scan_spine, dim3(1), dim3(kScanThreads), 0, st, bpos,
-              Count{nullptr, int64_t(xb) * kScanTile}, nullptr, nullptr);
-    GS_LAUNCH("k_tile_count", k_tile_count, dim3(xb), dim3(kXT), agg_lds, st, S, rounds, agg_bins,
-              bpos, cap, ranges, rank, copies);
-  }
+  // every block's first index-order position: ranked pairs store
+  // their ranks there, and every item's pair offset (recorded in proj for
+  // the backward) follows from them
+  GS_LAUNCH("k_tile_reduce", k_tile_reduce, dim3(xb > 0 ? xb : 1u), dim3(kXT), 0, st, S, bpos,
+            ranges, nr, copies, nc);
+  const bool scanned = xb > kSpineBlocks;
+  if (scanned)
+    GS_LAUNCH("k_tile_spine", k_tile_spine, dim3(1), dim3(kSpineThreads), 0, st, bpos, int(xb));
+  if (xb > 0)
+    GS_LAUNCH("k_tile_count", (S.rounds == 1 ? k_tile_count<1> : k_tile_count<kAggRounds>), dim3(xb),
+              dim3(kXT), agg_lds, st, S, bpos, scanned, cap, ranges, rank,
+              copies);
   int64_t* proj_total = proj ? reinterpret_cast<int64_t*>(proj + L.total) : nullptr;
-  GS_LAUNCH("k_tile_scan", k_tile_scan, dim3(1), dim3(kTS), 0, st, ranges, copies, T, proj_total,
-            cap, n_tot, n_eff, n_long, n_mid, n_pairs_dev);
+  GS_LAUNCH("k_tile_scan", (T <= 2 * kTS ? k_tile_scan<2> : k_tile_scan<4>), dim3(1), dim3(kTS), 0,
+            st, ranges, copies, T, proj_total, cap, n_tot, n_eff, n_long, n_mid, n_pairs_dev);
   Items Sb = S;
   Sb.goff_proj = nullptr;
   if (xb > 0)
-    GS_LAUNCH("k_bucket", k_bucket, dim3(xb), dim3(kXT), agg_lds, st, Sb, rounds, agg_bins, n_eff,
-              bpos, rank, ranges, copies, bucket);
+    GS_LAUNCH("k_bucket", (S.rounds == 1 ? k_bucket<1> : k_bucket<kAggRounds>), dim3(xb), dim3(kXT),
+              agg_lds, st, Sb, n_eff, bpos, scanned, rank, ranges, copies,
+              bucket);
   GS_LAUNCH("k_tile_sort_wave", k_tile_sort_wave, dim3(unsigned((T + 3) / 4)), dim3(256), 0, st,
             T, n_tot, n_eff, n_mid, n_long, bucket, vals, keys, ranges);
   GS_LAUNCH("k_tile_sort_mid", k_tile_sort_mid, dim3(unsigned(T < kMidBlocks ? T : kMidBlocks)),
