@@ -18,12 +18,12 @@ def densify_step(params: dict, m: dict, v: dict, accum: torch.Tensor, count: tor
     n = params["means"].shape[0]
     dev = params["means"].device
     ws = torch.empty(max(gsmi.gs_densify_workspace_bytes(n), 16), dtype=torch.uint8, device=dev)
-    counts = torch.zeros(2, dtype=torch.int64, device=dev)
+    counts = torch.empty(2, dtype=torch.int64, device=dev)
     gsmi.gs_densify_classify(n, accum, count, params["opacity_logits"], grad_thr, min_opacity,
                              ws, counts, stream)
     n_pruned, n_cand = (int(x) for x in counts.cpu())
     k = int(max(0, min(int(k_of(n - n_pruned, n_cand)), n_cand)))
-    n_new_dev = torch.zeros(1, dtype=torch.int64, device=dev)
+    n_new_dev = torch.empty(1, dtype=torch.int64, device=dev)
     gsmi.gs_densify_plan(n, k, n_cand, params["log_scales"], max_scale, ws, n_new_dev, stream)
     n_new = int(n_new_dev.item())
     newp = {name: torch.empty((n_new,) + tuple(params[name].shape[1:]), dtype=torch.float32,
