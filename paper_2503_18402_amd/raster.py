@@ -173,7 +173,11 @@ class RasterizeFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, dL_dimage):
-        g = render_backward(ctx.params, ctx.frame, dL_dimage.float(), mean2d_abs=ctx.mean2d_abs)
+        # written, not added to zeros, unless the statistic is to be added to
+        g = None if ctx.mean2d_abs is not None else {k: torch.empty_like(v)
+                                                     for k, v in ctx.params.items()}
+        g = render_backward(ctx.params, ctx.frame, dL_dimage.float(), grads=g,
+                            mean2d_abs=ctx.mean2d_abs, accumulate=g is None)
         return g["means"], g["log_scales"], g["quats"], g["opacity_logits"], g["sh"], None
 
 
