@@ -18,13 +18,12 @@
 //   3. bucket: every pair stores the 64-bit sort key
 //              (bits(depth_f32) << 32) | Gaussian index at its tile's first
 //              slot plus its rank: no atomics;
-//   4. sort:   each tile's keys are sorted by a bitonic network and the
-//              values written (and the keys when asked for): lists of up to
+//   4. sort:   each tile's keys are sorted by a bitonic network on 32-bit words and
+//              the values written (and the keys when asked for): lists of up to
 //              512 keys by one wave in registers, up to 2048 by a 256-thread
 //              block in registers with LDS exchanges for the strides that
-//              cross waves, longer ones by a 1024-thread block in LDS (lists
-//              longer than one LDS chunk also run the network's long strides
-//              through global memory).
+//              cross waves, longer ones by a 1024-thread block (lists of more
+//              than 8192 keys merge their sorted chunks on the 64-bit keys).
 // The slot order after step 3 depends on atomic timing; after step 4 it does
 // not.  A block whose pairs fall on at most 2048 tiles it can index (all tiles
 // of its view at low resolutions, where every tile collects thousands of
@@ -699,7 +698,7 @@ __device__ __forceinline__ void cx(uint64_t& a, uint64_t& b) {
 
 // lane l reads lane l ^ M.  Within a row of 16 lanes the exchange runs on the
 // DPP path of the VALU (xor 1, 2, 3: quad permutes; 7, 15: half-row and row
-// mirrors), within 32 lanes as a swizzle (xor 4, 8, 16, 31), otherwise as a
+// mirrors; 8: a rotation), within 32 lanes as a swizzle (xor 4, 16, 31), otherwise as a
 // permute through the LDS crossbar
 template <int M>
 __device__ __forceinline__ uint32_t xor_lane(uint32_t x) {
@@ -708,6 +707,7 @@ __device__ __forceinline__ uint32_t xor_lane(uint32_t x) {
   else if constexpr (M == 2) return uint32_t(__builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true));
   else if constexpr (M == 3) return uint32_t(__builtin_amdgcn_update_dpp(0, v, 0x1B, 0xF, 0xF, true));
   else if constexpr (M == 7) return uint32_t(__builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true));
+  else if constexpr (M == 8) return uint32_t(__builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true));
   else if constexpr (M == 15) return uint32_t(__builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true));
   else if constexpr (M < 32) return uint32_t(__builtin_amdgcn_ds_swizzle(v, (M << 10) | 0x1F));
   else return uint32_t(__shfl_xor(v, M, 64));
@@ -860,6 +860,241 @@ __device__ inline void block_reg_sort(uint64_t (&k)[8], uint32_t len, uint64_t* 
   }
 }
 
+// ---- lists sorted as 32-bit words.  A comparator of 64-bit keys costs a compare and
+// four selects, of words one v_med3 across lanes (the median with 0 is the smaller,
+// with ~0 the larger) and a minimum and a maximum in a lane.  So the network sorts words:
+// the key's depth above the list's least, shifted down to what the slot leaves of 32
+// bits (23 for 512 keys: exact in a list whose depths lie within a factor of two), over
+// the key's slot in the bucket.  Then the keys are fetched in that order, and what shared
+// a word's depth is put right on the keys themselves: neighbours exchanged until none
+// is out of order.  A list that is not done after kFixPasses (hundreds of equal
+// depths) is sorted on its keys by the 64-bit networks instead.
+constexpr int kFixPasses = 12;
+
+__device__ __forceinline__ uint32_t med3(uint32_t a, uint32_t b, uint32_t c) {
+  return max(min(a, b), min(max(a, b), c));
+}
+__device__ __forceinline__ void cxw(uint32_t& a, uint32_t& b) {
+  const uint32_t x = min(a, b), y = max(a, b);
+  a = x;
+  b = y;
+}
+
+// lane masks: bit[i] is ~0 in the lanes that keep the larger at stride 2^i
+struct LaneBits {
+  uint32_t bit[6];
+  __device__ __forceinline__ explicit LaneBits(int lane) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) bit[i] = ((lane >> i) & 1) ? ~0u : 0u;
+  }
+};
+
+template <int M, bool MIRROR>
+__device__ __forceinline__ void cross_words(uint32_t (&k)[8], const LaneBits& B) {
+  constexpr int kBit = MIRROR ? (M + 1) / 2 : M;
+  const uint32_t bound = B.bit[__builtin_ctz(kBit)];
+  uint32_t p[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) p[r] = xor_lane<M>(k[MIRROR ? 7 - r : r]);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) k[r] = med3(k[r], p[r], bound);
+}
+
+// the plain steps of strides D, D / 2 .. 1 (in elements)
+template <int D>
+__device__ __forceinline__ void plain_words(uint32_t (&k)[8], const LaneBits& B) {
+  if constexpr (D >= 8) {
+    cross_words<D / 8, false>(k, B);
+    plain_words<D / 2>(k, B);
+  } else {
+    if constexpr (D >= 4) { cxw(k[0], k[4]); cxw(k[1], k[5]); cxw(k[2], k[6]); cxw(k[3], k[7]); }
+    if constexpr (D >= 2) { cxw(k[0], k[2]); cxw(k[1], k[3]); cxw(k[4], k[6]); cxw(k[5], k[7]); }
+    cxw(k[0], k[1]); cxw(k[2], k[3]); cxw(k[4], k[5]); cxw(k[6], k[7]);
+  }
+}
+
+// the stages H, 2 H .. 256 that a list of len needs: mirror step, then the plain ones
+template <int H>
+__device__ __forceinline__ void stages_words(uint32_t (&k)[8], uint32_t len, const LaneBits& B) {
+  if constexpr (H < 512) {
+    if (uint32_t(H) >= len) return;
+    if constexpr (H == 1) {
+      cxw(k[0], k[1]); cxw(k[2], k[3]); cxw(k[4], k[5]); cxw(k[6], k[7]);
+    } else if constexpr (H == 2) {
+      cxw(k[0], k[3]); cxw(k[1], k[2]); cxw(k[4], k[7]); cxw(k[5], k[6]);
+    } else if constexpr (H == 4) {
+      cxw(k[0], k[7]); cxw(k[1], k[6]); cxw(k[2], k[5]); cxw(k[3], k[4]);
+    } else {
+      cross_words<2 * H / 8 - 1, true>(k, B);
+    }
+    if constexpr (H > 1) plain_words<H / 2>(k, B);
+    stages_words<2 * H>(k, len, B);
+  }
+}
+
+// Sorts a list of n <= 512 W keys (n > 0) by W waves and writes it out; every thread of
+// the W waves calls it.  s: 2 * 512 W words of LDS (W 1: the keys; else two buffers of
+// words), edge: 2 W keys.  With IN_PLACE the sorted keys go back to the list instead.
+// Returns false, with nothing written, if kFixPasses did not do.
+template <int W, bool IN_PLACE = false>
+__device__ inline bool sort_list_words(uint64_t* list, uint32_t n, uint32_t start, uint32_t t,
+                                       uint32_t* s, uint64_t* edge, uint32_t* __restrict__ vals,
+                                       uint64_t* __restrict__ keys) {
+  constexpr int kSlotBits = W == 1 ? 9 : W == 4 ? 11 : 13;
+  static_assert((512 * W) == (1 << kSlotBits), "one slot per key");
+  const int lane = threadIdx.x & 63;
+  const int w = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  auto sync = [&]() {
+    if constexpr (W == 1) __builtin_amdgcn_wave_barrier();
+    else __syncthreads();
+  };
+  const uint32_t len = n <= 8u ? 8u : pow2_ceil(n);
+  const uint32_t lanes = len / 8u, q = uint32_t(w * 64 + lane);  // lanes that hold keys
+  const bool idle = uint32_t(w * 512) >= len;                    // wave-uniform
+  const uint32_t e0 = 8u * q;  // the lane's elements of the sorted list
+  uint64_t* s_keys = reinterpret_cast<uint64_t*>(s);
+  // slots q, q + lanes ..: a load covers whole cache lines
+  uint32_t k[8], dmin = ~0u, dmax = 0u;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const uint32_t slot = uint32_t(r) * lanes + q;
+    const bool have = q < lanes && slot < n;
+    const uint64_t key = have ? list[slot] : ~uint64_t(0);
+    if (W == 1 && have) s_keys[slot] = key;
+    k[r] = uint32_t(key >> 32);
+    dmin = have ? min(dmin, k[r]) : dmin;
+    dmax = have ? max(dmax, k[r]) : dmax;
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    dmin = min(dmin, uint32_t(__shfl_xor(int(dmin), d, 64)));
+    dmax = max(dmax, uint32_t(__shfl_xor(int(dmax), d, 64)));
+  }
+  if constexpr (W > 1) {
+    if (lane == 0) edge[w] = (uint64_t(dmin) << 32) | dmax;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      dmin = min(dmin, uint32_t(edge[i] >> 32));
+      dmax = max(dmax, uint32_t(edge[i]));
+    }
+    __syncthreads();
+  }
+  const uint32_t range = dmax - dmin;
+  const int bits = range ? 32 - __builtin_clz(range) : 0;
+  const int shift = max(bits - (32 - kSlotBits), 0);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const uint32_t slot = uint32_t(r) * lanes + q;
+    k[r] = (q < lanes && slot < n) ? (((k[r] - dmin) >> shift) << kSlotBits) | slot : ~0u;
+  }
+  const LaneBits B(lane);
+  if (!idle) stages_words<1>(k, len, B);
+  if constexpr (W > 1) {
+    int buf = 0;
+    // partner e ^ m, whose bit hb (a wave's) is the other's; the lower keeps the minimum
+    auto lds_step = [&](uint32_t m, uint32_t hb) {
+      uint4* mine = reinterpret_cast<uint4*>(s + buf * 512 * W + e0);
+      if (!idle) {
+        mine[0] = make_uint4(k[0], k[1], k[2], k[3]);
+        mine[1] = make_uint4(k[4], k[5], k[6], k[7]);
+      }
+      __syncthreads();
+      if (!idle) {
+        const uint4* o = reinterpret_cast<const uint4*>(s + buf * 512 * W + (e0 ^ (m & ~7u)));
+        const uint4 a = o[0], b = o[1];
+        uint32_t p[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        const bool mirror = m & 1u, lower = (uint32_t(w * 512) & hb) == 0u;  // uniform
+        if (mirror) {
+          const uint32_t f[8] = {p[7], p[6], p[5], p[4], p[3], p[2], p[1], p[0]};
+#pragma unroll
+          for (int r = 0; r < 8; ++r) k[r] = lower ? min(k[r], f[r]) : max(k[r], f[r]);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 8; ++r) k[r] = lower ? min(k[r], p[r]) : max(k[r], p[r]);
+        }
+      }
+      buf ^= 1;
+    };
+    for (uint32_t h = 512; h < len; h <<= 1) {
+      lds_step(2 * h - 1, h);
+      for (uint32_t d = h >> 1; d >= 512u; d >>= 1) lds_step(d, d);
+      if (!idle) plain_words<256>(k, B);
+    }
+  } else {
+    __builtin_amdgcn_wave_barrier();
+  }
+  // the keys in that order
+  uint64_t x[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const uint32_t slot = k[r] & ((1u << kSlotBits) - 1u);
+    x[r] = e0 + uint32_t(r) < n ? (W == 1 ? s_keys[slot] : list[slot]) : ~uint64_t(0);
+  }
+  auto out_of_order = [&]() {
+    uint64_t next = __shfl_down(x[0], 1, 64);
+    bool bad = lane < 63 && next < x[7];
+#pragma unroll
+    for (int r = 0; r < 7; ++r) bad |= x[r + 1] < x[r];
+    if constexpr (W > 1) {
+      if (lane == 0) edge[2 * w] = x[0];
+      if (lane == 63) edge[2 * w + 1] = x[7];
+      __syncthreads();
+      if (lane == 63 && w + 1 < W) bad |= edge[2 * w + 2] < x[7];
+      return __syncthreads_or(bad) != 0;
+    } else {
+      return __ballot(bad) != 0ull;
+    }
+  };
+  int pass = 0;
+  while (out_of_order()) {
+    if (++pass > kFixPasses) return false;
+    cx(x[0], x[1]); cx(x[2], x[3]); cx(x[4], x[5]); cx(x[6], x[7]);
+    cx(x[1], x[2]); cx(x[3], x[4]); cx(x[5], x[6]);
+    uint64_t up = __shfl_down(x[0], 1, 64), dn = __shfl_up(x[7], 1, 64);
+    if constexpr (W > 1) {
+      if (lane == 0) edge[2 * w] = x[0];
+      if (lane == 63) edge[2 * w + 1] = x[7];
+      __syncthreads();
+      if (lane == 63) up = w + 1 < W ? edge[2 * w + 2] : ~uint64_t(0);
+      if (lane == 0) dn = w > 0 ? edge[2 * w - 1] : 0ull;
+      __syncthreads();
+    } else {
+      if (lane == 63) up = ~uint64_t(0);
+      if (lane == 0) dn = 0ull;
+    }
+    x[7] = up < x[7] ? up : x[7];
+    x[0] = dn > x[0] ? dn : x[0];
+  }
+  sync();  // every key is fetched
+  if constexpr (IN_PLACE) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (e0 + uint32_t(r) < n) list[e0 + uint32_t(r)] = x[r];
+    sync();
+    return true;
+  }
+  // out through LDS, 64 values in a row a store
+  uint32_t* s_out = s;
+#pragma unroll
+  for (int r = 0; r < 8; ++r)
+    if (e0 + uint32_t(r) < n) s_out[e0 + uint32_t(r)] = uint32_t(x[r]);
+  sync();
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const uint32_t i = uint32_t(r * 64 * W) + q;
+    if (i < n) vals[start + i] = s_out[i];
+  }
+  if (keys) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (e0 + uint32_t(r) < n)
+        keys[start + e0 + uint32_t(r)] = (uint64_t(t) << 32) | (x[r] >> 32);
+  }
+  sync();  // s is reused by the caller
+  return true;
+}
+
 // A tile's list of n <= 512 W keys sorted by block_reg_sort and written out.
 template <int W>
 __device__ inline void sort_list_regs(const uint64_t* __restrict__ bucket, uint32_t start,
@@ -883,14 +1118,16 @@ __device__ inline void sort_list_regs(const uint64_t* __restrict__ bucket, uint3
   }
 }
 
-// One wave per tile, four tiles per block.  Also writes every tile's range end
+// One wave per tile, four tiles per block: 1M Gaussians at 1600x1064, 6700 lists of 335
+// keys, 17 us; 35 with the network on the 64-bit keys.  Also writes every tile's range end
 // (or [0,0) everywhere after a capacity overflow) and flags the presence of
 // lists for the two larger tiers.
 __global__ __launch_bounds__(256) void k_tile_sort_wave(
     int n_tiles, const int64_t* __restrict__ n_tot, const int64_t* __restrict__ n_eff,
     int64_t* __restrict__ n_mid, int64_t* __restrict__ n_long,
-    const uint64_t* __restrict__ bucket, uint32_t* __restrict__ vals,
+    uint64_t* __restrict__ bucket, uint32_t* __restrict__ vals,
     uint64_t* __restrict__ keys, uint32_t* __restrict__ ranges) {
+  __shared__ __align__(16) uint32_t s_words[4][2 * kWaveKeys];
   const int lane = threadIdx.x & 63;
   const uint32_t t = blockIdx.x * 4u + (threadIdx.x >> 6);
   if (t >= uint32_t(n_tiles)) return;  // wave-uniform; no block barrier below
@@ -912,6 +1149,8 @@ __global__ __launch_bounds__(256) void k_tile_sort_wave(
     return;
   }
   if (n == 0) return;
+  if (sort_list_words<1>(bucket + start, n, start, t, s_words[threadIdx.x >> 6], nullptr, vals, keys))
+    return;
   uint64_t k[8];
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
@@ -930,34 +1169,39 @@ __global__ __launch_bounds__(256) void k_tile_sort_wave(
 }
 
 // Lists of kWaveKeys+1 .. kSmall keys: 256-thread blocks striding over the
-// tiles, 8 keys per lane in registers (block_reg_sort: LDS only for the
-// strides that cross waves; 0.046 -> 0.029 ms against the network in LDS at
-// 1M Gaussians, 200x133, tile 8).  Up to 2048 blocks: at 400x266 (1700 tiles)
+// tiles, 8 words per lane in registers, LDS only for the
+// strides that cross waves (1M Gaussians, 200x133, tile 8: 12 us, 29 as 64-bit keys in
+// registers, 46 in LDS; 36 thousand such lists of 16 views of 4M: 320 against 971).  Up to 2048 blocks: at 400x266 (1700 tiles)
 // every tile then has its own block (binning 161 -> 153 us against 1024 blocks).
 constexpr int kMidThreads = 256;
 constexpr int kMidBlocks = 2048;
 
 __global__ __launch_bounds__(kMidThreads) void k_tile_sort_mid(
     int n_tiles, const int64_t* __restrict__ n_eff, const int64_t* __restrict__ n_mid,
-    const uint64_t* __restrict__ bucket, uint32_t* __restrict__ vals,
+    uint64_t* __restrict__ bucket, uint32_t* __restrict__ vals,
     uint64_t* __restrict__ keys, const uint32_t* __restrict__ ranges) {
-  __shared__ uint64_t s[kSmall];
+  __shared__ __align__(16) uint64_t s[kSmall];
+  __shared__ uint64_t s_edge[2 * kMidThreads / 64];
   if (*n_eff == 0 || *n_mid == 0) return;
   for (uint32_t t = blockIdx.x; t < uint32_t(n_tiles); t += gridDim.x) {
     const uint32_t start = ranges[2 * size_t(t)];
     const uint32_t n = ranges[2 * size_t(t) + 1] - start;
     if (n <= uint32_t(kWaveKeys) || n > uint32_t(kSmall)) continue;  // block-uniform
-    sort_list_regs<kMidThreads / 64>(bucket, start, n, t, s, vals, keys);
+    if (!sort_list_words<kMidThreads / 64>(bucket + start, n, start, t,
+                                           reinterpret_cast<uint32_t*>(s), s_edge, vals, keys))
+      sort_list_regs<kMidThreads / 64>(bucket, start, n, t, s, vals, keys);
   }
 }
 
 // Longer lists: 1024-thread blocks, each striding over the tiles (a block
 // needs much of a CU's LDS, so one block per tile would serialise on empty
 // tiles), with LDS chunks of kChunk keys.  A list of at most kChunk keys is
-// sorted in LDS (block_reg_sort over the block's 16 waves measured slower
-// here: 0.070 against 0.058 ms at 1M Gaussians, 200x133, tile 8).  A longer one is sorted in place in the bucket: each chunk is
-// sorted in LDS, then for every further merge size the strides >= kChunk run on
-// global memory and the shorter ones per chunk in LDS.  (All waves of a block
+// sorted as words (30 us at 1M Gaussians, 200x133, tile 8; 46 as 64-bit keys in LDS).
+// A longer one is sorted in place in the bucket: each chunk as words,
+// then for every further merge size the strides >= kChunk run on
+// global memory and the shorter ones per chunk in LDS (16 views of mixed sizes, 102
+// lists of up to 11 thousand keys: 280 us, 242 with only the shorter lists as words, 154
+// with the chunks too, 127 with the tiles looked up together).  (All waves of a block
 // share one CU, whose L1 keeps the block's global writes coherent across the
 // barriers.)  The 64 KB chunk lets two blocks share a CU, so 512 blocks take
 // all of a low-resolution view's long lists at once; with 16384-key chunks one
@@ -967,7 +1211,7 @@ constexpr int kChunk = 8192;
 constexpr int kBigThreads = 1024;
 constexpr int kBigBlocks = 512;
 
-__device__ inline void sort_long(uint64_t* s, uint64_t* a, uint32_t n) {
+__device__ inline void sort_long(uint64_t* s, uint64_t* edge, uint64_t* a, uint32_t n) {
   const uint32_t len = pow2_ceil(n);
   auto load = [&](uint32_t c0, uint32_t m) {
     for (uint32_t i = threadIdx.x; i < m; i += kBigThreads) s[i] = a[c0 + i];
@@ -980,6 +1224,9 @@ __device__ inline void sort_long(uint64_t* s, uint64_t* a, uint32_t n) {
   // every chunk sorted on its own (chunks are aligned blocks of the network)
   for (uint32_t c0 = 0; c0 < n; c0 += kChunk) {
     const uint32_t m = (n - c0 < uint32_t(kChunk)) ? n - c0 : uint32_t(kChunk);
+    if (sort_list_words<kBigThreads / 64, true>(a + c0, m, 0u, 0u, reinterpret_cast<uint32_t*>(s),
+                                                edge, nullptr, nullptr))
+      continue;
     load(c0, m);
     lds_sort<kBigThreads>(s, m, kChunk);
     store(c0, m);
@@ -998,12 +1245,39 @@ __device__ inline void sort_long(uint64_t* s, uint64_t* a, uint32_t n) {
   }
 }
 
+// Calls f(tile, first slot, length) for the block's tiles (blockIdx.x, + gridDim.x, ..)
+// whose list has more than `lo` keys.  THREADS tiles are looked up at a time: one
+// after the other, each a round trip to memory, cost 512 blocks on 81600 tiles 100 us.
+// Every thread of the block calls it, and f with block-uniform arguments.
+template <int THREADS, class F>
+__device__ inline void for_each_list(int n_tiles, const uint32_t* ranges, uint32_t lo, F&& f) {
+  __shared__ uint32_t s_t[THREADS];
+  __shared__ int s_n;
+  for (int64_t base = blockIdx.x; base < n_tiles; base += int64_t(gridDim.x) * THREADS) {
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const int64_t mine = base + int64_t(threadIdx.x) * gridDim.x;
+    if (mine < n_tiles) {
+      const uint32_t n = ranges[2 * mine + 1] - ranges[2 * mine];
+      if (n > lo) s_t[atomicAdd(&s_n, 1)] = uint32_t(mine);
+    }
+    __syncthreads();
+    const int count = s_n;
+    for (int i = 0; i < count; ++i) {
+      const uint32_t t = s_t[i], start = ranges[2 * size_t(t)];
+      f(t, start, ranges[2 * size_t(t) + 1] - start);
+      __syncthreads();  // f's LDS is reused by the next list
+    }
+  }
+}
+
 __global__ __launch_bounds__(kBigThreads) void k_tile_sort_big(
     int n_tiles, const int64_t* __restrict__ n_eff, const int64_t* __restrict__ n_long,
     uint64_t* __restrict__ bucket,
     uint32_t* __restrict__ vals, uint64_t* __restrict__ keys,
     uint32_t* __restrict__ ranges) {
-  __shared__ uint64_t s[kChunk];
+  __shared__ __align__(16) uint64_t s[kChunk];
+  __shared__ uint64_t s_edge[2 * kBigThreads / 64];
   // empty tiles read [0, 0): the wave tier leaves them at [p, p) because a
   // tile's end is its neighbour's start, which must stay until every wave has
   // read it.  Here every range is final, and the long-list loop below reads
@@ -1013,21 +1287,20 @@ __global__ __launch_bounds__(kBigThreads) void k_tile_sort_big(
     if (ranges[2 * size_t(t)] == ranges[2 * size_t(t) + 1])
       ranges[2 * size_t(t)] = ranges[2 * size_t(t) + 1] = 0u;
   if (*n_eff == 0 || *n_long == 0) return;
-  for (uint32_t t = blockIdx.x; t < uint32_t(n_tiles); t += gridDim.x) {
-    const uint32_t start = ranges[2 * size_t(t)], end = ranges[2 * size_t(t) + 1];
-    const uint32_t n = end - start;
-    if (n <= uint32_t(kSmall)) continue;  // block-uniform
-    if (n <= uint32_t(kChunk)) {
-      for (uint32_t i = threadIdx.x; i < n; i += kBigThreads) s[i] = bucket[start + i];
-      __syncthreads();
-      lds_sort<kBigThreads>(s, n, pow2_ceil(n));
-      write_sorted<kBigThreads>(s, n, start, t, vals, keys);
-    } else {
-      sort_long(s, bucket + start, n);
-      write_sorted<kBigThreads>(bucket + start, n, start, t, vals, keys);
-    }
-    __syncthreads();  // s is reused by the block's next tile
-  }
+  for_each_list<kBigThreads>(
+      n_tiles, ranges, kSmall, [&](uint32_t t, uint32_t start, uint32_t n) {
+        if (n > uint32_t(kChunk)) {
+          sort_long(s, s_edge, bucket + start, n);
+          write_sorted<kBigThreads>(bucket + start, n, start, t, vals, keys);
+        } else if (!sort_list_words<kBigThreads / 64>(bucket + start, n, start, t,
+                                                      reinterpret_cast<uint32_t*>(s), s_edge, vals,
+                                                      keys)) {
+          for (uint32_t i = threadIdx.x; i < n; i += kBigThreads) s[i] = bucket[start + i];
+          __syncthreads();
+          lds_sort<kBigThreads>(s, n, pow2_ceil(n));
+          write_sorted<kBigThreads>(s, n, start, t, vals, keys);
+        }
+      });
 }
 
 struct WsLayout {
