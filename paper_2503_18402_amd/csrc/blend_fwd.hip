@@ -14,10 +14,12 @@
 // the colour's part runs under the mask of the pixels reached and is branched
 // over when there is none; a stopped pixel is a raised threshold, not a test; the
 // record is one 48-byte piece, read at one address while the one before is
-// blended.  1M Gaussians at 1600x1064, 16-pixel tiles: 246 us with every lane
-// selecting its updates and records read as used, 186 with the mask, 180 with
-// the record read ahead (16 views of mixed sizes: 1455 to 1103; tiles of 8: 435
-// to 390, of 32: 467 to 273).
+// blended; and the walk itself takes few scalar instructions, which bound the kernel
+// as much as the vector ones did.  1M Gaussians at 1600x1064, 16-pixel tiles: 246 us
+// with every lane selecting its updates and records read as used, 186 with the mask, 180
+// with the record read ahead, 160 with 9 scalar instructions an entry for 13 (16 views
+// of mixed sizes 1455, 1103 with the record read ahead, 940; tiles of 8 435, 379; of 32
+// 467, 240).
 #include <type_traits>
 
 #include "blend_common.hpp"
@@ -61,7 +63,7 @@ struct FwdRec {
   float b;
   uint32_t pos;      // list position, from 1
   uint32_t mask;     // bit w: the box touches wave w's square; kNotPlain
-  uint32_t pad;      // 48 bytes: 16-byte aligned float4s
+  uint32_t pad;      // 48 bytes: 16-byte aligned float4s (64: bank conflicts, 164 us)
 };
 
 constexpr uint32_t kNotPlain = 1u << 31;
@@ -102,17 +104,30 @@ __device__ __forceinline__ void fwd_blend(FwdPix& P, const FwdEnt& e, float px, 
 }
 
 // Walks the entries of `todo` among the 64 at rec, on the scalar unit: the next
-// entry's record is read while the current one is blended (past the last one: any
-// record, not used).
+// entry's record is read while the current one is blended (past the last one, the
+// record before the 64 is read and not used).  The scalar instructions are as many as
+// the vector ones leave time for, so there are few: the lowest bit is found and
+// cleared, and its record's place added to a base that the lanes hold.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
 template <class Blend>
 __device__ __forceinline__ void fwd_walk(const FwdRec* rec, uint64_t todo, Blend&& blend) {
+  typedef __attribute__((address_space(3))) const char lds_char;
+  uint32_t base = uint32_t(reinterpret_cast<uintptr_t>((lds_char*)rec));
+  asm("" : "+v"(base));
   auto fetch = [&](FwdEnt& e) {
-    const FwdRec& r = rec[__builtin_ctzll(todo | (1ull << 63))];
-    todo &= todo - 1ull;
-    e.r0 = r.r0;
-    e.r1 = r.r1;
-    e.b = r.b;
-    e.pos = r.pos;
+    int k;  // -1 when none is left
+    asm("s_ff1_i32_b64 %0, %1" : "=s"(k) : "s"(todo));
+    asm("s_bitset0_b64 %0, %1" : "+s"(todo) : "s"(k));
+    lds_char* r = (lds_char*)(uintptr_t)(base + uint32_t(k * int(sizeof(FwdRec))));
+    const f32x4 r0 = *(__attribute__((address_space(3))) const f32x4*)r;
+    const f32x4 r1 = *(__attribute__((address_space(3))) const f32x4*)(r + 16);
+    const u32x2 r2 = *(__attribute__((address_space(3))) const u32x2*)(r + 32);
+    e.r0 = make_float4(r0.x, r0.y, r0.z, r0.w);
+    e.r1 = make_float4(r1.x, r1.y, r1.z, r1.w);
+    e.b = __uint_as_float(r2.x);
+    e.pos = r2.y;
   };
   int left = __builtin_popcountll(todo);
   if (left == 0) return;
@@ -136,7 +151,8 @@ __global__ __launch_bounds__(WaveShape<TILE>::kThreads) void k_blend_fwd(
     uint32_t* __restrict__ last_contrib, float bg0, float bg1, float bg2, L1Fuse l1) {
   using S = WaveShape<TILE>;
   constexpr int NT = S::kThreads, NW = S::kWaves, R = S::kRegion, SUB = S::kSub, P = S::kPix;
-  __shared__ FwdRec s_rec[BATCH];
+  __shared__ FwdRec s_all[1 + BATCH];  // (one to read past a walk's last)
+  FwdRec* const s_rec = s_all + 1;
 
   const int t = xcd_tile(blockIdx.x, RV);
   const int v = view_of_tile(RV, t);
@@ -246,10 +262,10 @@ __global__ __launch_bounds__(WaveShape<TILE>::kThreads) void k_blend_fwd(
 //      colour entering it (or, if none, after the round);
 //   C. from that chunk on, its wave walks the pixel's list until it stops.
 // Bound by one wave's issue rate and by the rounds, each a gather, a walk and a
-// barrier.  A 128x96 view of 48 tiles of 16: 17 us, against 51 with one block per tile
+// barrier.  A 128x96 view of 48 tiles of 16: 16 us, against 51 with one block per tile
 // and a second launch for its short lists; 425 tiles of up to 3152 entries, where no
-// pixel needs more than 1205 and half the pixels 530: 66 against 139 with the whole list
-// evaluated; 950 tiles of 180: 23 against 38.  (With chunks of up to 48 entries in rounds
+// pixel needs more than 1205 and half the pixels 530: 56 against 139 with the whole list
+// evaluated; 950 tiles of 180: 21 against 38.  (With chunks of up to 48 entries in rounds
 // of their own, 4 waves took 18, 76 and 20 us, 8 waves 15, 58 and 22, 16 waves 16, 68
 // and 40: but the chunks' bounds decide how T is rounded, an image that differs in its
 // last bits flips the sign of an L1 gradient now and then, and with it a Gaussian's
@@ -265,7 +281,7 @@ __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
     const uint32_t* __restrict__ vals, float* __restrict__ image, float* __restrict__ final_T,
     uint32_t* __restrict__ last_contrib, float bg0, float bg1, float bg2, L1Fuse l1) {
   constexpr int GX = TileShape<TILE>::kGroupsX, Q = TileShape<TILE>::kGroups;
-  __shared__ FwdRec s_rec[kFWaves][64];
+  __shared__ FwdRec s_rec[kFWaves][1 + 64];  // (one to read past a walk's last)
   __shared__ float4 s_ch[2][kFWaves][64];    // A: (product, colour); rounds alternate
   __shared__ uint32_t s_lp[2][kFWaves][64];  // A: last entry with alpha >= 1/255
   // the groups of a tile run on one XCD
@@ -285,7 +301,7 @@ __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
   const float py = float((q / GX) * 8 + (lane >> 3)) + 0.5f;
   const uint32_t start = ranges[2 * t], len = ranges[2 * t + 1] - start;
   const float4* rec = reinterpret_cast<const float4*>(proj + size_t(v) * stride);
-  FwdRec* const my = s_rec[wv];
+  FwdRec* const my = s_rec[wv] + 1;
 
   const int64_t pb = RV.pix_base[v];
   const int64_t plane = int64_t(W) * H;
