@@ -204,15 +204,16 @@ struct BwdRec {
   float4 r0;       // mean, A, B
   float4 r1;       // C, log2 opacity, r, g
   float b;
-  uint32_t mask;   // bit q: the box touches group q
   uint32_t slot;   // the pair's gradient slot
-  uint32_t pad;
+  uint32_t pad[2];
 };
 
-// stages list entry g of tile (tx, ty); returns whether it is a plain_record
+// Stages list entry g of tile (tx, ty).  mask: bit q if its box touches group q; returns
+// whether it is a plain_record.
 template <int TILE>
-__device__ __forceinline__ bool bwd_stage(BwdRec& e, uint32_t g, const float4* rec,
-                                          const uint32_t* goff, int tx, int ty) {
+__device__ __forceinline__ bool bwd_stage(BwdRec& e, uint32_t& mask, uint32_t g,
+                                          const float4* rec, const uint32_t* goff, int tx,
+                                          int ty) {
   const float4 r0 = rec[3 * size_t(g)];
   const float4 r1 = rec[3 * size_t(g) + 1];
   const float4 r2 = rec[3 * size_t(g) + 2];
@@ -221,7 +222,7 @@ __device__ __forceinline__ bool bwd_stage(BwdRec& e, uint32_t g, const float4* r
   e.r0 = to_tile_frame<TILE>(r0, lo, tx, ty);
   e.r1 = r1;
   e.b = r2.x;
-  e.mask = group_mask<TILE>(lo, hi, tx, ty);
+  mask = group_mask<TILE>(lo, hi, tx, ty);
   const int tx0 = box_x(lo) / TILE, ty0 = box_y(lo) / TILE, tx1 = box_x(hi) / TILE;
   e.slot = first + uint32_t((ty - ty0) * (tx1 - tx0 + 1) + (tx - tx0));
   return plain_record(r0, r1.x, r1.y);
@@ -279,28 +280,37 @@ __device__ __forceinline__ bool bwd_entry(BwdPix<TILE>& P, const BwdRec& e, uint
   return hit != 0ull;
 }
 
-// the groups of mask whose pixels may have blended the entry at list position pos
+// What a wave holds of its staged entries, entry i in lane i: the groups of its box whose
+// pixels may have blended it; and which entries have any.
+struct BwdMasks {
+  uint32_t groups;
+  uint64_t todo;
+};
+// the lane's entry at list position pos (1-based) with the box mask given
 template <int TILE>
-__device__ __forceinline__ uint32_t live_groups(const BwdPix<TILE>& P, uint32_t mask, uint32_t pos) {
-  uint32_t m = __builtin_amdgcn_readfirstlane(mask);
+__device__ __forceinline__ BwdMasks live_masks(const BwdPix<TILE>& P, uint32_t mask, uint32_t pos) {
 #pragma unroll
   for (int q = 0; q < TileShape<TILE>::kGroups; ++q)
-    if (pos > P.glast[q]) m &= ~(1u << q);
-  return m;
+    if (pos > P.glast[q]) mask &= ~(1u << q);
+  return BwdMasks{mask, __ballot(mask != 0u)};
 }
 
-// walks the nb staged entries at list positions first + 1.. back to front
+// walks the staged entries at list positions first + 1.. back to front
 template <int TILE, int ENTS>
-__device__ __forceinline__ void bwd_walk(BwdPix<TILE>& P, WaveSum<ENTS>& S, const BwdRec* rec, int nb,
-                                         uint32_t first, bool all_plain, float px0, float py0) {
+__device__ __forceinline__ void bwd_walk(BwdPix<TILE>& P, WaveSum<ENTS>& S, const BwdRec* rec,
+                                         const BwdMasks& M, uint32_t first, bool all_plain,
+                                         float px0, float py0) {
   auto walk = [&](auto is_plain) {
-    for (int k = nb - 1; k >= 0; --k) {
-      const BwdRec& e = rec[k];
-      const uint32_t pos = first + uint32_t(k) + 1u;
-      const uint32_t m = live_groups<TILE>(P, e.mask, pos);
-      if (m == 0u) continue;
+    for (uint64_t todo = M.todo; todo != 0ull;) {
+      int k;  // the last one left
+      asm("s_flbit_i32_b64 %0, %1" : "=s"(k) : "s"(todo));
+      k ^= 63;
+      asm("s_bitset0_b64 %0, %1" : "+s"(todo) : "s"(k));
+      const uint32_t m = uint32_t(__builtin_amdgcn_readlane(int(M.groups), k));
+      const BwdRec e = rec[k];  // (all of it now, the slot too)
       float acc[kG];
-      if (bwd_entry<TILE, decltype(is_plain)::value>(P, e, m, pos, px0, py0, acc))
+      if (bwd_entry<TILE, decltype(is_plain)::value>(P, e, m, first + uint32_t(k) + 1u, px0, py0,
+                                                     acc))
         S.add(acc, e.slot);
     }
   };
@@ -310,13 +320,16 @@ __device__ __forceinline__ void bwd_walk(BwdPix<TILE>& P, WaveSum<ENTS>& S, cons
 
 // One 64-lane wave per tile walks the list back to front in chunks staged in
 // LDS, the next chunk's indices read ahead.
-// Bound by instruction issue (38 vector instructions per pixel and entry reached)
+// Bound by instruction issue (34 vector instructions per pixel and entry reached)
 // and, at the ends, by the longest lists.  1M Gaussians at 1600x1064, 16-pixel
 // tiles: 490 us with every lane selecting its updates and all nine sums finished
-// in registers per entry, 365 so (16 views of mixed sizes 2740 to 2035; tiles of
-// 8: 608 to 450, of 32: 953 to 754).  Measured and not taken there: chunks of 32
+// in registers per entry, 360 under the mask with the sums in batches, 348 with the
+// entries that any pixel may have blended found by one ballot a chunk instead of a mask
+// read and tested per entry (16 views of mixed sizes 2740, 2000, 1878; tiles of
+// 8: 608, now 462; of 32: 953, 613).  Measured and not taken there: chunks of 32
 // and 48 entries 375 to 400, the sums through LDS alone 486, through the f32
-// matrix instruction (which shares the vector units) 548.
+// matrix instruction (which shares the vector units) 548, seven waves per SIMD by
+// spilling a register 361, sums in batches of three 359.
 constexpr int kBwdChunk = 64;
 
 template <int TILE>
@@ -354,12 +367,15 @@ __global__ __launch_bounds__(64) void k_blend_bwd(
   while (c1 > start) {
     __builtin_amdgcn_wave_barrier();  // the previous chunk is consumed
     bool plain = true;
-    if (c0 + uint32_t(lane) < c1) plain = bwd_stage<TILE>(s_rec[lane], g, rec, goff, tx, ty);
+    uint32_t mask = 0u;
+    if (c0 + uint32_t(lane) < c1)
+      plain = bwd_stage<TILE>(s_rec[lane], mask, g, rec, goff, tx, ty);
+    const BwdMasks M = live_masks<TILE>(P, mask, c0 - start + uint32_t(lane) + 1u);
     __builtin_amdgcn_wave_barrier();
     const bool all_plain = __ballot(!plain) == 0ull;
     const uint32_t m1 = c0, m0 = first_of(m1);
     if (m0 + uint32_t(lane) < m1) g = vals[m0 + uint32_t(lane)];
-    bwd_walk(P, S, s_rec, int(c1 - c0), c0 - start, all_plain, px0, py0);
+    bwd_walk(P, S, s_rec, M, c0 - start, all_plain, px0, py0);
     c1 = m1;
     c0 = m0;
   }
@@ -380,8 +396,8 @@ __global__ __launch_bounds__(64) void k_blend_bwd(
 // The T recovery by division therefore runs over at most one chunk.
 // Bound by the longest wave: staging, two walks of a chunk, one wave's issue rate.
 // 16 waves per tile while two such blocks per CU hold every tile (a launch of up to
-// 512 tiles: 48 tiles 37 us against 46 with 8 waves, 425 tiles 74 against 101); above
-// that, where blocks queue, 8 (950 tiles: 44 against 49).  4 waves: 49 to 161.  With 8
+// 512 tiles: 48 tiles 35 us against 46 with 8 waves, 425 tiles 72 against 101); above
+// that, where blocks queue, 8 (950 tiles: 43 against 49).  4 waves: 49 to 161.  With 8
 // waves of several chunks for the lists above 48 entries and k_blend_bwd for the others
 // these launches took 96, 119 and 64 us.
 constexpr uint32_t kMinChunk = 32;
@@ -421,11 +437,14 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
   BwdRec* const my = s_rec[wv];
 
   bool all_plain = true;
+  BwdMasks M;
   auto stage = [&](uint32_t i0, uint32_t i1) {  // at most kBwdChunk entries
     __builtin_amdgcn_wave_barrier();
     bool plain = true;
+    uint32_t mask = 0u;
     if (i0 + uint32_t(lane) < i1)
-      plain = bwd_stage<TILE>(my[lane], vals[start + i0 + uint32_t(lane)], rec, goff, tx, ty);
+      plain = bwd_stage<TILE>(my[lane], mask, vals[start + i0 + uint32_t(lane)], rec, goff, tx, ty);
+    M = live_masks<TILE>(P, mask, i0 + uint32_t(lane) + 1u);
     all_plain = __ballot(!plain) == 0ull;
     __builtin_amdgcn_wave_barrier();
   };
@@ -436,14 +455,15 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
 #pragma unroll
     for (int q = 0; q < Q; ++q) Pr[q] = 1.0f, Sc[q] = 0.0f;
     for (uint32_t b0 = c0; b0 < c1; b0 += kBwdChunk) {
-      const int nb = int(min(c1 - b0, uint32_t(kBwdChunk)));
       stage(b0, c1);
       if (nch == 1) continue;
-      for (int k = 0; k < nb; ++k) {
+      for (uint64_t todo = M.todo; todo != 0ull;) {
+        int k;
+        asm("s_ff1_i32_b64 %0, %1" : "=s"(k) : "s"(todo));
+        asm("s_bitset0_b64 %0, %1" : "+s"(todo) : "s"(k));
         const BwdRec& e = my[k];
         const uint32_t pos = b0 + uint32_t(k) + 1u;
-        const uint32_t m = live_groups<TILE>(P, e.mask, pos);
-        if (m == 0u) continue;
+        const uint32_t m = uint32_t(__builtin_amdgcn_readlane(int(M.groups), k));
         const float4 r0 = e.r0, r1 = e.r1;
         const float cb = e.b;
 #pragma unroll
@@ -483,13 +503,12 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
   }
   // C
   WaveSum<ENTS> S(s_part[wv], s_slot[wv], lane, pair_grad, cap);
-  uint32_t b0 = c0 + (c1 - c0 - 1u) / kBwdChunk * kBwdChunk, b1 = c1;
+  uint32_t b0 = c0 + (c1 - c0 - 1u) / kBwdChunk * kBwdChunk;
   while (true) {
-    bwd_walk(P, S, my, int(b1 - b0), b0, all_plain, px0, py0);
+    bwd_walk(P, S, my, M, b0, all_plain, px0, py0);
     if (b0 == c0) break;
-    b1 = b0;
     b0 -= kBwdChunk;
-    stage(b0, b1);
+    stage(b0, b0 + kBwdChunk);
   }
   if (S.cnt) S.flush();
 }
