@@ -24,6 +24,7 @@
 //              block in registers with LDS exchanges for the strides that
 //              cross waves, longer ones by a 1024-thread block (lists of more
 //              than 8192 keys merge their sorted chunks on the 64-bit keys).
+// Launches of few Gaussians and tiles run in one kernel instead (k_bin_direct).
 // The slot order after step 3 depends on atomic timing; after step 4 it does
 // not.  A block whose pairs fall on at most 2048 tiles it can index (all tiles
 // of its view at low resolutions, where every tile collects thousands of
@@ -1303,6 +1304,140 @@ __global__ __launch_bounds__(kBigThreads) void k_tile_sort_big(
       });
 }
 
+// ---- small launches in one kernel: few Gaussians and few tiles, where seven launches of
+// a few blocks each are mostly launches.  Block t < n_tiles goes over all items: those
+// whose box holds its tile make its list, in LDS, and what every box has of the tiles
+// before it gives the list's first slot, without asking another block.  One more block
+// writes the items' pair offsets and the totals.
+// Against the general passes: 4096 Gaussians, 48 tiles: 11 us against 33; 8192 and 192:
+// 16 against 39; 1024 and 2048: 26 against 94.  A block's loop is items / 1024 steps
+// and 512 blocks run at a time, so the gain ends with tiles times items: 8192 and 1024
+// 35 against 54, 8 views of 2048 and 384 tiles 25 against 29; there is the line.  The
+// items of a view are bounded by the keys that fit the LDS.
+constexpr int kDirectThreads = 1024;
+constexpr int kDirectKeys = kChunk;          // items of a view
+constexpr int64_t kDirectItems = 16384;      // items of the launch
+constexpr int64_t kDirectWork = 1 << 23;     // tiles x items
+
+// the sum of x over the block; s_w holds 16 words, every thread calls it
+__device__ inline uint32_t block_sum1024(uint32_t x, uint32_t* s_w) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) x += uint32_t(__shfl_xor(int(x), d, 64));
+  if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = x;
+  __syncthreads();
+  uint32_t all = 0;
+#pragma unroll
+  for (int w = 0; w < kDirectThreads / 64; ++w) all += s_w[w];
+  __syncthreads();
+  return all;
+}
+
+__global__ __launch_bounds__(kDirectThreads) void k_bin_direct(
+    Items S, int n_views, int n_tiles, int64_t cap, uint64_t* __restrict__ bucket,
+    uint32_t* __restrict__ vals, uint64_t* __restrict__ keys, uint32_t* __restrict__ ranges,
+    int64_t* __restrict__ proj_total, int64_t* __restrict__ n_pairs_user) {
+  __shared__ __align__(16) uint64_t s[kDirectKeys];
+  __shared__ uint64_t s_edge[2 * kDirectThreads / 64];
+  __shared__ uint32_t s_w[kDirectThreads / 64];
+  __shared__ uint32_t s_n;
+  const int tid = threadIdx.x, lane = tid & 63, m = n_views * S.n;
+  auto tt_of = [&](int v, int g) {
+    return reinterpret_cast<const uint32_t*>(S.proj + size_t(v) * S.stride + S.tt_off)[g];
+  };
+  if (int(blockIdx.x) == n_tiles) {  // the items' pair offsets
+    uint32_t carry = 0;
+    for (int base = 0; base < m; base += kDirectThreads) {
+      const int i = base + tid, v = i / S.n, g = i - v * S.n;
+      const uint32_t tt = i < m ? tt_of(v, g) : 0u;
+      const uint32_t inc = wave_incl_scan(tt);
+      if (lane == 63) s_w[tid >> 6] = inc;
+      __syncthreads();
+      uint32_t before = carry;
+#pragma unroll
+      for (int w = 0; w < kDirectThreads / 64; ++w) {
+        const uint32_t x = s_w[w];
+        before += w < (tid >> 6) ? x : 0u;
+        carry += x;
+      }
+      if (i < m)
+        reinterpret_cast<uint32_t*>(S.goff_proj + size_t(v) * S.stride + S.goff_off)[g] =
+            before + inc - tt;
+      __syncthreads();  // s_w is rewritten by the next step
+    }
+    if (tid == 0) {
+      *proj_total = int64_t(carry);
+      *n_pairs_user = int64_t(carry);
+    }
+    return;
+  }
+  const uint32_t t = blockIdx.x;
+  int v = 0;
+  for (int k = 1; k < n_views; ++k) v = S.TI.tile_base[k] <= int(t) ? k : v;
+  const int lt = int(t) - S.TI.tile_base[v];
+  const int ty = lt / S.TI.gw[v], tx = lt - ty * S.TI.gw[v];
+  if (tid == 0) s_n = 0u;
+  __syncthreads();
+  uint32_t all = 0, before = 0;
+  for (int base = 0; base < m; base += kDirectThreads) {
+    const int i = base + tid, u = i / S.n, g = i - u * S.n;
+    const uint32_t tt = i < m ? tt_of(u, g) : 0u;
+    all += tt;
+    if (u < v) before += tt;
+    if (tt > 0u && u == v) {
+      const float4 r2 =
+          reinterpret_cast<const float4*>(S.proj + size_t(v) * S.stride)[3 * size_t(g) + 2];
+      const uint32_t lo = __float_as_uint(r2.z), hi = __float_as_uint(r2.w);
+      const int x0 = box_x(lo) >> S.tile_log2, y0 = box_y(lo) >> S.tile_log2;
+      const int x1 = box_x(hi) >> S.tile_log2, y1 = box_y(hi) >> S.tile_log2;
+      // the box's tiles before (tx, ty): its rows above, and of this row those to the left
+      const int w = x1 - x0 + 1;
+      before += uint32_t(w * max(min(y1 + 1, ty) - y0, 0));
+      if (ty >= y0 && ty <= y1) {
+        before += uint32_t(min(max(tx - x0, 0), w));
+        if (tx >= x0 && tx <= x1)
+          s[atomicAdd(&s_n, 1u)] = (uint64_t(__float_as_uint(r2.y)) << 32) | uint32_t(g);
+      }
+    }
+  }
+  all = block_sum1024(all, s_w);
+  before = block_sum1024(before, s_w);  // (its barriers: the list is whole)
+  const uint32_t n = s_n;
+  const bool fits = int64_t(all) <= cap;  // block-uniform, and the same in every block
+  if (tid == 0) {
+    ranges[2 * size_t(t)] = fits && n ? before : 0u;
+    ranges[2 * size_t(t) + 1] = fits && n ? before + n : 0u;
+  }
+  if (!fits || n == 0u) return;
+  if (n <= uint32_t(kWaveKeys)) {
+    if (tid >= 64) return;  // no block barrier below
+    if (sort_list_words<1>(s, n, before, t, reinterpret_cast<uint32_t*>(s + kWaveKeys), nullptr,
+                           vals, keys))
+      return;
+    uint64_t k[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) k[r] = 8u * lane + r < n ? s[8 * lane + r] : ~uint64_t(0);
+    wave_sort(k, n <= 8u ? 8u : pow2_ceil(n));
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const uint32_t i = 8u * lane + r;
+      if (i < n) {
+        vals[before + i] = uint32_t(k[r]);
+        if (keys) keys[before + i] = (uint64_t(t) << 32) | (k[r] >> 32);
+      }
+    }
+    return;
+  }
+  for (uint32_t i = tid; i < n; i += kDirectThreads) bucket[before + i] = s[i];
+  __syncthreads();
+  if (!sort_list_words<kDirectThreads / 64>(bucket + before, n, before, t,
+                                            reinterpret_cast<uint32_t*>(s), s_edge, vals, keys)) {
+    for (uint32_t i = tid; i < n; i += kDirectThreads) s[i] = bucket[before + i];
+    __syncthreads();
+    lds_sort<kDirectThreads>(s, n, pow2_ceil(n));
+    write_sorted<kDirectThreads>(s, n, before, t, vals, keys);
+  }
+}
+
 struct WsLayout {
   size_t cnt, copies, bucket, rank, bpos, total;
   WsLayout(int64_t n_views, int64_t n, int64_t cap) {
@@ -1413,6 +1548,12 @@ hipError_t launch_bin_sort(const Views& V, int n, char* proj, int64_t cap, void*
   const bool any_agg = min_view_tiles <= kAggBins;
   S.rounds = 1;
   const int64_t m = int64_t(V.n_views) * n;
+  int64_t* proj_total = proj ? reinterpret_cast<int64_t*>(proj + L.total) : nullptr;
+  if (n > 0 && n <= kDirectKeys && m <= kDirectItems && m * T <= kDirectWork) {
+    GS_LAUNCH("k_bin_direct", k_bin_direct, dim3(unsigned(T) + 1u), dim3(kDirectThreads), 0, st, S,
+              V.n_views, T, cap, bucket, vals, keys, ranges, proj_total, n_pairs_dev);
+    return hipGetLastError();
+  }
   if (any_agg) {
     const int64_t want = (m + int64_t(kXT) * kAggBlocks - 1) / (int64_t(kXT) * kAggBlocks);
     S.rounds = int(std::min<int64_t>(std::max<int64_t>(want, 1), kAggRounds));
@@ -1441,7 +1582,6 @@ hipError_t launch_bin_sort(const Views& V, int n, char* proj, int64_t cap, void*
     GS_LAUNCH("k_tile_count", (S.rounds == 1 ? k_tile_count<1> : k_tile_count<kAggRounds>), dim3(xb),
               dim3(kXT), agg_lds, st, S, bpos, scanned, cap, ranges, rank,
               copies);
-  int64_t* proj_total = proj ? reinterpret_cast<int64_t*>(proj + L.total) : nullptr;
   GS_LAUNCH("k_tile_scan", (T <= 2 * kTS ? k_tile_scan<2> : k_tile_scan<4>), dim3(1), dim3(kTS), 0,
             st, ranges, copies, T, proj_total, cap, n_tot, n_eff, n_long, n_mid, n_pairs_dev);
   Items Sb = S;

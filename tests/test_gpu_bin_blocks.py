@@ -2,7 +2,8 @@
 the same projected records: one item, one more than a block's, several rounds per
 block and more blocks than their positions are added up for directly; views of
 few and of many tiles in one launch, in any order; footprints of every tile of a
-view next to ones of a single tile; both storage orders."""
+view next to ones of a single tile; both storage orders; and the one-kernel binning of
+small launches up to its limits, with a capacity that just fits and one that does not."""
 import numpy as np
 import pytest
 import torch
@@ -23,6 +24,12 @@ SMALL, FEW, MANY = (40, 24), (300, 200), (1019, 525)
 
 @pytest.mark.parametrize("n,sizes,tile,giants,spatial", [
     (1, [SMALL, MANY], 8, 0, False),
+    (1, [SMALL], 16, 1, False),
+    (1023, [SMALL, FEW, SMALL], 8, 3, False),
+    (1025, [(47, 33)] * 7, 8, 1, True),
+    (8192, [FEW], 16, 4, False),
+    (8193, [FEW], 16, 4, False),
+    (2048, [(256, 250), (8, 8)] * 2, 8, 0, False),
     (257, [MANY] * 3, 16, 2, False),
     (1025, [SMALL, MANY, FEW], 8, 5, False),
     (2049, [FEW, SMALL] * 8, 16, 0, True),
@@ -52,3 +59,18 @@ def test_blocks_equal_radix(n, sizes, tile, giants, spatial):
     assert torch.equal(vals[:np_], fr.vals[:np_])
     assert torch.equal(ranges, fr.ranges)
     assert torch.equal(proj, fr.proj)   # the items' pair offsets and the total
+
+
+@pytest.mark.parametrize("n", [700, 9000])
+def test_capacity_that_just_fits(n):
+    sc = scenes.make_scene(n, seed=n, ls_mu=-3.0)
+    cams = _cams([FEW, SMALL])
+    params = raster.to_device(sc, "cuda")
+    want = raster.render(params, cams, tile=16)
+    total = int(want.n_pairs_dev.item())
+    fits = raster.render(params, cams, tile=16, capacity=total, check_capacity=False)
+    over = raster.render(params, cams, tile=16, capacity=total - 1, check_capacity=False)
+    torch.cuda.synchronize()
+    assert int(fits.n_pairs_dev.item()) == int(over.n_pairs_dev.item()) == total
+    assert torch.equal(fits.ranges, want.ranges) and torch.equal(fits.vals, want.vals[:total])
+    assert not over.ranges.any()
