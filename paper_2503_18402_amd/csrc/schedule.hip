@@ -412,15 +412,23 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_f
 // sum their output columns' windows.  Row weights sit in LDS, formed once per
 // block; a thread holds four input columns (one 16-byte load per row when the
 // rows are 16-byte aligned) and the next kDsBatch rows are in flight while the
-// current ones are summed.  64 views of 1200x800 to 300x200: 231 us, 3.4 TB/s of
-// the 783 MB in and out, against 882 us for one thread per output, which loads
-// each input for the 4 outputs around it and forms every weight again.
-constexpr int kDsRows = 8;       // output rows per block
+// current ones are summed.  64 views of 1200x800 to 300x200: 179 us, 4.4 TB/s of
+// the 783 MB in and out (224 with 8 output rows a strip, room for four output columns
+// a thread where one is used, and the column sums in one plane), against 882 us for one
+// thread per output, which loads each input for the 4 outputs around it and forms every
+// weight again.  Batches of 3 or 6 rows 187 and 182, of 8 275; strips of 25 rows 190.
+constexpr int kDsRows = 16;      // output rows per block, or half where that leaves few blocks
+constexpr int kDsBlocks = 1024;
 constexpr int kDsTable = 256;    // input rows a block may walk
 constexpr int kDsBatch = 4;
 constexpr int kDsThreads = 512;  // at most; 4 input columns per thread
 
-template <bool VEC>
+// NU: output columns per thread, at most.  VEC: 16-byte loads.  PLANES: the columns'
+// place in LDS.  Neighbouring outputs read a factor apart: where that is an even number
+// of columns, or one, a thread's four columns go to four planes, so that such taps lie
+// next to each other or nearly; at odd ones they spread over the banks as they are
+// (factor 4: 212 us in one plane, 179 in four; factor 3, 16 views to 400x266: 80 and 85).
+template <bool VEC, int NU, int PLANES>
 __global__ __launch_bounds__(kDsThreads) void k_downsample_strip(
     int H, int W, int h, int w, int rows_out, int tile_w, int tiles_x, int groups_y,
     const float* __restrict__ src, float* __restrict__ dst) {
@@ -482,10 +490,10 @@ __global__ __launch_bounds__(kDsThreads) void k_downsample_strip(
     }
   };
   // the thread's output columns j0 + tid + u T: window, centre, 1 / weight sum
-  double cx[4], rx[4];
-  int xs[4], xn[4];
+  double cx[NU], rx[NU];
+  int xs[NU], xn[NU];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < NU; ++u) {
     const int j = j0 + tid + u * T;
     xs[u] = xn[u] = 0;
     cx[u] = rx[u] = 0.0;
@@ -506,21 +514,21 @@ __global__ __launch_bounds__(kDsThreads) void k_downsample_strip(
   for (int b = 0; b < kDsBatch; ++b) load(b, cur[b]);
   __syncthreads();
   int i_cur = __builtin_amdgcn_readfirstlane(s_low[0]);
+  auto place = [&](int c) { return PLANES == 4 ? (c & 3) * T + (c >> 2) : c; };
   auto emit = [&]() {  // output row i_cur is complete in acc0
     if (i_cur >= i0 && i_cur < i1) {
       double* buf = s_col + (i_cur & 1) * 4 * T;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) buf[at[u]] = acc0[u];
+      for (int u = 0; u < 4; ++u) buf[VEC && PLANES == 4 ? u * T + tid : place(at[u])] = acc0[u];
       __syncthreads();  // the other buffer is rewritten only after the next barrier
       const double ry = s_ry[i_cur - i0];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < NU; ++u) {
         const int j = j0 + tid + u * T;
         if (j < j1) {
           double row = 0.0, d = cx[u];
-          const double* q = buf + xs[u];
           for (int k = 0; k < xn[u]; ++k, d += 1.0)
-            row = fma(tri(d, sx, ix), q[k], row);
+            row = fma(tri(d, sx, ix), buf[place(xs[u] + k)], row);
           dst[(plane * h + i_cur) * int64_t(w) + j] = float(row * (rx[u] * ry));
         }
       }
@@ -694,10 +702,15 @@ hipError_t launch_downsample(int n_planes, int H, int W, int h, int w, const flo
   if (sx >= 1.0 && sy >= 1.0) {
     // rows per strip: (rows + 1) sy + 3 input rows at most; columns per block:
     // (tile_w + 1) sx + 6 input columns at most, four per thread
-    const int rows_out = std::min(kDsRows, int((kDsTable - 3) / sy) - 1);
+    int rows_out = std::min(kDsRows, int((kDsTable - 3) / sy) - 1);
     const int most = int((4 * kDsThreads - 6) / sx) - 1;
     if (rows_out >= 1 && most >= 1) {
       const int tiles_x = (w + most - 1) / most, tile_w = (w + tiles_x - 1) / tiles_x;
+      // (a strip reads two output rows' window again; few blocks leave CUs idle: 64 views
+      // of 96x64 to 48x32 11 us with 768 blocks of 8 rows, 18 with half of them)
+      if (rows_out > kDsRows / 2 &&
+          int64_t(n_planes) * ((h + rows_out - 1) / rows_out) * tiles_x < kDsBlocks)
+        rows_out = kDsRows / 2;
       const int groups_y = (h + rows_out - 1) / rows_out;
       const int64_t blocks = int64_t(n_planes) * groups_y * tiles_x;
       const int span = std::min(W + 3, int((tile_w + 1) * sx) + 7);
@@ -705,14 +718,14 @@ hipError_t launch_downsample(int n_planes, int H, int W, int h, int w, const flo
       const bool vec = W % 4 == 0 && (reinterpret_cast<uintptr_t>(src) & 15u) == 0;
       const size_t lds = size_t(8) * T * sizeof(double);
       if (blocks < (int64_t(1) << 31)) {
-        if (vec)
-          GS_LAUNCH("k_downsample_strip", k_downsample_strip<true>, dim3(unsigned(blocks)),
-                    dim3(unsigned(T)), lds, st, H, W, h, w, rows_out, tile_w, tiles_x, groups_y,
-                    src, dst);
-        else
-          GS_LAUNCH("k_downsample_strip", k_downsample_strip<false>, dim3(unsigned(blocks)),
-                    dim3(unsigned(T)), lds, st, H, W, h, w, rows_out, tile_w, tiles_x, groups_y,
-                    src, dst);
+        const int factor = int(sx + 0.5);
+        const bool planes = vec && (factor == 1 || factor % 2 == 0), one = tile_w <= T;
+        auto* const strip =
+            planes ? (one ? k_downsample_strip<true, 1, 4> : k_downsample_strip<true, 4, 4>)
+            : vec  ? (one ? k_downsample_strip<true, 1, 1> : k_downsample_strip<true, 4, 1>)
+                   : (one ? k_downsample_strip<false, 1, 1> : k_downsample_strip<false, 4, 1>);
+        GS_LAUNCH("k_downsample_strip", strip, dim3(unsigned(blocks)), dim3(unsigned(T)), lds, st,
+                  H, W, h, w, rows_out, tile_w, tiles_x, groups_y, src, dst);
         return hipGetLastError();
       }
     }

@@ -40,6 +40,9 @@ def test_transforms_match_oracle(n, H, W):
     (2000, 8, 16, 8), (1260, 12, 10, 5), (1270, 12, 10, 5),  # 1 row per strip, the last strip
                                             # factor, and one thread per output past it
     (17, 3000, 17, 2), (9, 9, 1, 1), (5, 7, 8, 3),
+    (5600, 16, 2800, 8), (5600, 20, 2733, 5), (5601, 17, 2800, 8),   # 16 rows per strip
+    (60, 128, 48, 100), (60, 130, 30, 65), (64, 512, 8, 64),  # one and several columns a
+                                            # thread, its four in one LDS plane or in four
 ])
 def test_downsample_strips_match_oracle(H, W, h, w):
     x = np.random.default_rng(H * w).uniform(size=(2, 3, H, W)).astype(np.float32)
