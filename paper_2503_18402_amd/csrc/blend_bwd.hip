@@ -52,19 +52,25 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
                                                   false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-__device__ __forceinline__ void wave_sum9(const float* v, float* q) {
+// the halvings: lane l of a row holds the sum over lanes l, l + 16, l + 32, l + 48
+__device__ __forceinline__ void half_sums9(const float* v, float* q) {
   const float r01 = swap32_add(v[0], v[1]);  // lanes 0-31: v0, 32-63: v1 (pair sums)
   const float r23 = swap32_add(v[2], v[3]);
   const float r45 = swap32_add(v[4], v[5]);
   const float r67 = swap32_add(v[6], v[7]);
   const float r8 = swap32_add(v[8], 0.0f);   // lanes 0-31: v8, 32-63: 0
-  q[0] = row_sum16(swap16_add(r01, r23));     // rows: v0, v2, v1, v3
-  q[1] = row_sum16(swap16_add(r45, r67));     // rows: v4, v6, v5, v7
-  q[2] = row_sum16(swap16_add(r8, r8));       // rows: v8, v8, 0, 0
+  q[0] = swap16_add(r01, r23);               // rows: v0, v2, v1, v3
+  q[1] = swap16_add(r45, r67);               // rows: v4, v6, v5, v7
+  q[2] = swap16_add(r8, r8);                 // rows: v8, v8, 0, 0
+}
+__device__ __forceinline__ void wave_sum9(const float* v, float* q) {
+  half_sums9(v, q);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) q[k] = row_sum16(q[k]);
 }
 
-// ---- one wave's walk over a tile's list, shared by the short- and the
-// long-list kernels.  The wave's 64 lanes own the tile's pixels (lane l: pixel
+// ---- one wave's walk over a tile's list, shared by k_blend_bwd and the
+// list-parallel kernel.  The wave's 64 lanes own the tile's pixels (lane l: pixel
 // (l % 8, l / 8) of every 8x8 group); per pixel it carries T, dL/dC and the
 // colour behind the current entry dotted with dL/dC.
 template <int TILE>
@@ -116,36 +122,20 @@ __device__ __forceinline__ void bwd_load_pixels(BwdPix<TILE>& P, const RViews& R
 }
 
 // ---- sums over the wave's pixels.  Nine values per list entry have to be added
-// over 64 lanes, in a fixed order.  Lane swaps cost 8 cycles per SIMD here and
-// DPP adds 4.6 (a plain add 2.6), so only the first two halvings run in
-// registers: DPP adds with bank masks put two values' sums into one register
-// (lanes l and l ^ 8 of a row, then the mirrored half rows), 14 instructions for
-// all nine, which leaves four partial sums per 16-lane row and value.  Those go
-// to LDS, written and not waited for; after ENTS (at most 4) entries lane 16 e + c
-// adds the 16 partial sums of entry e's value c and writes it to the pair's slot:
-// one store for them all.
+// over 64 lanes, in a fixed order: wave_sum9's.  Its first two halvings run in
+// registers, which leaves one partial sum per lane of a row; its prefix over the row
+// would cost twelve DPP adds of 4.6 cycles per SIMD and idle lanes.  So those 16
+// partial sums go to LDS, written and not waited for; after ENTS (at most 4) entries
+// lane 16 e + c adds the 16 of entry e's value c, in the prefix's order, and writes it to
+// the pair's slot: one store for them all.  (Two halvings within the rows instead, 14 DPP
+// adds with bank masks, take 8 to 14% less: 1M Gaussians at 1600x1064 348 us against 377,
+// 16 views of 4M 5.6 ms against 6.5.  But another order of the sums moves gradients that
+// cancel, such as the rotation of a Gaussian next to the camera whose footprint is the
+// whole view: by 6e-5 of the norm of all rotations' in those 16 views.  That order for
+// footprints of up to 8 tiles only: 373 us and 6.1 ms, and single rotations still moved
+// by 2e-4.)
 constexpr int kPartStride = 20;  // 16 partial sums, padded against bank conflicts
 constexpr int kPartEnt = kG * kPartStride;
-
-// v0, v4, v8: per row of 16 lanes, four partial sums per value; bank b (four
-// lanes) of v0 holds value kBank[b], of v4 value kBank[b] + 4, every bank of v8
-// value 8.  (A DPP read of a register needs two instructions after its write.)
-__device__ __forceinline__ void row_sums9(float (&v)[kG]) {
-#define GS_DPP(d, s, ctrl, bank) \
-  "v_add_f32_dpp %" #d ", %" #s ", %" #s " " ctrl " row_mask:0xf bank_mask:" bank "\n\t"
-  asm("s_nop 1\n\t"
-      GS_DPP(0, 0, "row_ror:8", "0x3") GS_DPP(2, 2, "row_ror:8", "0x3")
-      GS_DPP(4, 4, "row_ror:8", "0x3") GS_DPP(6, 6, "row_ror:8", "0x3")
-      GS_DPP(8, 8, "row_ror:8", "0xf")
-      GS_DPP(0, 1, "row_ror:8", "0xc") GS_DPP(2, 3, "row_ror:8", "0xc")
-      GS_DPP(4, 5, "row_ror:8", "0xc") GS_DPP(6, 7, "row_ror:8", "0xc")
-      GS_DPP(0, 0, "row_half_mirror", "0x5") GS_DPP(4, 4, "row_half_mirror", "0x5")
-      GS_DPP(8, 8, "row_half_mirror", "0xf")
-      GS_DPP(0, 2, "row_half_mirror", "0xa") GS_DPP(4, 6, "row_half_mirror", "0xa")
-      : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
-        "+v"(v[7]), "+v"(v[8]));
-#undef GS_DPP
-}
 
 // scale of value c in the pair's slot: the conic's natural-unit gradients from
 // the base-2 sums; the offset sums (0, 1), opacity and colour as they are
@@ -167,11 +157,12 @@ struct WaveSum {
   __device__ __forceinline__ WaveSum(float* part_, uint32_t* slots_, int lane, float* pair_grad_,
                                      int64_t cap_)
       : part(part_), slots(slots_), pair_grad(pair_grad_), cnt(0) {
-    const int row = lane >> 4, bank = (lane >> 2) & 3, i = lane & 3;
-    const int c0 = ((bank & 1) << 1) | (bank >> 1);  // 0, 2, 1, 3
-    put = uint32_t(c0 * kPartStride + 4 * row + i);
-    // every bank holds value 8's four sums, the odd ones mirrored
-    put8 = uint32_t(8 * kPartStride + 4 * row + ((bank & 1) ? 3 - i : i));
+    const int row = lane >> 4, i = lane & 15;
+    const int c0 = ((row & 1) << 1) | (row >> 1);  // 0, 2, 1, 3
+    put = uint32_t(c0 * kPartStride + i);
+    // value 8 is row 0's; the other rows' go to the padding, which nobody reads
+    const int k = (lane - 16) % 36;
+    put8 = uint32_t(row == 0 ? 8 * kPartStride + i : (k >> 2) * kPartStride + 16 + (k & 3));
     cap = uint32_t(cap_ < 0xffffffffll ? cap_ : 0xffffffffll);
   }
   __device__ __forceinline__ void flush() {
@@ -189,11 +180,12 @@ struct WaveSum {
     cnt = 0;
   }
   __device__ __forceinline__ void add(float (&acc)[kG], uint32_t slot) {
-    row_sums9(acc);
+    float q[3];
+    half_sums9(acc, q);
     float* p = part + cnt * kPartEnt;
-    p[put] = acc[0];
-    p[put + 4 * kPartStride] = acc[4];
-    p[put8] = acc[8];
+    p[put] = q[0];
+    p[put + 4 * kPartStride] = q[1];
+    p[put8] = q[2];
     slots[cnt] = slot;
     if (++cnt == ENTS) flush();
   }
@@ -323,13 +315,13 @@ __device__ __forceinline__ void bwd_walk(BwdPix<TILE>& P, WaveSum<ENTS>& S, cons
 // Bound by instruction issue (34 vector instructions per pixel and entry reached)
 // and, at the ends, by the longest lists.  1M Gaussians at 1600x1064, 16-pixel
 // tiles: 490 us with every lane selecting its updates and all nine sums finished
-// in registers per entry, 360 under the mask with the sums in batches, 348 with the
-// entries that any pixel may have blended found by one ballot a chunk instead of a mask
-// read and tested per entry (16 views of mixed sizes 2740, 2000, 1878; tiles of
-// 8: 608, now 462; of 32: 953, 613).  Measured and not taken there: chunks of 32
+// in registers per entry, 377 under the mask, with the sums in batches and the
+// entries that any pixel may have blended found by one ballot a chunk (12 us less than a
+// mask read and tested per entry) (16 views of mixed sizes 2730, now 2100; tiles of
+// 8: 610, now 540; of 32: 957, 652).  Measured with cheaper sums and not taken: chunks of 32
 // and 48 entries 375 to 400, the sums through LDS alone 486, through the f32
 // matrix instruction (which shares the vector units) 548, seven waves per SIMD by
-// spilling a register 361, sums in batches of three 359.
+// spilling a register 361, sums in batches of three 359 (each against 348).
 constexpr int kBwdChunk = 64;
 
 template <int TILE>
@@ -383,24 +375,27 @@ __global__ __launch_bounds__(64) void k_blend_bwd(
 }
 
 // ---- launches with few tiles (low resolutions: up to thousands of entries per
-// list): one block of NW waves per tile, the list cut into up to NW chunks, one per
-// wave.  Which entries a pixel blends is fixed by the
+// list): one block of NW waves per tile, the list cut into up to kMaxChunks chunks dealt
+// to the waves.  Which entries a pixel blends is fixed by the
 // forward's last_contrib and the alpha test alone, so the chunks are
 // independent:
 //   A. each chunk's transmittance product and its colour dotted with dL/dC (front
 //      to back, T = 1 at its start) per pixel;
-//   B. in every wave, per pixel: the transmittance after its chunk (the product of
-//      the chunks up to it) and the colour behind it dotted with dL/dC (the
-//      background's and, back to front, the later chunks');
+//   B. per pixel, the transmittance entering each chunk (prefix of the products), by one
+//      wave per group; then in every wave, the colour behind its chunk dotted with
+//      dL/dC (the background's and, back to front, the later chunks', weighted by it);
 //   C. the chunk's backward walk from that state, as in k_blend_bwd.
 // The T recovery by division therefore runs over at most one chunk.
 // Bound by the longest wave: staging, two walks of a chunk, one wave's issue rate.
 // 16 waves per tile while two such blocks per CU hold every tile (a launch of up to
 // 512 tiles: 48 tiles 35 us against 46 with 8 waves, 425 tiles 72 against 101); above
-// that, where blocks queue, 8 (950 tiles: 43 against 49).  4 waves: 49 to 161.  With 8
-// waves of several chunks for the lists above 48 entries and k_blend_bwd for the others
-// these launches took 96, 119 and 64 us.
+// that, where blocks queue, 8 (950 tiles: 43 against 49).  4 waves: 49 to 161.  Up to
+// kMaxChunks chunks whatever the waves, so that the results do not depend on this choice:
+// 36, 78 and 53 us.  With 8 waves of several chunks for the lists above 48 entries and
+// k_blend_bwd for the others these launches took 96, 119 and 64 us.
 constexpr uint32_t kMinChunk = 32;
+constexpr int kMaxChunks = 16;
+constexpr uint32_t kOneChunk = 48;  // a list of up to this length is walked as one
 constexpr int kWideTiles = 512;
 
 template <int TILE, int NW>
@@ -415,7 +410,7 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
   constexpr int ENTS = 2;  // 80 KB with 16 waves at tiles of 8: two blocks per CU
   __shared__ __align__(16) float s_part[NW][ENTS * kPartEnt];
   __shared__ uint32_t s_slot[NW][ENTS];
-  __shared__ float2 s_ch[NW][Q][64];  // A: (product, colour . dL/dC)
+  __shared__ float2 s_ch[kMaxChunks][Q][64];  // (product, then T entering; colour . dL/dC)
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int t = xcd_tile(blockIdx.x, RV);
   const uint32_t start = ranges[2 * t], end = ranges[2 * t + 1];
@@ -428,9 +423,10 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
   bwd_load_pixels<TILE>(P, RV, v, tx, ty, lane, final_T, last_contrib, dL_dimage, bg0, bg1, bg2);
   const uint32_t len = min(P.mylast, end - start);  // entries anyone blends
   if (len == 0u) return;                            // block-uniform
-  const int nch = int(min((len + kMinChunk - 1u) / kMinChunk, uint32_t(NW)));
+  const int nch = end - start <= kOneChunk
+                      ? 1
+                      : int(min((len + kMinChunk - 1u) / kMinChunk, uint32_t(kMaxChunks)));
   const uint32_t ch = (len + uint32_t(nch) - 1u) / uint32_t(nch);
-  const uint32_t c0 = min(uint32_t(wv) * ch, len), c1 = min(c0 + ch, len);
   const float4* rec = reinterpret_cast<const float4*>(proj + size_t(v) * stride);
   const uint32_t* goff = reinterpret_cast<const uint32_t*>(proj + size_t(v) * stride + goff_off);
   const float px0 = float(lane & 7) + 0.5f, py0 = float(lane >> 3) + 0.5f;
@@ -449,11 +445,12 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
     __builtin_amdgcn_wave_barrier();
   };
 
-  // A (its last batch stays staged for C)
-  {
-    float Pr[Q], Sc[Q];
+  // A (the last batch staged stays for C)
+  for (int c = wv; c < nch; c += NW) {
+    const uint32_t c0 = uint32_t(c) * ch, c1 = min(c0 + ch, len);
+    float Pr[Q], C0[Q], C1[Q], C2[Q];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) Pr[q] = 1.0f, Sc[q] = 0.0f;
+    for (int q = 0; q < Q; ++q) Pr[q] = 1.0f, C0[q] = C1[q] = C2[q] = 0.0f;
     for (uint32_t b0 = c0; b0 < c1; b0 += kBwdChunk) {
       stage(b0, c1);
       if (nch == 1) continue;
@@ -473,42 +470,62 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
                                          py0 + float((q / GX) * 8));
           if (__builtin_expect((x.p2 <= 0.0f) & (x.q >= kLog2AlphaMin) & (pos <= P.last[q]), 1)) {
             const float a = fminf(kAlphaMax, __builtin_amdgcn_exp2f(x.q));
-            const float cg = fmaf(r1.z, P.g0[q], fmaf(r1.w, P.g1[q], cb * P.g2[q]));
-            Sc[q] = fmaf(a * Pr[q], cg, Sc[q]);
+            const float w = a * Pr[q];
+            C0[q] = fmaf(w, r1.z, C0[q]);
+            C1[q] = fmaf(w, r1.w, C1[q]);
+            C2[q] = fmaf(w, cb, C2[q]);
             Pr[q] *= 1.0f - a;
           }
         }
       }
     }
 #pragma unroll
-    for (int q = 0; q < Q; ++q) s_ch[wv][q][lane] = make_float2(Pr[q], Sc[q]);
+    for (int q = 0; q < Q; ++q)
+      s_ch[c][q][lane] = make_float2(
+          Pr[q], fmaf(C0[q], P.g0[q], fmaf(C1[q], P.g1[q], C2[q] * P.g2[q])));
   }
   __syncthreads();
-  if (c0 == c1) return;
   // B
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    float T = 1.0f;
-    for (int j = 0; j <= wv; ++j) T *= s_ch[j][q][lane].x;
-    // the forward's T_final is the transmittance after the last chunk
-    if (wv == nch - 1) continue;
-    P.T[q] = T;
-    // (in units of the transmittance entering what lies behind)
-    float b = fmaf(bg0, P.g0[q], fmaf(bg1, P.g1[q], bg2 * P.g2[q]));
-    for (int j = nch - 1; j > wv; --j) {
-      const float2 pc = s_ch[j][q][lane];
-      b = fmaf(pc.x, b, pc.y);
+  if (nch > 1) {
+    if (wv < Q) {
+      float T = 1.0f;
+      for (int c = 0; c < nch; ++c) {
+        const float pr = s_ch[c][wv][lane].x;
+        s_ch[c][wv][lane].x = T;
+        T *= pr;
+      }
     }
-    P.SdL[q] = T * b;
+    __syncthreads();
   }
-  // C
+  // C, the wave's last chunk first: P holds T and the colour behind the whole list, which
+  // a chunk's walk needs after it for the chunk before
   WaveSum<ENTS> S(s_part[wv], s_slot[wv], lane, pair_grad, cap);
-  uint32_t b0 = c0 + (c1 - c0 - 1u) / kBwdChunk * kBwdChunk;
-  while (true) {
-    bwd_walk(P, S, my, M, b0, all_plain, px0, py0);
-    if (b0 == c0) break;
-    b0 -= kBwdChunk;
-    stage(b0, b0 + kBwdChunk);
+  float behind[Q];  // behind chunk j, from the last one on
+#pragma unroll
+  for (int q = 0; q < Q; ++q) behind[q] = P.SdL[q];
+  int j = nch;
+  for (int c = wv + (nch - 1 - wv) / NW * NW; c >= 0 && wv < nch; c -= NW) {
+    const uint32_t c0 = uint32_t(c) * ch, c1 = min(c0 + ch, len);
+    for (; j > c + 1; --j)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const float2 x = s_ch[j - 1][q][lane];
+        behind[q] = fmaf(x.x, x.y, behind[q]);
+      }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      // the forward's T_final is the transmittance after the last chunk
+      if (c + 1 < nch) P.T[q] = s_ch[c + 1][q][lane].x;
+      P.SdL[q] = behind[q];
+    }
+    uint32_t b0 = c0 + (c1 - c0 - 1u) / kBwdChunk * kBwdChunk;
+    if (c + NW < nch) stage(b0, c1);  // (A left the wave's last chunk staged)
+    while (true) {
+      bwd_walk(P, S, my, M, b0, all_plain, px0, py0);
+      if (b0 == c0) break;
+      b0 -= kBwdChunk;
+      stage(b0, b0 + kBwdChunk);
+    }
   }
   if (S.cnt) S.flush();
 }

@@ -211,7 +211,7 @@ __device__ inline uint32_t for_each_pair(const Items& S, int v, int64_t first, c
 }
 
 // Pair count of each block's items (the block decomposition of k_tile_count
-// and k_bucket), from which block_first (or, for many blocks, k_scan_spine) forms
+// and k_bucket), from which block_first (or, for many blocks, k_tile_spine) forms
 // each block's first index-order position.  Also clears the tiles' counters
 // (p[0, np), and their copies q[0, nq)) for k_tile_count.
 __global__ __launch_bounds__(kXT) void k_tile_reduce(Items S, uint32_t* __restrict__ block_pairs,
@@ -684,7 +684,8 @@ __device__ inline void write_sorted(const uint64_t* a, uint32_t n, uint32_t star
   }
 }
 
-// ---- lists of at most kWaveKeys keys: one wave per tile, 8 keys per lane in
+// ---- the networks on the 64-bit keys, for lists that the words (below) do not put in
+// order: at most kWaveKeys keys by one wave, 8 keys per lane in
 // registers (element 8 lane + r in k[r]), padded with +infinity to a power of
 // two; the same direction-free network with in-lane steps for strides below 8
 // and lane shuffles above, so no LDS and no barriers.
@@ -1172,7 +1173,8 @@ __global__ __launch_bounds__(256) void k_tile_sort_wave(
 // Lists of kWaveKeys+1 .. kSmall keys: 256-thread blocks striding over the
 // tiles, 8 words per lane in registers, LDS only for the
 // strides that cross waves (1M Gaussians, 200x133, tile 8: 12 us, 29 as 64-bit keys in
-// registers, 46 in LDS; 36 thousand such lists of 16 views of 4M: 320 against 971).  Up to 2048 blocks: at 400x266 (1700 tiles)
+// registers, 46 in LDS; 36 thousand such lists of 16 views of 4M: 320 against 971).
+// Up to 2048 blocks: at 400x266 (1700 tiles)
 // every tile then has its own block (binning 161 -> 153 us against 1024 blocks).
 constexpr int kMidThreads = 256;
 constexpr int kMidBlocks = 2048;

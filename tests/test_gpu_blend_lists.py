@@ -1,9 +1,9 @@
 """The blend kernels at the edges of their chunks, against the FP64 oracle: lists of
 one entry, of the 64 a chunk holds and one to either side of one and two chunks,
 and what is left for the last flush of the backward's sums; records that may
-reach the opacity clamp among plain ones; tiles of 8, 16 and 32 pixels, ragged views.  The views have more tiles than the list-parallel
-kernels take, so every list is walked by the ordinary ones.  Then the list-parallel
-kernels on a small view: one chunk, chunks of the least size, the last of one round
+reach the opacity clamp among plain ones; tiles of 8, 16 and 32 pixels, ragged views.
+The views have more tiles than the list-parallel kernels take, so every list is walked by
+the ordinary ones.  Then the list-parallel kernels on a small view: one chunk, chunks of the least size, the last of one round
 and the first of the next, a wave's second batch, with pixels that stop and that do not.
 
 Tolerances: an image value sums at most 129 weighted colours in float32 (below
