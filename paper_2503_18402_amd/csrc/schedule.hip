@@ -10,7 +10,7 @@
 // over the three channels, which takes the norm over channels.  A 1200x800 view
 // takes 0.05 ms (16 us rows, 30 us columns: rounds of LDS and L2 latency; the
 // 54 MB that it moves would take 10 us), against 1.49 ms for a direct DFT of
-// HW(H + W) terms, which was bound by FP64 arithmetic.
+// HW(H + W) terms, which is bound by FP64 arithmetic; small views take the direct sums.
 // Views are added in order, so the map is deterministic.  H and W are at most
 // kDftMax (a line, or its Bluestein padding of at most 8192 values, fits in LDS).
 //
@@ -397,6 +397,89 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_f
   }
 }
 
+// Small views: the sums themselves, a thread per frequency and one root per term, for
+// lines of up to kDirect values together, kDirectChirp where one of them would need a
+// chirp.  Both ways are chains of latency: the transforms' stages and barriers a fixed
+// one, the sums' one step per term.  Four views, the sums and the transforms: 64x32 35 and
+// 55 us, 80x48 40 and 56, 128x96 63 and 57, 200x132 121 and 66; with chirps 101x67 49 and
+// 98, 150x101 67 and 80, 199x133 121 and 89.
+constexpr int kDirect = 144, kDirectChirp = 256;
+constexpr int kDirectThreads = 128;
+__global__ __launch_bounds__(256) void k_roots(int W, int H, double2* __restrict__ row_tab,
+                                               double2* __restrict__ col_tab) {
+  const int i = int(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i >= W + H) return;
+  const int k = i < W ? i : i - W, n = i < W ? W : H;
+  double s, c;
+  sincospi(2.0 * double(k) / double(n), &s, &c);
+  (i < W ? row_tab : col_tab)[k] = make_double2(c, -s);
+}
+// one block per row of a channel: its non-negative column frequencies
+__global__ __launch_bounds__(kDirectThreads) void k_dft_rows(int H, int W,
+                                                             const float* __restrict__ img,
+                                                             const double2* __restrict__ tab,
+                                                             double2* __restrict__ rows) {
+  extern __shared__ double2 s_root[];  // W roots, then the row
+  double* s_row = reinterpret_cast<double*>(s_root + W);
+  const int y = blockIdx.x, c = blockIdx.y, nk = W / 2 + 1;
+  const float* src = img + (size_t(c) * H + y) * W;
+  for (int x = threadIdx.x; x < W; x += kDirectThreads) s_row[x] = double(src[x]), s_root[x] = tab[x];
+  __syncthreads();
+  for (int k = threadIdx.x; k < nk; k += kDirectThreads) {
+    double re = 0.0, im = 0.0;
+    int i = 0;  // x k mod W
+#pragma unroll 8
+    for (int x = 0; x < W; ++x) {
+      const double2 w = s_root[i];
+      re = fma(s_row[x], w.x, re);
+      im = fma(s_row[x], w.y, im);
+      i += k;
+      i -= i >= W ? W : 0;
+    }
+    rows[(size_t(c) * H + y) * nk + k] = make_double2(re, im);
+  }
+}
+// one block per column frequency, the three channels side by side; M as in k_fft_cols
+__global__ __launch_bounds__(kDirectThreads) void k_dft_cols(int H, int W,
+                                                             const double2* __restrict__ rows,
+                                                             const double2* __restrict__ tab,
+                                                             double inv_n, int first,
+                                                             double* __restrict__ mag) {
+  extern __shared__ double2 s_root[];  // H roots, then the three columns
+  double2* s_col = s_root + H;
+  const int kx = blockIdx.x, nk = W / 2 + 1, mx = (W - kx) % W;
+  const bool mirror = mx != kx && mx >= nk;  // (-ky, -kx) is another column
+  for (int y = threadIdx.x; y < H; y += kDirectThreads) {
+    s_root[y] = tab[y];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s_col[c * H + y] = rows[(size_t(c) * H + y) * nk + kx];
+  }
+  __syncthreads();
+  for (int ky = threadIdx.x; ky < H; ky += kDirectThreads) {
+    double re[3] = {}, im[3] = {};
+    int i = 0;  // y ky mod H
+#pragma unroll 4
+    for (int y = 0; y < H; ++y) {
+      const double2 w = s_root[i];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const double2 a = s_col[c * H + y];
+        re[c] = fma(a.x, w.x, fma(-a.y, w.y, re[c]));
+        im[c] = fma(a.x, w.y, fma(a.y, w.x, im[c]));
+      }
+      i += ky;
+      i -= i >= H ? H : 0;
+    }
+    double sum = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) sum = fma(re[c], re[c], fma(im[c], im[c], sum));
+    const double v = sqrt(sum) * inv_n;
+    const size_t o = size_t(ky) * W + kx, om = size_t(ky ? H - ky : 0) * W + mx;
+    mag[o] = first ? v : mag[o] + v;
+    if (mirror) mag[om] = first ? v : mag[om] + v;
+  }
+}
+
 // Anti-aliased downsampling of [n][C][H][W] to [n][C][h][w].  Output sample i
 // weighs the inputs of its window with a triangle around (i + 0.5) in / out.
 // Coordinates, weights and sums are FP64: in FP32 the tap centre
@@ -417,8 +500,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_f
 // a thread where one is used, and the column sums in one plane), against 882 us for one
 // thread per output, which loads each input for the 4 outputs around it and forms every
 // weight again.  Batches of 3 or 6 rows 187 and 182, of 8 275; strips of 25 rows 190.
-constexpr int kDsRows = 16;      // output rows per block, or half where that leaves few blocks
-constexpr int kDsBlocks = 1024;
+constexpr int kDsRows = 16;      // output rows per block, or fewer where that leaves few blocks
+constexpr int kDsBlocks = 1024, kDsFew = 256;
 constexpr int kDsTable = 256;    // input rows a block may walk
 constexpr int kDsBatch = 4;
 constexpr int kDsThreads = 512;  // at most; 4 input columns per thread
@@ -657,6 +740,20 @@ hipError_t launch_frequency_map(int n_images, int H, int W, const float* images,
   double2* row_tab = reinterpret_cast<double2*>(p);
   p += align256(row.table() * sizeof(double2));
   double2* col_tab = reinterpret_cast<double2*>(p);
+  const double inv_n = 1.0 / double(n_images);
+  if (W + H <= (row.blue() || col.blue() ? kDirectChirp : kDirect)) {
+    GS_LAUNCH("k_roots", k_roots, dim3(unsigned((W + H + 255) / 256)), dim3(256), 0, st, W, H,
+              row_tab, col_tab);
+    for (int k = 0; k < n_images; ++k) {
+      GS_LAUNCH("k_dft_rows", k_dft_rows, dim3(unsigned(H), 3u), dim3(kDirectThreads),
+                size_t(W) * (sizeof(double2) + sizeof(double)), st, H, W,
+                images + size_t(k) * 3 * H * W, row_tab, rows);
+      GS_LAUNCH("k_dft_cols", k_dft_cols, dim3(unsigned(W / 2 + 1)), dim3(kDirectThreads),
+                size_t(4) * H * sizeof(double2), st, H, W, rows, col_tab, inv_n, k == 0 ? 1 : 0,
+                mag);
+    }
+    return hipGetLastError();
+  }
   const int tab_lds = std::max(row.blue() ? row.len : 0, col.blue() ? col.len : 0);
   GS_LAUNCH("k_fft_tables", k_fft_tables, dim3(2), dim3(kTabThreads), tab_lds * sizeof(double2),
             st, row, col, row_tab, col_tab);
@@ -671,7 +768,6 @@ hipError_t launch_frequency_map(int n_images, int H, int W, const float* images,
   const dim3 rgrid(unsigned((H + 1) / 2), 3u);
   const dim3 cgrid(unsigned((groups + kXcds - 1) / kXcds * kXcds));
   const size_t rlds = size_t(row.len) * sizeof(double2), clds = size_t(nc) * sizeof(double2);
-  const double inv_n = 1.0 / double(n_images);
 #define GS_FFT_ROWS(T, E)                                                                      \
   GS_LAUNCH("k_fft_rows", HIP_KERNEL_NAME(k_fft_rows<T, E>), rgrid, dim3(T), rlds, st, row, H, W, img, row_tab, \
             rows)
@@ -706,11 +802,14 @@ hipError_t launch_downsample(int n_planes, int H, int W, int h, int w, const flo
     const int most = int((4 * kDsThreads - 6) / sx) - 1;
     if (rows_out >= 1 && most >= 1) {
       const int tiles_x = (w + most - 1) / most, tile_w = (w + tiles_x - 1) / tiles_x;
-      // (a strip reads two output rows' window again; few blocks leave CUs idle: 64 views
-      // of 96x64 to 48x32 11 us with 768 blocks of 8 rows, 18 with half of them)
-      if (rows_out > kDsRows / 2 &&
-          int64_t(n_planes) * ((h + rows_out - 1) / rows_out) * tiles_x < kDsBlocks)
-        rows_out = kDsRows / 2;
+      // A strip reads two output rows' window again, but few blocks leave CUs idle, and one
+      // strip's rows are a chain: fewer rows a strip below kDsBlocks blocks, one below
+      // kDsFew.  1 view of 400x264 to half 14.5 us in strips of 8, 9.4 of 4, 7.7 of 2, 7.8 of
+      // 1 (a thread per output 7.9); 1 of 64x42 to an eighth 16.7, 15.0, 10.7, 8.3 (31.7);
+      // 8 of 800x528 to a half 24, 25, 28, 37 (73).
+      while (rows_out > 1 && int64_t(n_planes) * ((h + rows_out - 1) / rows_out) * tiles_x <
+                                 (rows_out > 2 ? kDsBlocks : kDsFew))
+        rows_out = (rows_out + 1) / 2;
       const int groups_y = (h + rows_out - 1) / rows_out;
       const int64_t blocks = int64_t(n_planes) * groups_y * tiles_x;
       const int span = std::min(W + 3, int((tile_w + 1) * sx) + 7);

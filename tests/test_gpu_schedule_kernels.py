@@ -12,7 +12,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,H,W", [
     (1, 1, 1), (1, 1, 2), (2, 3, 5),        # no stage, one stage, an odd row left over
-    (1, 61, 122), (1, 67, 134),             # the largest direct prime, the smallest chirp
+    (1, 61, 122), (1, 134, 134),            # the largest direct prime, the smallest chirp
+    (1, 67, 134),
+    (2, 40, 104), (2, 41, 104),             # the last sums without transforms, the first with
+    (1, 67, 189), (1, 67, 190), (1, 150, 67),   # the same where a line would need a chirp
     (2, 343, 320), (1, 342, 321),           # 64- and 256-thread rows; radices 7, 5, 19
     (1, 64, 1281), (1, 40, 2562),           # 512- and 1024-thread rows
     (1, 1706, 12), (1, 1708, 12),           # three channels of columns at once, one at a time
@@ -41,6 +44,7 @@ def test_transforms_match_oracle(n, H, W):
                                             # factor, and one thread per output past it
     (17, 3000, 17, 2), (9, 9, 1, 1), (5, 7, 8, 3),
     (5600, 16, 2800, 8), (5600, 20, 2733, 5), (5601, 17, 2800, 8),   # 16 rows per strip
+    (400, 16, 200, 8), (1600, 20, 800, 10), (2800, 17, 1400, 8),     # 2, 4 and 8 rows
     (60, 128, 48, 100), (60, 130, 30, 65), (64, 512, 8, 64),  # one and several columns a
                                             # thread, its four in one LDS plane or in four
 ])
