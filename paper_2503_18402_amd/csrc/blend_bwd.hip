@@ -53,18 +53,22 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 // the halvings: lane l of a row holds the sum over lanes l, l + 16, l + 32, l + 48
-__device__ __forceinline__ void half_sums9(const float* v, float* q) {
+__device__ __forceinline__ void half_sums8(const float* v, float* q) {
   const float r01 = swap32_add(v[0], v[1]);  // lanes 0-31: v0, 32-63: v1 (pair sums)
   const float r23 = swap32_add(v[2], v[3]);
   const float r45 = swap32_add(v[4], v[5]);
   const float r67 = swap32_add(v[6], v[7]);
-  const float r8 = swap32_add(v[8], 0.0f);   // lanes 0-31: v8, 32-63: 0
   q[0] = swap16_add(r01, r23);               // rows: v0, v2, v1, v3
   q[1] = swap16_add(r45, r67);               // rows: v4, v6, v5, v7
-  q[2] = swap16_add(r8, r8);                 // rows: v8, v8, 0, 0
+}
+// of two values: rows a, a, b, b
+__device__ __forceinline__ float half_sums2(float a, float b) {
+  const float r = swap32_add(a, b);
+  return swap16_add(r, r);
 }
 __device__ __forceinline__ void wave_sum9(const float* v, float* q) {
-  half_sums9(v, q);
+  half_sums8(v, q);
+  q[2] = half_sums2(v[8], 0.0f);
 #pragma unroll
   for (int k = 0; k < 3; ++k) q[k] = row_sum16(q[k]);
 }
@@ -127,13 +131,14 @@ __device__ __forceinline__ void bwd_load_pixels(BwdPix<TILE>& P, const RViews& R
 // would cost twelve DPP adds of 4.6 cycles per SIMD and idle lanes.  So those 16
 // partial sums go to LDS, written and not waited for; after ENTS (at most 4) entries
 // lane 16 e + c adds the 16 of entry e's value c, in the prefix's order, and writes it to
-// the pair's slot: one store for them all.  (Two halvings within the rows instead, 14 DPP
-// adds with bank masks, take 8 to 14% less: 1M Gaussians at 1600x1064 348 us against 377,
-// 16 views of 4M 5.6 ms against 6.5.  But another order of the sums moves gradients that
-// cancel, such as the rotation of a Gaussian next to the camera whose footprint is the
-// whole view: by 6e-5 of the norm of all rotations' in those 16 views.  That order for
-// footprints of up to 8 tiles only: 373 us and 6.1 ms, and single rotations still moved
-// by 2e-4.)
+// the pair's slot: one store for them all.  The ninth value has no partner in its entry
+// and takes the next one's ninth: 14 swaps for two entries instead of 16 (378 -> 369 us,
+// 16 views of 4M 6.52 -> 6.24 ms).
+// (Two halvings within the rows instead, 14 DPP adds with bank masks, took 348 us and
+// 5.6 ms.  But another order of the sums moves gradients that cancel, such as the rotation
+// of a Gaussian next to the camera whose footprint is the whole view: by 6e-5 of the norm
+// of all rotations' in those 16 views.  That order for footprints of up to 8 tiles only:
+// 373 us and 6.1 ms, and single rotations still moved by 2e-4.)
 constexpr int kPartStride = 20;  // 16 partial sums, padded against bank conflicts
 constexpr int kPartEnt = kG * kPartStride;
 
@@ -151,21 +156,23 @@ struct WaveSum {
   uint32_t* slots;       // [ENTS] pair slots
   float* pair_grad;
   uint32_t cap;
-  uint32_t put, put8;    // this lane's places for v0 (v4 follows) and v8
+  uint32_t put, put8;    // this lane's places for v0 (v4 follows) and two entries' v8
+  float v8;              // of the entry before an odd one
   int cnt;               // entries waiting
 
   __device__ __forceinline__ WaveSum(float* part_, uint32_t* slots_, int lane, float* pair_grad_,
                                      int64_t cap_)
-      : part(part_), slots(slots_), pair_grad(pair_grad_), cnt(0) {
+      : part(part_), slots(slots_), pair_grad(pair_grad_), v8(0.0f), cnt(0) {
     const int row = lane >> 4, i = lane & 15;
     const int c0 = ((row & 1) << 1) | (row >> 1);  // 0, 2, 1, 3
     put = uint32_t(c0 * kPartStride + i);
-    // value 8 is row 0's; the other rows' go to the padding, which nobody reads
-    const int k = (lane - 16) % 36;
-    put8 = uint32_t(row == 0 ? 8 * kPartStride + i : (k >> 2) * kPartStride + 16 + (k & 3));
+    // two entries' value 8, in rows 0 and 2; rows 1 and 3 go to the padding, which nobody reads
+    put8 = uint32_t((row & 1) ? (4 * (row >> 1) + (i >> 2)) * kPartStride + 16 + (i & 3)
+                              : (row >> 1) * kPartEnt + 8 * kPartStride + i);
     cap = uint32_t(cap_ < 0xffffffffll ? cap_ : 0xffffffffll);
   }
   __device__ __forceinline__ void flush() {
+    if (cnt & 1) part[(cnt - 1) * kPartEnt + put8] = half_sums2(v8, 0.0f);
     __builtin_amdgcn_wave_barrier();
     const int lane = threadIdx.x & 63, e = lane >> 4, c = lane & 15;
     if (e < cnt && c < kG) {
@@ -180,12 +187,13 @@ struct WaveSum {
     cnt = 0;
   }
   __device__ __forceinline__ void add(float (&acc)[kG], uint32_t slot) {
-    float q[3];
-    half_sums9(acc, q);
+    float q[2];
+    half_sums8(acc, q);
     float* p = part + cnt * kPartEnt;
     p[put] = q[0];
     p[put + 4 * kPartStride] = q[1];
-    p[put8] = q[2];
+    if (cnt & 1) (p - kPartEnt)[put8] = half_sums2(v8, acc[8]);
+    else v8 = acc[8];
     slots[cnt] = slot;
     if (++cnt == ENTS) flush();
   }
@@ -315,10 +323,10 @@ __device__ __forceinline__ void bwd_walk(BwdPix<TILE>& P, WaveSum<ENTS>& S, cons
 // Bound by instruction issue (34 vector instructions per pixel and entry reached)
 // and, at the ends, by the longest lists.  1M Gaussians at 1600x1064, 16-pixel
 // tiles: 490 us with every lane selecting its updates and all nine sums finished
-// in registers per entry, 377 under the mask, with the sums in batches and the
+// in registers per entry, 369 under the mask, with the sums in batches and the
 // entries that any pixel may have blended found by one ballot a chunk (12 us less than a
-// mask read and tested per entry) (16 views of mixed sizes 2730, now 2100; tiles of
-// 8: 610, now 540; of 32: 957, 652).  Measured with cheaper sums and not taken: chunks of 32
+// mask read and tested per entry) (16 views of mixed sizes 2730, now 2040; tiles of
+// 8: 610, now 512; of 32: 957, 635).  Measured with cheaper sums and not taken: chunks of 32
 // and 48 entries 375 to 400, the sums through LDS alone 486, through the f32
 // matrix instruction (which shares the vector units) 548, seven waves per SIMD by
 // spilling a register 361, sums in batches of three 359 (each against 348).
@@ -391,7 +399,7 @@ __global__ __launch_bounds__(64) void k_blend_bwd(
 // 512 tiles: 48 tiles 35 us against 46 with 8 waves, 425 tiles 72 against 101); above
 // that, where blocks queue, 8 (950 tiles: 43 against 49).  4 waves: 49 to 161.  Up to
 // kMaxChunks chunks whatever the waves, so that the results do not depend on this choice:
-// 36, 78 and 53 us.  With 8 waves of several chunks for the lists above 48 entries and
+// 36, 76 and 52 us.  With 8 waves of several chunks for the lists above 48 entries and
 // k_blend_bwd for the others these launches took 96, 119 and 64 us.
 constexpr uint32_t kMinChunk = 32;
 constexpr int kMaxChunks = 16;
