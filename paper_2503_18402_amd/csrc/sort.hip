@@ -1249,11 +1249,13 @@ __device__ inline void sort_long(uint64_t* s, uint64_t* edge, uint64_t* a, uint3
 }
 
 // Calls f(tile, first slot, length) for the block's tiles (blockIdx.x, + gridDim.x, ..)
-// whose list has more than `lo` keys.  THREADS tiles are looked up at a time: one
+// whose list has more than `lo` keys, and sets the ranges of its empty tiles to [0, 0):
+// the thread that looks a tile up is the only one of the launch that touches an empty
+// tile's range, so no other reads it half written.  THREADS tiles are looked up at a time: one
 // after the other, each a round trip to memory, cost 512 blocks on 81600 tiles 100 us.
 // Every thread of the block calls it, and f with block-uniform arguments.
 template <int THREADS, class F>
-__device__ inline void for_each_list(int n_tiles, const uint32_t* ranges, uint32_t lo, F&& f) {
+__device__ inline void for_each_list(int n_tiles, uint32_t* ranges, uint32_t lo, F&& f) {
   __shared__ uint32_t s_t[THREADS];
   __shared__ int s_n;
   for (int64_t base = blockIdx.x; base < n_tiles; base += int64_t(gridDim.x) * THREADS) {
@@ -1262,7 +1264,8 @@ __device__ inline void for_each_list(int n_tiles, const uint32_t* ranges, uint32
     const int64_t mine = base + int64_t(threadIdx.x) * gridDim.x;
     if (mine < n_tiles) {
       const uint32_t n = ranges[2 * mine + 1] - ranges[2 * mine];
-      if (n > lo) s_t[atomicAdd(&s_n, 1)] = uint32_t(mine);
+      if (n == 0u) ranges[2 * mine] = ranges[2 * mine + 1] = 0u;
+      else if (n > lo) s_t[atomicAdd(&s_n, 1)] = uint32_t(mine);
     }
     __syncthreads();
     const int count = s_n;
@@ -1281,15 +1284,18 @@ __global__ __launch_bounds__(kBigThreads) void k_tile_sort_big(
     uint32_t* __restrict__ ranges) {
   __shared__ __align__(16) uint64_t s[kChunk];
   __shared__ uint64_t s_edge[2 * kBigThreads / 64];
+  if (*n_eff == 0) return;  // every range is [0, 0) already
   // empty tiles read [0, 0): the wave tier leaves them at [p, p) because a
   // tile's end is its neighbour's start, which must stay until every wave has
-  // read it.  Here every range is final, and the long-list loop below reads
-  // non-empty tiles only.
-  for (uint32_t t = blockIdx.x * kBigThreads + threadIdx.x; t < uint32_t(n_tiles);
-       t += gridDim.x * kBigThreads)
-    if (ranges[2 * size_t(t)] == ranges[2 * size_t(t) + 1])
-      ranges[2 * size_t(t)] = ranges[2 * size_t(t) + 1] = 0u;
-  if (*n_eff == 0 || *n_long == 0) return;
+  // read it.  Without long lists they are set here, in whole cache lines; else
+  // by the lookup below, which deals the tiles to the blocks in another order.
+  if (*n_long == 0) {
+    for (uint32_t t = blockIdx.x * kBigThreads + threadIdx.x; t < uint32_t(n_tiles);
+         t += gridDim.x * kBigThreads)
+      if (ranges[2 * size_t(t)] == ranges[2 * size_t(t) + 1])
+        ranges[2 * size_t(t)] = ranges[2 * size_t(t) + 1] = 0u;
+    return;
+  }
   for_each_list<kBigThreads>(
       n_tiles, ranges, kSmall, [&](uint32_t t, uint32_t start, uint32_t n) {
         if (n > uint32_t(kChunk)) {
