@@ -251,9 +251,9 @@ __global__ __launch_bounds__(WaveShape<TILE>::kThreads) void k_blend_fwd(
 }
 
 // ---- launches with few tiles (low resolutions: up to thousands of entries per
-// list): one block of kFWaves waves per 8x8 group of a tile, lane l at pixel
+// list): NW waves per 8x8 group of a tile, lane l at pixel
 // (l % 8, l / 8).  The list is cut into up to kFMaxChunks chunks and walked in rounds
-// of kFWaves, one per wave, until no pixel is left.  Transmittance only decreases along the list, so a pixel
+// of NW, one per wave, until no pixel is left.  Transmittance only decreases along the list, so a pixel
 // stops inside a chunk exactly when T entering it times the product of (1 - alpha)
 // over its entries falls below 1e-4:
 //   A. per chunk, with no stopping: the product, the colour (T = 1 at the
@@ -261,6 +261,21 @@ __global__ __launch_bounds__(WaveShape<TILE>::kThreads) void k_blend_fwd(
 //   B. in every wave, from all chunks: the chunk where the pixel stops, and T and
 //      colour entering it (or, if none, after the round);
 //   C. from that chunk on, its wave walks the pixel's list until it stops.
+// A list of up to kFWalk entries is only walked (C).
+//
+// Up to kFFew8 or kFFew16 tiles (of 8 or 16 pixels): a block of kFWaves waves per
+// group; the groups of a short list are a wave each of the tile's first block.  More tiles:
+// a block of kFMoreWaves waves per tile, at tiles of 16 a wave per group (NW 1, no
+// barriers).  There a wave per group or so fills the chip, the waves and LDS of more
+// lie idle in short lists, and blocks cost: each adds its loss with one atomic on
+// one address, 14 ns apiece whatever else runs.  2000 tiles of 16, lists of 10 / 48 / 100 /
+// 300 entries on average: 35 / 40 / 47 / 84 us against 110 / 115 / 117 / 141 with 8 waves per
+// group (13 / 21 / 32 / 81 and 37 / 57 / 61 / 130 without the loss; as two launches with
+// the short lists in k_blend_fwd, 52 / 96 / 94 / 298).  2000 of 8 without the loss, 10 / 100 /
+// 300: 12 / 22 / 48 against 16 / 24 / 53.  The lines: 600 tiles of 16 with 1000 entries take 91
+// us with a wave per group and 82 with eight, 770 the same; 770 of 8 56 with four waves
+// and 51 with eight, 1000 62 and 66.
+//
 // Bound by one wave's issue rate and by the rounds, each a gather, a walk and a
 // barrier.  A 128x96 view of 48 tiles of 16: 16 us, against 51 with one block per tile
 // and a second launch for its short lists; 425 tiles of up to 3152 entries, where no
@@ -273,35 +288,45 @@ __global__ __launch_bounds__(WaveShape<TILE>::kThreads) void k_blend_fwd(
 constexpr int kFWaves = 8;
 constexpr int kFMaxChunks = 16;
 constexpr uint32_t kFMinChunk = 32;
-constexpr uint32_t kFWalk = 48;  // up to this length a list is only walked (C)
+constexpr uint32_t kFWalk = 48;
+constexpr int kFFew8 = 960, kFFew16 = 768;
+constexpr int kFMoreWaves = 4;
 
-template <int TILE>
-__global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
+// NW: waves per group; GPB: groups per block, one or all of the tile's
+template <int TILE, int NW, int GPB>
+__global__ __launch_bounds__(64 * NW * GPB) void k_blend_fwd_long(
     RViews RV, const char* __restrict__ proj, size_t stride, const uint32_t* __restrict__ ranges,
     const uint32_t* __restrict__ vals, float* __restrict__ image, float* __restrict__ final_T,
     uint32_t* __restrict__ last_contrib, float bg0, float bg1, float bg2, L1Fuse l1) {
   constexpr int GX = TileShape<TILE>::kGroupsX, Q = TileShape<TILE>::kGroups;
-  __shared__ FwdRec s_rec[kFWaves][1 + 64];  // (one to read past a walk's last)
-  __shared__ float4 s_ch[2][kFWaves][64];    // A: (product, colour); rounds alternate
-  __shared__ uint32_t s_lp[2][kFWaves][64];  // A: last entry with alpha >= 1/255
-  // the groups of a tile run on one XCD
-  const int xcd = blockIdx.x % kXcds, q = (blockIdx.x / kXcds) % Q;
-  const int block = int(blockIdx.x / (kXcds * Q)) * kXcds + xcd;
+  static_assert(GPB == 1 || (GPB == Q && NW == 1), "a group's waves share barriers");
+  __shared__ FwdRec s_rec[NW * GPB][1 + 64];  // (one to read past a walk's last)
+  __shared__ float4 s_ch[2][NW > 1 ? NW : 1][64];    // A: (product, colour); rounds alternate
+  __shared__ uint32_t s_lp[2][NW > 1 ? NW : 1][64];  // A: last entry with alpha >= 1/255
+  // the blocks of a tile run on one XCD
+  constexpr int kBlocks = Q / GPB;
+  const int xcd = blockIdx.x % kXcds, bq = (blockIdx.x / kXcds) % kBlocks;
+  const int block = int(blockIdx.x / (kXcds * kBlocks)) * kXcds + xcd;
   if (block >= RV.total_tiles) return;
   const int t = xcd_tile(block, RV);
   const int v = view_of_tile(RV, t);
   const int lt = t - RV.tile_base[v];
   const int gw = RV.gw[v], W = RV.W[v], H = RV.H[v];
   const int tx = lt % gw, ty = lt / gw;
-  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const uint32_t start = ranges[2 * t], len = ranges[2 * t + 1] - start;
+  const bool only_walk = len <= kFWalk;
+  const bool own_group = GPB > 1 || only_walk;
+  if (GPB == 1 && only_walk && bq != 0) return;
+  const int q = own_group ? min(wave, Q - 1) : bq;
+  const int wv = own_group ? 0 : wave;  // among the group's waves
   const int gx0 = tx * TILE + (q % GX) * 8, gy0 = ty * TILE + (q / GX) * 8;
   const int x = gx0 + (lane & 7), y = gy0 + (lane >> 3);
   // pixel centre in the tile's frame
   const float px = float((q % GX) * 8 + (lane & 7)) + 0.5f;
   const float py = float((q / GX) * 8 + (lane >> 3)) + 0.5f;
-  const uint32_t start = ranges[2 * t], len = ranges[2 * t + 1] - start;
   const float4* rec = reinterpret_cast<const float4*>(proj + size_t(v) * stride);
-  FwdRec* const my = s_rec[wv] + 1;
+  FwdRec* const my = s_rec[wave] + 1;
 
   const int64_t pb = RV.pix_base[v];
   const int64_t plane = int64_t(W) * H;
@@ -353,23 +378,23 @@ __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
   };
 
   const bool in = (x < W) & (y < H);
-  bool alive = in;
+  bool alive = in & (!own_group | (wave < Q));
   float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
   uint32_t last = 0u;
   const uint32_t chunks = min((len + kFMinChunk - 1u) / kFMinChunk, uint32_t(kFMaxChunks));
-  const uint32_t ch = len <= kFWalk ? kFWalk : (len + chunks - 1u) / chunks;
+  const uint32_t ch = only_walk ? kFWalk : (len + chunks - 1u) / chunks;
   // (the next round's indices are read ahead)
   uint32_t g = index(uint32_t(wv) * ch, min(uint32_t(wv + 1) * ch, len));
   int par = 0;
-  for (uint32_t r0 = 0; r0 < len && __ballot(alive) != 0ull; r0 += kFWaves * ch, par ^= 1) {
+  for (uint32_t r0 = 0; r0 < len && __ballot(alive) != 0ull; r0 += NW * ch, par ^= 1) {
     const uint32_t c0 = r0 + uint32_t(wv) * ch, c1 = min(c0 + ch, len);
-    const int nch = int(min((len - r0 + ch - 1u) / ch, uint32_t(kFWaves)));
+    const int nch = int(min((len - r0 + ch - 1u) / ch, uint32_t(NW)));
     bool mine = false;
     if (wv < nch) stage(c0, c1, g);
-    g = index(c0 + kFWaves * ch, min(c0 + (kFWaves + 1u) * ch, len));
+    g = index(c0 + NW * ch, min(c0 + (NW + 1u) * ch, len));
     uint32_t at = c0;  // the staged entries
-    if (len <= kFWalk) {
-      mine = alive & (wv == 0);
+    if (only_walk) {
+      mine = alive;
       alive = false;
     } else {
       // A
@@ -381,14 +406,16 @@ __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
           stage(at, c1, index(at, c1));
           walk(std::false_type{});
         }
-        s_ch[par][wv][lane] = make_float4(X.T, X.C0, X.C1, X.C2);
-        s_lp[par][wv][lane] = X.last;
+        if (NW > 1) {
+          s_ch[par][wv][lane] = make_float4(X.T, X.C0, X.C1, X.C2);
+          s_lp[par][wv][lane] = X.last;
+        }
       }
-      __syncthreads();
+      if (NW > 1) __syncthreads();
       // B
       for (int c = 0; c < nch; ++c) {
-        const float4 pc = s_ch[par][c][lane];
-        const uint32_t lp = s_lp[par][c][lane];
+        const float4 pc = NW > 1 ? s_ch[par][c][lane] : make_float4(X.T, X.C0, X.C1, X.C2);
+        const uint32_t lp = NW > 1 ? s_lp[par][c][lane] : X.last;
         const float Tn = T * pc.x;
         const bool stop = alive & (Tn < kTMin);
         mine |= stop & (c == wv);
@@ -418,7 +445,7 @@ __global__ __launch_bounds__(64 * kFWaves) void k_blend_fwd_long(
     }
   }
   if (wv == 0 && alive) write(T, C0, C1, C2, last);  // the pixels that never stopped
-  if (l1.loss) l1_block_add<kFWaves>(l1, l1_abs);
+  if (l1.loss) l1_block_add<NW * GPB>(l1, l1_abs);
 }
 
 template <int TILE>
@@ -428,8 +455,11 @@ hipError_t launch_tile(int batch, const RViews& RV, const char* proj, size_t str
                        hipStream_t st) {
   if (few_tiles(RV, TILE)) {
     constexpr int T = TILE <= 16 ? TILE : 16;
-    const unsigned nb = unsigned((RV.total_tiles + kXcds - 1) / kXcds * kXcds) * TileShape<T>::kGroups;
-    GS_LAUNCH("k_blend_fwd_long", k_blend_fwd_long<T>, dim3(nb), dim3(64 * kFWaves), 0, st, RV,
+    constexpr int Q = TileShape<T>::kGroups;
+    const bool few = RV.total_tiles <= (T == 8 ? kFFew8 : kFFew16);
+    const unsigned nb = unsigned((RV.total_tiles + kXcds - 1) / kXcds * kXcds) * (few ? Q : 1);
+    auto* const kern = few ? k_blend_fwd_long<T, kFWaves, 1> : k_blend_fwd_long<T, kFMoreWaves / Q, Q>;
+    GS_LAUNCH("k_blend_fwd_long", kern, dim3(nb), dim3(64 * (few ? kFWaves : kFMoreWaves)), 0, st, RV,
               proj, stride, ranges, vals, image, final_T, last_contrib, bg[0], bg[1], bg[2], l1);
     return hipGetLastError();
   }
