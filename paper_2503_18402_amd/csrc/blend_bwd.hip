@@ -395,16 +395,18 @@ __global__ __launch_bounds__(64) void k_blend_bwd(
 //   C. the chunk's backward walk from that state, as in k_blend_bwd.
 // The T recovery by division therefore runs over at most one chunk.
 // Bound by the longest wave: staging, two walks of a chunk, one wave's issue rate.
-// 16 waves per tile while two such blocks per CU hold every tile (a launch of up to
-// 512 tiles: 48 tiles 35 us against 46 with 8 waves, 425 tiles 72 against 101); above
-// that, where blocks queue, 8 (950 tiles: 43 against 49).  4 waves: 49 to 161.  Up to
+// 16 waves per tile while such blocks hold every tile at once: two per CU at tiles of 8 (80
+// KB each), up to kWideTiles8 tiles (48 tiles 35 us against 46 with 8 waves, 425 tiles 72
+// against 101); one per CU at tiles of 16 (103 KB), up to kWideTiles16 (300 tiles with lists of 100 entries
+// 59 us, 37 with 8 waves, of 300 76 and 72, of 1000 96 either way).  Above
+// that, where blocks queue, 8 (950 tiles of 8: 43 against 49).  4 waves: 49 to 161.  Up to
 // kMaxChunks chunks whatever the waves, so that the results do not depend on this choice:
 // 36, 76 and 52 us.  With 8 waves of several chunks for the lists above 48 entries and
 // k_blend_bwd for the others these launches took 96, 119 and 64 us.
 constexpr uint32_t kMinChunk = 32;
 constexpr int kMaxChunks = 16;
 constexpr uint32_t kOneChunk = 48;  // a list of up to this length is walked as one
-constexpr int kWideTiles = 512;
+constexpr int kWideTiles8 = 512, kWideTiles16 = 256;
 
 template <int TILE, int NW>
 __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
@@ -1341,7 +1343,7 @@ void launch_bwd_tile(dim3 grid, const RViews& RV, int n, const char* proj,
                      const uint32_t* order, hipStream_t st) {
   if (few_tiles(RV, TILE)) {
     constexpr int T = TILE <= 16 ? TILE : 16;
-    const bool wide = RV.total_tiles <= kWideTiles;
+    const bool wide = RV.total_tiles <= (TILE == 8 ? kWideTiles8 : kWideTiles16);
     GS_LAUNCH("k_blend_bwd_long", (wide ? k_blend_bwd_long<T, 16> : k_blend_bwd_long<T, 8>), grid,
               dim3(wide ? 1024 : 512), 0, st, RV, n, proj, stride, ranges, vals, final_T,
               last_contrib, dL, goff, pairs, cap, bg[0], bg[1], bg[2]);
