@@ -403,14 +403,27 @@ __global__ __launch_bounds__(64) void k_blend_bwd(
 // kMaxChunks chunks whatever the waves, so that the results do not depend on this choice:
 // 36, 76 and 52 us.  With 8 waves of several chunks for the lists above 48 entries and
 // k_blend_bwd for the others these launches took 96, 119 and 64 us.
+//
+// A list of up to kOneChunk entries is one wave's, which leaves the rest of its block's
+// LDS idle.  So where the tiles are more than twice the blocks that are resident (two of 8
+// waves per CU at tiles of 16, three at tiles of 8: kOwnTiles16, kOwnTiles8), the short
+// lists go to blocks of their own behind the others, kShortWaves tiles each.  2000 tiles of 16 with
+// lists of 10 / 20 / 30 / 48 / 100 entries on average: 23 / 33 / 59 / 124 / 124 us, and 50 /
+// 78 / 102 / 116 / 124 with each short list in its tile's block (33 / 42 / 141 / 295 / 288
+// with k_blend_bwd for the short ones); of 8: 18 / 26 / 39 / 63 / 67 and 28 / 42 / 55 / 60 /
+// 67.  Below that line lists of about 48 lose as much as shorter ones gain: 1000 tiles of 16, 30
+// and 48 entries 35 and 78 against 56 and 64; 1500 of 8, 29 and 53 against 42 and 47.  1, 2
+// or 8 tiles a block at 2000 of 16, 10 and 30 entries: 52 and 114, 36 and 80, 25 and 56.
 constexpr uint32_t kMinChunk = 32;
 constexpr int kMaxChunks = 16;
 constexpr uint32_t kOneChunk = 48;  // a list of up to this length is walked as one
 constexpr int kWideTiles8 = 512, kWideTiles16 = 256;
+constexpr int kShortWaves = 4;
+constexpr int kOwnTiles8 = 1536, kOwnTiles16 = 1024;
 
 template <int TILE, int NW>
 __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
-    RViews RV, int n, const char* __restrict__ proj, size_t stride,
+    RViews RV, int short_blocks, const char* __restrict__ proj, size_t stride,
     const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
     const float* __restrict__ final_T, const uint32_t* __restrict__ last_contrib,
     const float* __restrict__ dL_dimage, size_t goff_off,
@@ -422,9 +435,25 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
   __shared__ uint32_t s_slot[NW][ENTS];
   __shared__ float2 s_ch[kMaxChunks][Q][64];  // (product, then T entering; colour . dL/dC)
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int t = xcd_tile(blockIdx.x, RV);
+  // `alone`: the wave takes a short list by itself, in one of the launch's last blocks (a
+  // tile per wave) or, without those, as the first wave of the tile's block
+  int block = blockIdx.x;
+  bool alone = block >= int(gridDim.x) - short_blocks;  // block-uniform
+  if (alone) {
+    const int i = block - (int(gridDim.x) - short_blocks);
+    if (wv >= kShortWaves) return;
+    block = (i / kXcds * kShortWaves + wv) * kXcds + i % kXcds;
+  }
+  if (block >= RV.total_tiles) return;
+  const int t = xcd_tile(block, RV);
   const uint32_t start = ranges[2 * t], end = ranges[2 * t + 1];
-  if (start == end) return;
+  const bool is_short = end - start <= kOneChunk;
+  if (start == end || (alone && !is_short)) return;
+  if (is_short && !alone) {
+    if (short_blocks || wv > 0) return;
+    alone = true;
+  }
+  const int cw = alone ? 0 : wv;  // among the tile's waves
   const int v = view_of_tile(RV, t);
   const int lt = t - RV.tile_base[v];
   const int gw = RV.gw[v];
@@ -432,9 +461,8 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
   BwdPix<TILE> P;
   bwd_load_pixels<TILE>(P, RV, v, tx, ty, lane, final_T, last_contrib, dL_dimage, bg0, bg1, bg2);
   const uint32_t len = min(P.mylast, end - start);  // entries anyone blends
-  if (len == 0u) return;                            // block-uniform
-  const int nch = end - start <= kOneChunk
-                      ? 1
+  if (len == 0u) return;                            // the same in all of a tile's waves
+  const int nch = alone ? 1
                       : int(min((len + kMinChunk - 1u) / kMinChunk, uint32_t(kMaxChunks)));
   const uint32_t ch = (len + uint32_t(nch) - 1u) / uint32_t(nch);
   const float4* rec = reinterpret_cast<const float4*>(proj + size_t(v) * stride);
@@ -456,7 +484,7 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
   };
 
   // A (the last batch staged stays for C)
-  for (int c = wv; c < nch; c += NW) {
+  for (int c = cw; c < nch; c += NW) {
     const uint32_t c0 = uint32_t(c) * ch, c1 = min(c0 + ch, len);
     float Pr[Q], C0[Q], C1[Q], C2[Q];
 #pragma unroll
@@ -489,12 +517,13 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
         }
       }
     }
+    if (nch == 1) continue;
 #pragma unroll
     for (int q = 0; q < Q; ++q)
       s_ch[c][q][lane] = make_float2(
           Pr[q], fmaf(C0[q], P.g0[q], fmaf(C1[q], P.g1[q], C2[q] * P.g2[q])));
   }
-  __syncthreads();
+  if (!alone) __syncthreads();
   // B
   if (nch > 1) {
     if (wv < Q) {
@@ -514,7 +543,7 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
 #pragma unroll
   for (int q = 0; q < Q; ++q) behind[q] = P.SdL[q];
   int j = nch;
-  for (int c = wv + (nch - 1 - wv) / NW * NW; c >= 0 && wv < nch; c -= NW) {
+  for (int c = cw + (nch - 1 - cw) / NW * NW; c >= 0 && cw < nch; c -= NW) {
     const uint32_t c0 = uint32_t(c) * ch, c1 = min(c0 + ch, len);
     for (; j > c + 1; --j)
 #pragma unroll
@@ -1344,9 +1373,14 @@ void launch_bwd_tile(dim3 grid, const RViews& RV, int n, const char* proj,
   if (few_tiles(RV, TILE)) {
     constexpr int T = TILE <= 16 ? TILE : 16;
     const bool wide = RV.total_tiles <= (TILE == 8 ? kWideTiles8 : kWideTiles16);
-    GS_LAUNCH("k_blend_bwd_long", (wide ? k_blend_bwd_long<T, 16> : k_blend_bwd_long<T, 8>), grid,
-              dim3(wide ? 1024 : 512), 0, st, RV, n, proj, stride, ranges, vals, final_T,
-              last_contrib, dL, goff, pairs, cap, bg[0], bg[1], bg[2]);
+    const int per = kShortWaves * kXcds;
+    const int shorts = RV.total_tiles <= (TILE == 8 ? kOwnTiles8 : kOwnTiles16)
+                           ? 0 : (RV.total_tiles + per - 1) / per * kXcds;
+    const int blocks = (RV.total_tiles + kXcds - 1) / kXcds * kXcds;
+    GS_LAUNCH("k_blend_bwd_long", (wide ? k_blend_bwd_long<T, 16> : k_blend_bwd_long<T, 8>),
+              dim3(unsigned(blocks + shorts)), dim3(wide ? 1024 : 512), 0, st, RV, shorts, proj,
+              stride, ranges, vals, final_T, last_contrib, dL, goff, pairs, cap, bg[0], bg[1],
+              bg[2]);
     return;
   }
   GS_LAUNCH("k_blend_bwd", HIP_KERNEL_NAME(k_blend_bwd<TILE>), grid,
