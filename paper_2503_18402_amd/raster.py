@@ -59,6 +59,14 @@ def _aligned(t: torch.Tensor) -> torch.Tensor:
     return t
 
 
+def _torch_stream(stream):
+    """``stream`` (None: the current one, or anything with a ``cuda_stream`` handle, as the
+    library's calls take it) as one that torch can make current."""
+    if stream is None or isinstance(stream, torch.cuda.Stream):
+        return stream
+    return torch.cuda.ExternalStream(stream.cuda_stream)
+
+
 def default_capacity(n: int, n_views: int) -> int:
     return max(1024, 8 * n * n_views)
 
@@ -102,7 +110,7 @@ def render(params: dict, cams, tile: int = 16, lds_batch: int = 256, bg=(0.0, 0.
             # overflow leaves every range empty, so that blend is short, and done again)
             np_host = torch.empty(1, dtype=torch.int64, pin_memory=True)
             counted = torch.cuda.Event()
-            with torch.cuda.stream(stream):  # (None: the current one)
+            with torch.cuda.stream(_torch_stream(stream)):
                 np_host.copy_(n_pairs, non_blocking=True)
                 counted.record()
         gsmi.gs_render_fwd(cams_c, cfg, n, proj, ranges, vals, image, final_T, last, stream)
