@@ -96,32 +96,41 @@ def render(params: dict, cams, tile: int = 16, lds_batch: int = 256, bg=(0.0, 0.
     ranges = torch.empty(2 * max(total_tiles, 1), dtype=torch.int32, device=dev)
     n_pairs = torch.zeros(1, dtype=torch.int64, device=dev)
     npx = sum(int(c.width) * int(c.height) for c in cams)
-    image = torch.empty(3 * npx, dtype=torch.float32, device=dev)
-    final_T = torch.empty(npx, dtype=torch.float32, device=dev)
-    last = torch.empty(npx, dtype=torch.int32, device=dev)
+    torch_stream = _torch_stream(stream)
+    image = None
+    read_count = check_capacity
     while True:
         ws = torch.empty(max(gsmi.gs_bin_sort_workspace_bytes(nv, n, cap), 16), dtype=torch.uint8,
                          device=dev)
         vals = torch.empty(max(cap, 1), dtype=torch.int32, device=dev)
         keys = torch.empty(max(cap, 1), dtype=torch.int64, device=dev) if want_keys else None
         gsmi.gs_bin_sort(cams_c, cfg, n, proj, cap, ws, keys, vals, ranges, n_pairs, stream)
-        if check_capacity:
+        # the workspace makes room for the image: nothing uses it but the sort, which `stream`
+        # has in front of what takes its place
+        if torch_stream is not None:
+            ws.record_stream(torch_stream)
+        del ws
+        if image is None:
+            image = torch.empty(3 * npx, dtype=torch.float32, device=dev)
+            final_T = torch.empty(npx, dtype=torch.float32, device=dev)
+            last = torch.empty(npx, dtype=torch.int32, device=dev)
+        if read_count:
             # the count is on its way before the blend starts and read while it runs (an
             # overflow leaves every range empty, so that blend is short, and done again)
             np_host = torch.empty(1, dtype=torch.int64, pin_memory=True)
             counted = torch.cuda.Event()
-            with torch.cuda.stream(_torch_stream(stream)):
+            with torch.cuda.stream(torch_stream):
                 np_host.copy_(n_pairs, non_blocking=True)
                 counted.record()
         gsmi.gs_render_fwd(cams_c, cfg, n, proj, ranges, vals, image, final_T, last, stream)
-        if not check_capacity:
+        if not read_count:
             break
         counted.synchronize()
         np_ = int(np_host[0])
         if np_ <= cap:
             break
         cap = int(np_ * 1.25) + 1024
-    del ws
+        read_count = False  # the same pairs again: they fit
     fr = Frame(cams_c=cams_c, cfg=cfg, n=n, sh_degree=sh_degree, proj=proj, vals=vals,
                keys=keys, ranges=ranges, n_pairs_dev=n_pairs, capacity=cap, image=image,
                final_T=final_T, last_contrib=last,
