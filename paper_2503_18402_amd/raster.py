@@ -94,7 +94,7 @@ def render(params: dict, cams, tile: int = 16, lds_batch: int = 256, bg=(0.0, 0.
     cap = default_capacity(n, nv) if capacity is None else int(capacity)
     total_tiles = gsmi.gs_total_tiles(cams_c, cfg)
     ranges = torch.empty(2 * max(total_tiles, 1), dtype=torch.int32, device=dev)
-    n_pairs = torch.zeros(1, dtype=torch.int64, device=dev)
+    n_pairs = torch.empty(1, dtype=torch.int64, device=dev)  # always written by the sort
     npx = sum(int(c.width) * int(c.height) for c in cams)
     torch_stream = _torch_stream(stream)
     image = None
