@@ -84,6 +84,12 @@ def render(params: dict, cams, tile: int = 16, lds_batch: int = 256, bg=(0.0, 0.
     """
     dev = params["means"].device
     n = params["means"].shape[0]
+    torch_stream = _torch_stream(stream)
+    if check_capacity:
+        with torch.cuda.stream(torch_stream):
+            if torch.cuda.is_current_stream_capturing():
+                raise RuntimeError("the pair count cannot be read back during graph capture: "
+                                   "pass a capacity and check_capacity=False")
     cams_c = gsmi.make_cameras(cams)
     cfg = gsmi.make_cfg(tile, lds_batch, bg, mip2d=mip2d, filter3d=filter3d)
     nv = len(cams)
@@ -96,7 +102,6 @@ def render(params: dict, cams, tile: int = 16, lds_batch: int = 256, bg=(0.0, 0.
     ranges = torch.empty(2 * max(total_tiles, 1), dtype=torch.int32, device=dev)
     n_pairs = torch.empty(1, dtype=torch.int64, device=dev)  # always written by the sort
     npx = sum(int(c.width) * int(c.height) for c in cams)
-    torch_stream = _torch_stream(stream)
     image = None
     read_count = check_capacity
     while True:
