@@ -1455,7 +1455,9 @@ struct WsLayout {
     copies = take(4 * size_t(kXcds) * kAggBins);
     bucket = take(8 * size_t(cap));
     rank = take(4 * size_t(cap));
-    bpos = take(4 * (size_t(n_views * ((n + kXT - 1) / kXT)) + 1));  // per expansion block
+    // per expansion block: at most one more a view than the items fill, whatever the views,
+    // so that a workspace for as many items of fewer views holds too
+    bpos = take(4 * (size_t((n_views * n + kXT - 1) / kXT) + GS_MAX_VIEWS));
     total = o;
   }
 };
