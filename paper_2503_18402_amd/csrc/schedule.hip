@@ -699,17 +699,24 @@ bool plan_stages(FftPlan& P, int n) {
   return n == 1;
 }
 
+// the length of a chirp convolution for n: the least 7-smooth one from 2n - 1 on, at most
+// 8192 for n <= 4096
+int chirp_length(int n) {
+  auto smooth = [](int m) {
+    for (int p : {2, 3, 5, 7})
+      while (m % p == 0) m /= p;
+    return m == 1;
+  };
+  int m = 2 * n - 1;
+  while (!smooth(m)) ++m;
+  return m;
+}
+
 FftPlan make_plan(int n) {
   FftPlan P{};
   P.n = P.len = n;
   if (!plan_stages(P, n)) {
-    auto smooth = [](int m) {
-      for (int p : {2, 3, 5, 7})
-        while (m % p == 0) m /= p;
-      return m == 1;
-    };
-    P.len = 2 * n - 1;
-    while (!smooth(P.len)) ++P.len;  // at most 8192 for n <= 4096
+    P.len = chirp_length(n);
     plan_stages(P, P.len);
   }
   auto magic = [](uint32_t d) { return d == 1u ? 0u : uint32_t(((uint64_t(1) << 32) + d - 1) / d); };
@@ -725,10 +732,11 @@ FftPlan make_plan(int n) {
 
 }  // namespace
 
+// Room for either kind of tables whatever the factors, so that a workspace for an image holds for
+// every smaller one (at most 0.6 MB beyond what the plans take).
 size_t frequency_map_ws_bytes(int H, int W) {
-  return align256(size_t(3) * H * (W / 2 + 1) * sizeof(double2)) +
-         align256(make_plan(W).table() * sizeof(double2)) +
-         align256(make_plan(H).table() * sizeof(double2));
+  auto tables = [](int n) { return align256((2 * size_t(chirp_length(n)) + n) * sizeof(double2)); };
+  return align256(size_t(3) * H * (W / 2 + 1) * sizeof(double2)) + tables(W) + tables(H);
 }
 
 hipError_t launch_frequency_map(int n_images, int H, int W, const float* images, double* mag,
