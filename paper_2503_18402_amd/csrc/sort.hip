@@ -870,8 +870,16 @@ __device__ inline void block_reg_sort(uint64_t (&k)[8], uint32_t len, uint64_t* 
 // the key's slot in the bucket.  Then the keys are fetched in that order, and what shared
 // a word's depth is put right on the keys themselves: neighbours exchanged until none
 // is out of order.  A list that is not done after kFixPasses (hundreds of equal
-// depths) is sorted on its keys by the 64-bit networks instead.
+// depths) is sorted on its keys by the 64-bit networks instead; and one whose depths are
+// seen to come in long runs at once: a quarter as many pairs as the network has places are
+// compared as they lie in the bucket, of which about L / 4 are equal with runs of L equal
+// depths; above kEqualPairs the runs are longer than the passes can put right.  1M Gaussians
+// on one plane facing the camera, 1600x1064: sorts 205 us with the words tried first, 128 so,
+// 116 with the 64-bit networks for every list; on two 262, 160 and 139; on 32, where the
+// words mostly do, 96, 102 and 140 (pairs above 12: 114, above 8: 136); depths that all
+// differ 58, 60 and 140.
 constexpr int kFixPasses = 12;
+constexpr int kEqualPairs = 16;
 
 __device__ __forceinline__ uint32_t med3(uint32_t a, uint32_t b, uint32_t c) {
   return max(min(a, b), min(max(a, b), c));
@@ -937,7 +945,7 @@ __device__ __forceinline__ void stages_words(uint32_t (&k)[8], uint32_t len, con
 // Sorts a list of n <= 512 W keys (n > 0) by W waves and writes it out; every thread of
 // the W waves calls it.  s: 2 * 512 W words of LDS (W 1: the keys; else two buffers of
 // words), edge: 2 W keys.  With IN_PLACE the sorted keys go back to the list instead.
-// Returns false, with nothing written, if kFixPasses did not do.
+// Returns false, with nothing written, if kFixPasses did not do or would not.
 template <int W, bool IN_PLACE = false>
 __device__ inline bool sort_list_words(uint64_t* list, uint32_t n, uint32_t start, uint32_t t,
                                        uint32_t* s, uint64_t* edge, uint32_t* __restrict__ vals,
@@ -957,6 +965,7 @@ __device__ inline bool sort_list_words(uint64_t* list, uint32_t n, uint32_t star
   uint64_t* s_keys = reinterpret_cast<uint64_t*>(s);
   // slots q, q + lanes ..: a load covers whole cache lines
   uint32_t k[8], dmin = ~0u, dmax = 0u;
+  int equal = 0;
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     const uint32_t slot = uint32_t(r) * lanes + q;
@@ -966,6 +975,8 @@ __device__ inline bool sort_list_words(uint64_t* list, uint32_t n, uint32_t star
     k[r] = uint32_t(key >> 32);
     dmin = have ? min(dmin, k[r]) : dmin;
     dmax = have ? max(dmax, k[r]) : dmax;
+    // (the slots of the lower half: every list has them)
+    if (r == 1 || r == 3) equal += __builtin_popcountll(__ballot(have && k[r] == k[r > 0 ? r - 1 : 0]));
   }
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) {
@@ -973,15 +984,23 @@ __device__ inline bool sort_list_words(uint64_t* list, uint32_t n, uint32_t star
     dmax = max(dmax, uint32_t(__shfl_xor(int(dmax), d, 64)));
   }
   if constexpr (W > 1) {
-    if (lane == 0) edge[w] = (uint64_t(dmin) << 32) | dmax;
+    if (lane == 0) {
+      edge[w] = (uint64_t(dmin) << 32) | dmax;
+      edge[W + w] = uint64_t(equal);
+    }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < W; ++i) {
       dmin = min(dmin, uint32_t(edge[i] >> 32));
       dmax = max(dmax, uint32_t(edge[i]));
     }
+    equal = lane < W ? int(edge[W + lane]) : 0;
+#pragma unroll
+    for (int d = W / 2; d >= 1; d >>= 1) equal += __shfl_xor(equal, d, 64);
+    equal = __builtin_amdgcn_readfirstlane(equal);
     __syncthreads();
   }
+  if (equal > kEqualPairs) return false;
   const uint32_t range = dmax - dmin;
   const int bits = range ? 32 - __builtin_clz(range) : 0;
   const int shift = max(bits - (32 - kSlotBits), 0);
