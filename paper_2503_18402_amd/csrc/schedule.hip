@@ -259,38 +259,97 @@ __device__ __forceinline__ void fft_block(double2* s, const FftPlan& P, uint32_t
   }
 }
 
-// The tables of the row plan (block 0) and the column plan (block 1): roots
-// e^{-2 pi i k / len}; for Bluestein the chirps e^{-pi i k^2 / n} and the
-// transform of the filter conj(chirp_|k|), |k| < n, scaled by 1 / len.
-constexpr int kTabThreads = 1024;
+// The tables of the row plan (blockIdx.y 0) and the column plan (1): roots
+// e^{-2 pi i k / len}; for Bluestein also the chirps e^{-pi i k^2 / n}.
+constexpr int kTabThreads = 256;
 __global__ __launch_bounds__(kTabThreads) void k_fft_tables(FftPlan row, FftPlan col,
                                                             double2* __restrict__ row_tab,
                                                             double2* __restrict__ col_tab) {
-  extern __shared__ double2 s_fft[];
-  const FftPlan& P = blockIdx.x == 0 ? row : col;
-  double2* tab = blockIdx.x == 0 ? row_tab : col_tab;
-  for (int k = threadIdx.x; k < P.len; k += kTabThreads) {
-    double s, c;
+  const FftPlan& P = blockIdx.y == 0 ? row : col;
+  double2* tab = blockIdx.y == 0 ? row_tab : col_tab;
+  const int k = int(blockIdx.x * kTabThreads + threadIdx.x);
+  double s, c;
+  if (k < P.len) {
     sincospi(2.0 * double(k) / double(P.len), &s, &c);
     tab[k] = make_double2(c, -s);
   }
-  if (!P.blue()) return;  // block-uniform
-  for (int k = threadIdx.x; k < P.len; k += kTabThreads) s_fft[k] = make_double2(0.0, 0.0);
-  __syncthreads();  // also orders the roots' writes before the block reads them
-  double2* chirp = tab + P.len;
-  for (int k = threadIdx.x; k < P.n; k += kTabThreads) {
-    double s, c;
+  if (P.blue() && k < P.n) {
     sincospi(double((k * k) % (2 * P.n)) / double(P.n), &s, &c);
-    chirp[k] = make_double2(c, -s);
-    s_fft[k] = make_double2(c, s);
-    if (k > 0) s_fft[P.len - k] = make_double2(c, s);
+    tab[P.len + k] = make_double2(c, -s);
   }
+}
+
+// a + b, the rounding error added to e
+__device__ __forceinline__ double add_exact(double a, double b, double& e) {
+  const double s = a + b, t = s - a;
+  e += (a - (s - t)) + (b - t);
+  return s;
+}
+
+// The transform of the chirp filter conj(chirp_|k|), |k| < n, scaled by 1 / len.  It goes
+// into every line of every image, so that its error stays where others average out: taken
+// by a transform in FP64, it made the map of four images of 71x211 1.8e-16 off, 1.4 so.
+// It is even, so a wave sums the n cosine terms of one value, with the roundings of
+// products and sums carried along (and all waves of the chip do, where one block ran the
+// transform: one image of 211x263 48 us, 36 so).  blockIdx.y as above.
+__global__ __launch_bounds__(kTabThreads) void k_chirp_filter(FftPlan row, FftPlan col,
+                                                              double2* __restrict__ row_tab,
+                                                              double2* __restrict__ col_tab) {
+  const FftPlan& P = blockIdx.y == 0 ? row : col;
+  double2* tab = blockIdx.y == 0 ? row_tab : col_tab;
+  const uint32_t len = uint32_t(P.len), n = uint32_t(P.n), lane = threadIdx.x & 63u;
+  const uint32_t k = blockIdx.x * (kTabThreads / 64) + (threadIdx.x >> 6);
+  if (!P.blue() || k > len / 2u) return;  // wave-uniform
+  const double2* chirp = tab + len;
+  const uint32_t x = lane * k, step = 64u * k - div_magic(64u * k, P.magic_len) * len;
+  uint32_t at = x - div_magic(x, P.magic_len) * len;  // j k mod len
+  double2 s = make_double2(0.0, 0.0), e = s;
+  for (uint32_t j = lane; j < n; j += 64u) {
+    const double2 h = chirp[j];
+    const double c = j ? 2.0 * tab[at].x : 1.0;
+    const double re = h.x * c, im = -h.y * c;
+    e.x += fma(h.x, c, -re);
+    e.y += fma(-h.y, c, -im);
+    s.x = add_exact(s.x, re, e.x);
+    s.y = add_exact(s.y, im, e.y);
+    at += step;
+    if (at >= len) at -= len;
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    const double sx = __shfl_xor(s.x, d, 64), sy = __shfl_xor(s.y, d, 64);
+    const double ex = __shfl_xor(e.x, d, 64), ey = __shfl_xor(e.y, d, 64);
+    s.x = add_exact(s.x, sx, e.x);
+    s.y = add_exact(s.y, sy, e.y);
+    e.x += ex;
+    e.y += ey;
+  }
+  if (lane == 0) {
+    const double scale = 1.0 / double(len);
+    const double2 f = make_double2((s.x + e.x) * scale, (s.y + e.y) * scale);
+    double2* filter = tab + len + n;
+    filter[k] = f;
+    if (k > 0) filter[len - k] = f;
+  }
+}
+
+// A chirp convolution runs about twice as many stages as a plain transform, and its error is a few
+// roundings of the size of what goes in.  So the mean of each row, and of the column of
+// frequency 0, goes round it: rounded to float32, so that the differences of a row's
+// values are exact, as is its product with the length, which is what it adds to frequency 0.
+// Error of the map of an image in [0, 1), of its 2-norm: 607x809 1.7e-16, and 3.7e-16
+// without this, 3.5e-16 with direct sums; 211x263 1.3, 4.0 and 2.1.
+template <int T>
+__device__ __forceinline__ double block_sum(double x, double* s_part) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
+  if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = x;
   __syncthreads();
-  fft_block<kTabThreads, 8>(s_fft, P, 1u, tab, false);
-  const double scale = 1.0 / double(P.len);
-  double2* filter = chirp + P.n;
-  for (int k = threadIdx.x; k < P.len; k += kTabThreads)
-    filter[k] = make_double2(s_fft[k].x * scale, s_fft[k].y * scale);
+  x = 0.0;
+#pragma unroll
+  for (int w = 0; w < T / 64; ++w) x += s_part[w];
+  __syncthreads();  // s_part is rewritten by the next call
+  return x;
 }
 
 // Row pass: one block per two rows of a channel, transformed together as the
@@ -306,11 +365,26 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T < 1024 ? 5 
   const bool two = y + 1 < H;
   const float* src = img + (size_t(c) * H + y) * W;
   const double2* chirp = tab + P.len;
+  __shared__ double s_part[T / 64], s_mean[2];
+  if (P.blue()) {  // block-uniform
+    double2 sum = make_double2(0.0, 0.0);
+    for (int x = threadIdx.x; x < W; x += T) {
+      sum.x += double(src[x]);
+      sum.y += two ? double(src[x + W]) : 0.0;
+    }
+    sum.x = block_sum<T>(sum.x, s_part);
+    sum.y = block_sum<T>(sum.y, s_part);
+    if (threadIdx.x == 0) {
+      s_mean[0] = double(float(sum.x / double(W)));
+      s_mean[1] = double(float(sum.y / double(W)));
+    }
+    __syncthreads();
+  }
   for (int x = threadIdx.x; x < P.len; x += T) {
     double2 a = make_double2(0.0, 0.0);
     if (x < W) {
       a = make_double2(double(src[x]), two ? double(src[x + W]) : 0.0);
-      if (P.blue()) a = cmul(a, chirp[x]);
+      if (P.blue()) a = cmul(make_double2(a.x - s_mean[0], a.y - s_mean[1]), chirp[x]);
     }
     s_fft[x] = a;
   }
@@ -324,6 +398,10 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T < 1024 ? 5 
     if (P.blue()) {
       a = cmul(make_double2(a.x, -a.y), chirp[k]);
       b = cmul(make_double2(b.x, -b.y), chirp[j]);
+      if (k == 0) {
+        a = make_double2(fma(double(W), s_mean[0], a.x), fma(double(W), s_mean[1], a.y));
+        b = a;
+      }
     }
     dst[k] = make_double2(0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
     if (two) dst[k + nk] = make_double2(0.5 * (a.y + b.y), 0.5 * (b.x - a.x));
@@ -353,11 +431,22 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_f
   const bool in = cc < cols;
   const int kx = kx0 + cc, mx = (W - kx) % W;
   const bool mirror = in && mx != kx && mx >= nk;  // (-ky, -kx) is another column
+  const bool centre = P.blue() && kx0 == 0;  // block-uniform: the block has frequency 0
+  __shared__ double s_part[T / 64], s_mean[CH];
   double acc[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.0;
   for (int c0 = 0; c0 < 3; c0 += CH) {
     if (c0 > 0) __syncthreads();  // the previous channel's spectra are consumed
+    if (centre) {
+      for (int ch = 0; ch < CH; ++ch) {
+        double sum = 0.0;
+        for (int y = threadIdx.x; y < H; y += T) sum += rows[(size_t(c0 + ch) * H + y) * nk].x;
+        sum = block_sum<T>(sum, s_part);
+        if (threadIdx.x == 0) s_mean[ch] = double(float(sum / double(H)));
+      }
+      __syncthreads();
+    }
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) {
       const double2* src = rows + size_t(c0 + ch) * H * nk + kx;
@@ -366,6 +455,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_f
         double2 a = make_double2(0.0, 0.0);
         if (y < H && in) {
           a = src[size_t(y) * nk];
+          if (centre && cc == 0) a.x -= s_mean[ch];
           if (P.blue()) a = cmul(a, chirp[y]);
         }
         col[y] = a;
@@ -379,7 +469,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_f
       if (ky < H) {
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch) {
-          const double2 f = s_fft[(ch * C + cc) * P.len + ky];
+          double2 f = s_fft[(ch * C + cc) * P.len + ky];
+          if (centre && cc + ky == 0) f.x = fma(double(H), s_mean[ch], f.x);  // (chirp 0 is 1)
           acc[e] = fma(f.x, f.x, fma(f.y, f.y, acc[e]));
         }
       }
@@ -699,26 +790,34 @@ bool plan_stages(FftPlan& P, int n) {
   return n == 1;
 }
 
-// the length of a chirp convolution for n: the least 7-smooth one from 2n - 1 on, at most
-// 8192 for n <= 4096
-int chirp_length(int n) {
-  auto smooth = [](int m) {
-    for (int p : {2, 3, 5, 7})
-      while (m % p == 0) m /= p;
-    return m == 1;
-  };
-  int m = 2 * n - 1;
-  while (!smooth(m)) ++m;
+int pow2_from(int x) {
+  int m = 1;
+  while (m < x) m *= 2;
   return m;
+}
+
+// The stages of the chirp convolution for n go into P: of the 7-smooth lengths from 2 n - 1 on, up
+// to 8 / 7 of it and to the power of two there, the one of fewest stages, each a barrier and
+// a rounding (n = 211: 448 = 8 x 8 x 7 rather than 432 = 4 x 4 x 3 x 3 x 3).
+void plan_chirp(FftPlan& P, int n) {
+  const int least = 2 * n - 1, most = pow2_from(least);  // at most 8192 for n <= 4096
+  int best = most, stages = kMaxStages + 1;
+  for (int m = least; m <= most && (m - least) * 7 <= least; ++m) {
+    int rest = m;
+    for (int p : {2, 3, 5, 7})
+      while (rest % p == 0) rest /= p;
+    if (rest != 1) continue;
+    plan_stages(P, m);
+    if (P.stages < stages) best = m, stages = P.stages;
+  }
+  P.len = best;
+  plan_stages(P, best);
 }
 
 FftPlan make_plan(int n) {
   FftPlan P{};
   P.n = P.len = n;
-  if (!plan_stages(P, n)) {
-    P.len = chirp_length(n);
-    plan_stages(P, P.len);
-  }
+  if (!plan_stages(P, n)) plan_chirp(P, n);
   auto magic = [](uint32_t d) { return d == 1u ? 0u : uint32_t(((uint64_t(1) << 32) + d - 1) / d); };
   uint32_t ns = 1;
   for (int k = 0; k < P.stages; ++k) {
@@ -735,7 +834,7 @@ FftPlan make_plan(int n) {
 // Room for either kind of tables whatever the factors, so that a workspace for an image holds for
 // every smaller one (at most 0.6 MB beyond what the plans take).
 size_t frequency_map_ws_bytes(int H, int W) {
-  auto tables = [](int n) { return align256((2 * size_t(chirp_length(n)) + n) * sizeof(double2)); };
+  auto tables = [](int n) { return align256((2 * size_t(pow2_from(2 * n - 1)) + n) * sizeof(double2)); };
   return align256(size_t(3) * H * (W / 2 + 1) * sizeof(double2)) + tables(W) + tables(H);
 }
 
@@ -762,9 +861,14 @@ hipError_t launch_frequency_map(int n_images, int H, int W, const float* images,
     }
     return hipGetLastError();
   }
-  const int tab_lds = std::max(row.blue() ? row.len : 0, col.blue() ? col.len : 0);
-  GS_LAUNCH("k_fft_tables", k_fft_tables, dim3(2), dim3(kTabThreads), tab_lds * sizeof(double2),
-            st, row, col, row_tab, col_tab);
+  const int most = std::max(row.len, col.len);
+  GS_LAUNCH("k_fft_tables", k_fft_tables, dim3(unsigned((most + kTabThreads - 1) / kTabThreads), 2u),
+            dim3(kTabThreads), 0, st, row, col, row_tab, col_tab);
+  const int chirps = std::max(row.blue() ? row.len : 0, col.blue() ? col.len : 0);
+  if (chirps)
+    GS_LAUNCH("k_chirp_filter", k_chirp_filter,
+              dim3(unsigned((chirps / 2 + kTabThreads / 64) / (kTabThreads / 64)), 2u),
+              dim3(kTabThreads), 0, st, row, col, row_tab, col_tab);
   // columns per block: up to 4 (64-byte pieces of the row spectra) while the
   // three channels' columns fit the register budget and 512 blocks remain, two
   // per CU (four 1200x800 views: 216 us with one column per block, 601 blocks,
