@@ -41,7 +41,12 @@ namespace {
 // a larger prime factor p goes through Bluestein's chirp convolution: two
 // transforms of a 7-smooth length >= 2n - 1 instead of p terms per value.
 constexpr int kMaxStages = 13;   // 2^13 is the longest length
-constexpr int kMaxPrime = 61;
+// The largest prime with a stage of its own, one value at a time, p terms each: lines of up
+// to kMidLine values are faster through a chirp from 41 on (400x610 = 61 x 10, four views
+// 192 and 145 us; 752x1128 = 47 x 16, 24, one 171 and 157; 41: 400x615 157 and 149; 37: 185x259
+// 41 and 34, but 592x888 88 and 97), longer ones, whose chirps fill the LDS, are not (848x1272
+// = 53 x 16, 24: 211 and 235; 944x944 200 and 197).
+constexpr int kMidLine = 800, kMaxPrimeMid = 37, kMaxPrime = 61;
 
 struct FftPlan {
   int n;       // the transform's length
@@ -492,9 +497,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_f
 // lines of up to kDirect values together, kDirectChirp where one of them would need a
 // chirp.  Both ways are chains of latency: the transforms' stages and barriers a fixed
 // one, the sums' one step per term.  Four views, the sums and the transforms: 64x32 35 and
-// 55 us, 80x48 40 and 56, 128x96 63 and 57, 200x132 121 and 66; with chirps 101x67 49 and
-// 98, 150x101 67 and 80, 199x133 121 and 89.
-constexpr int kDirect = 144, kDirectChirp = 256;
+// 55 us, 80x48 40 and 56, 128x96 63 and 57, 200x132 121 and 66; with chirps 211x71 66 and
+// 94, 250x67 71 and 76, 199x134 126 and 106; one view 20 and 31, 21 and 25, 35 and 34.
+constexpr int kDirect = 144, kDirectChirp = 320;
 constexpr int kDirectThreads = 128;
 __global__ __launch_bounds__(256) void k_roots(int W, int H, double2* __restrict__ row_tab,
                                                double2* __restrict__ col_tab) {
@@ -776,8 +781,9 @@ __global__ __launch_bounds__(256) void k_downsample(int64_t total, int H, int W,
 
 namespace {
 
-// appends n's factors to P (false when a prime factor exceeds kMaxPrime)
+// appends n's factors to P (false when a prime factor is too large for a stage)
 bool plan_stages(FftPlan& P, int n) {
+  const int most = n <= kMidLine ? kMaxPrimeMid : kMaxPrime;
   P.stages = 0;
   auto add = [&](int r) { P.radix[P.stages++] = r; };
   int twos = 0;
@@ -785,7 +791,7 @@ bool plan_stages(FftPlan& P, int n) {
   for (; twos >= 5 || twos == 3; twos -= 3) add(8);  // 2^4 as 4 x 4
   for (; twos >= 2; twos -= 2) add(4);
   if (twos) add(2);
-  for (int p = 3; p <= kMaxPrime && n > 1; p += 2)
+  for (int p = 3; p <= most && n > 1; p += 2)
     while (n % p == 0) add(p), n /= p;
   return n == 1;
 }

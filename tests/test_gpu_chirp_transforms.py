@@ -43,3 +43,38 @@ def test_chirps_match_oracle(n, H, W):
     norm = np.sqrt((imgs.astype(np.float64) ** 2).sum(axis=(1, 2, 3))).max()
     # 16 roundings of the 2-norm for each of up to 2 x 13 stages per axis
     assert np.abs(_map(imgs) - ref).max() <= 16 * 52 * 2.0 ** -53 * norm
+
+
+@pytest.mark.parametrize("n,H,W,kernel", [(1, 71, 211, "k_dft_rows"), (2, 131, 189, "k_dft_rows"),
+                                          (2, 131, 190, "k_fft_rows")])
+def test_small_views_are_summed(n, H, W, kernel):
+    """Up to 320 values of both lines together the sums take no longer than the chirps,
+    for one view and for several."""
+    imgs = np.random.default_rng(H + W).uniform(size=(n, 3, H, W)).astype(np.float32)
+    torch.cuda.synchronize()
+    gsmi.gs_profile_enable(True)
+    got = _map(imgs)
+    times = gsmi.gs_profile_collect()
+    gsmi.gs_profile_enable(False)
+    assert kernel in times, times
+    ref = np.fft.ifftshift(O.magnitude_map(imgs.astype(np.float64)))
+    norm = np.sqrt((imgs.astype(np.float64) ** 2).sum(axis=(1, 2, 3))).max()
+    assert np.abs(got - ref).max() <= 16 * 52 * 2.0 ** -53 * norm
+
+
+@pytest.mark.parametrize("n,H,W,sums", [(4, 61, 122, True), (1, 59, 118, True), (1, 37, 111, False),
+                                        (1, 799, 16, False), (1, 901, 16, False)])
+def test_large_stages_match_oracle(n, H, W, sums):
+    """Primes of 41 to 61 have a stage of their own in lines of more than 800 values only:
+    a small view of such lines is summed (four of 61x122 took 102 us through them, 80 before
+    there were transforms, 50 so)."""
+    imgs = np.random.default_rng(H + W).uniform(size=(n, 3, H, W)).astype(np.float32)
+    torch.cuda.synchronize()
+    gsmi.gs_profile_enable(True)
+    got = _map(imgs)
+    times = gsmi.gs_profile_collect()
+    gsmi.gs_profile_enable(False)
+    assert ("k_dft_rows" in times) == sums, times
+    ref = np.fft.ifftshift(O.magnitude_map(imgs.astype(np.float64)))
+    norm = np.sqrt((imgs.astype(np.float64) ** 2).sum(axis=(1, 2, 3))).max()
+    assert np.abs(got - ref).max() <= 16 * 52 * 2.0 ** -53 * norm
