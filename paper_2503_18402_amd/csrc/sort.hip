@@ -989,14 +989,15 @@ __device__ inline bool sort_list_words(uint64_t* list, uint32_t n, uint32_t star
       edge[W + w] = uint64_t(equal);
     }
     __syncthreads();
+    dmin = uint32_t(edge[lane & (W - 1)] >> 32);
+    dmax = uint32_t(edge[lane & (W - 1)]);
+    equal = int(edge[W + (lane & (W - 1))]);
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
-      dmin = min(dmin, uint32_t(edge[i] >> 32));
-      dmax = max(dmax, uint32_t(edge[i]));
+    for (int d = W / 2; d >= 1; d >>= 1) {
+      dmin = min(dmin, uint32_t(__shfl_xor(int(dmin), d, 64)));
+      dmax = max(dmax, uint32_t(__shfl_xor(int(dmax), d, 64)));
+      equal += __shfl_xor(equal, d, 64);
     }
-    equal = lane < W ? int(edge[W + lane]) : 0;
-#pragma unroll
-    for (int d = W / 2; d >= 1; d >>= 1) equal += __shfl_xor(equal, d, 64);
     equal = __builtin_amdgcn_readfirstlane(equal);
     __syncthreads();
   }
