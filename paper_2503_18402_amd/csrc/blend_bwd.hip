@@ -247,11 +247,11 @@ __device__ __forceinline__ bool bwd_entry(BwdPix<TILE>& P, const BwdRec& e, uint
       const Exponent x = exponent_at(r0, r1.x, r1.y, px0 + float((q % GX) * 8),
                                      py0 + float((q / GX) * 8));
       // each compare's lane mask on its own: ANDed on the scalar unit
-      const bool ok0 = PLAIN || x.p2 <= 0.0f, ok1 = x.q >= kLog2AlphaMin, ok2 = pos <= P.last[q];
+      const bool ok0 = falls_off<PLAIN>(x), ok1 = reaches(x, kLog2AlphaMin), ok2 = pos <= P.last[q];
       hit |= (PLAIN ? ~0ull : __ballot(ok0)) & __ballot(ok1) & __ballot(ok2);
       if (__builtin_expect(ok0 & ok1 & ok2, 1)) {
         const float raw = __builtin_amdgcn_exp2f(x.q);
-        const float a = PLAIN ? raw : fminf(kAlphaMax, raw);
+        const float a = alpha_of<PLAIN>(raw);
         const float inv = __builtin_amdgcn_rcpf(1.0f - a);
         const float Ti = P.T[q] * inv;
         const float wgt = a * Ti;
@@ -334,7 +334,7 @@ constexpr int kBwdChunk = 64;
 
 template <int TILE>
 __global__ __launch_bounds__(64) void k_blend_bwd(
-    RViews RV, int n, const char* __restrict__ proj, size_t stride,
+    RViews RV, const char* __restrict__ proj, size_t stride,
     const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
     const float* __restrict__ final_T, const uint32_t* __restrict__ last_contrib,
     const float* __restrict__ dL_dimage, size_t goff_off,
@@ -506,8 +506,8 @@ __global__ __launch_bounds__(64 * NW) void k_blend_bwd_long(
           if (((m >> q) & 1u) == 0u) continue;  // wave-uniform
           const Exponent x = exponent_at(r0, r1.x, r1.y, px0 + float((q % GX) * 8),
                                          py0 + float((q / GX) * 8));
-          if (__builtin_expect((x.p2 <= 0.0f) & (x.q >= kLog2AlphaMin) & (pos <= P.last[q]), 1)) {
-            const float a = fminf(kAlphaMax, __builtin_amdgcn_exp2f(x.q));
+          if (__builtin_expect(falls_off<false>(x) & reaches(x, kLog2AlphaMin) & (pos <= P.last[q]), 1)) {
+            const float a = alpha_of<false>(__builtin_amdgcn_exp2f(x.q));
             const float w = a * Pr[q];
             C0[q] = fmaf(w, r1.z, C0[q]);
             C1[q] = fmaf(w, r1.w, C1[q]);
@@ -1365,8 +1365,8 @@ __global__ __launch_bounds__(1024) void k_zero_pairs(float* __restrict__ p,
 }
 
 template <int TILE>
-void launch_bwd_tile(dim3 grid, const RViews& RV, int n, const char* proj,
-                     size_t stride, const uint32_t* ranges, const uint32_t* vals,
+void launch_bwd_tile(dim3 grid, const RViews& RV, const char* proj, size_t stride,
+                     const uint32_t* ranges, const uint32_t* vals,
                      const float* final_T, const uint32_t* last_contrib, const float* dL,
                      size_t goff, float* pairs, int64_t cap, const float* bg,
                      const uint32_t* order, hipStream_t st) {
@@ -1384,7 +1384,7 @@ void launch_bwd_tile(dim3 grid, const RViews& RV, int n, const char* proj,
     return;
   }
   GS_LAUNCH("k_blend_bwd", HIP_KERNEL_NAME(k_blend_bwd<TILE>), grid,
-            dim3(64), 0, st, RV, n, proj, stride, ranges, vals, final_T,
+            dim3(64), 0, st, RV, proj, stride, ranges, vals, final_T,
             last_contrib, dL, goff, pairs, cap, bg[0], bg[1], bg[2], order);
 }
 
@@ -1422,15 +1422,15 @@ hipError_t bwd_to_planes(const Views& V, int n, const gs_raster_cfg& cfg, const 
     const dim3 grid(unsigned(V.total_tiles));
     switch (cfg.tile) {
       case 8:
-        launch_bwd_tile<8>(grid, RV, n, proj, L.stride, ranges, vals, final_T,
+        launch_bwd_tile<8>(grid, RV, proj, L.stride, ranges, vals, final_T,
                            last_contrib, dL_dimage, goff, pairs, cap, cfg.bg, order, st);
         break;
       case 16:
-        launch_bwd_tile<16>(grid, RV, n, proj, L.stride, ranges, vals, final_T,
+        launch_bwd_tile<16>(grid, RV, proj, L.stride, ranges, vals, final_T,
                             last_contrib, dL_dimage, goff, pairs, cap, cfg.bg, order, st);
         break;
       default:
-        launch_bwd_tile<32>(grid, RV, n, proj, L.stride, ranges, vals, final_T,
+        launch_bwd_tile<32>(grid, RV, proj, L.stride, ranges, vals, final_T,
                             last_contrib, dL_dimage, goff, pairs, cap, cfg.bg, order, st);
         break;
     }

@@ -1,8 +1,8 @@
-// Pieces shared by the forward and backward blend kernels.  The alpha of a
-// (pixel, Gaussian) evaluation is computed by ONE inline function so that the
-// backward replays exactly the forward's float32 decisions (cutoff, clamp,
-// early exit); the library is built without floating-point contraction and
-// every fused multiply-add here is explicit.
+// Pieces shared by the forward and backward blend kernels.  The exponent of a
+// (pixel, Gaussian) evaluation, the tests on it and the clamp are inline functions
+// that every walk uses, so that the backward replays exactly the forward's float32
+// decisions (the early exit it takes from last_contrib); the library is built without
+// floating-point contraction and every fused multiply-add here is explicit.
 #pragma once
 
 #include "gs_internal.hpp"
@@ -72,21 +72,17 @@ __device__ __forceinline__ bool plain_record(const float4 r0, const float C, con
          (d - r0.w * r0.w > 1.0e-4f * d);
 }
 
-// The same with the alpha where the pixel takes the Gaussian (`ok`).
-struct Alpha {
-  float dx, dy, raw, a;
-  bool ok;
-};
-__device__ __forceinline__ Alpha alpha_at(const float4 r0, const float C, const float lo,
-                                          const float px, const float py) {
-  const Exponent e = exponent_at(r0, C, lo, px, py);
-  Alpha r;
-  r.dx = e.dx;
-  r.dy = e.dy;
-  r.ok = (e.p2 <= 0.0f) & (e.q >= kLog2AlphaMin);
-  r.raw = __builtin_amdgcn_exp2f(e.q);
-  r.a = fminf(kAlphaMax, r.raw);
-  return r;
+// The decisions that the backward has to replay as the forward took them: the two tests
+// for whether a pixel takes the Gaussian, and the clamp.  PLAIN: the record is a
+// plain_record, for which the first test holds and the clamp changes nothing.
+template <bool PLAIN>
+__device__ __forceinline__ bool falls_off(const Exponent& x) {
+  return PLAIN || x.p2 <= 0.0f;
+}
+__device__ __forceinline__ bool reaches(const Exponent& x, float least) { return x.q >= least; }
+template <bool PLAIN>
+__device__ __forceinline__ float alpha_of(float raw) {
+  return PLAIN ? raw : fminf(kAlphaMax, raw);
 }
 
 // Workgroups are dealt to the XCDs round-robin (block b runs on XCD b % 8), and each

@@ -86,9 +86,9 @@ struct FwdPix {
 template <bool PLAIN, bool STOP>
 __device__ __forceinline__ void fwd_blend(FwdPix& P, const FwdEnt& e, float px, float py) {
   const Exponent x = exponent_at(e.r0, e.r1.x, e.r1.y, px, py);
-  if (__builtin_expect((PLAIN || x.p2 <= 0.0f) & (x.q >= P.thr), 1)) {
+  if (__builtin_expect(falls_off<PLAIN>(x) & reaches(x, P.thr), 1)) {
     const float raw = __builtin_amdgcn_exp2f(x.q);
-    const float a = PLAIN ? raw : fminf(kAlphaMax, raw);
+    const float a = alpha_of<PLAIN>(raw);
     const float aT = a * P.T;
     // T (1 - alpha), reusing the weight's product where the pixel may stop
     const float Tn = STOP ? P.T - aT : P.T * (1.0f - a);

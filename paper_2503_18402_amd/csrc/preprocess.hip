@@ -55,12 +55,10 @@ struct Gauss3 {
 };
 
 // One view's splat without the colour: the record words, the tile count, and
-// the unit viewing direction for the colour (has_colour: the splat passed the
-// culls that precede the footprint, so a colour is evaluated for it).
+// the unit viewing direction for the colour (evaluated where count > 0).
 struct Splat {
   float4 r0, r1, r2;
   uint32_t count;
-  bool has_colour;
   float dx, dy, dz;
 };
 
@@ -71,7 +69,6 @@ __device__ __forceinline__ Splat splat_geometry(const DevView& cv, const Gauss3&
   P.r1 = P.r0;
   P.r2 = P.r0;
   P.count = 0;
-  P.has_colour = false;
   P.dx = P.dy = P.dz = 0.0f;
   const float mx = G.mx, my = G.my, mz = G.mz;
   // depth: the exact float32 sequence that defines the sort key
@@ -112,7 +109,6 @@ __device__ __forceinline__ Splat splat_geometry(const DevView& cv, const Gauss3&
     k2 = fmaxf(0.0f, 2.0f * logf(255.0f * ov));
   }
   if (!(det > 0.0f && ov >= kAlphaMin)) return P;
-  P.has_colour = true;
   const float idet = 1.0f / det;
   const float ca = c11 * idet, cb = -c01 * idet, cc = c00 * idet;
   // screen mean in double: float32 spacing at 1000+ px (6e-5 px) would otherwise
