@@ -68,8 +68,8 @@ typedef struct {
  * {128, 256, 512} Gaussians staged in LDS per step of the forward blend;
  * bg is the background colour added as T_final * bg.  Binning is
  * result-neutral: the image does not depend on lds_batch, and across tile
- * sizes, or between a launch of fewer than 2048 tiles (which splits long
- * lists across waves) and one of more, it changes only by float32 rounding.
+ * sizes, or between a launch of fewer than 2048 tiles (which cuts long
+ * lists into chunks) and one of more, it changes only by float32 rounding.
  *
  * Mip-Splatting's filters (the backbone family with an anti-aliased primitive
  * representation that the paper equips, Sec. 5 and the supplementary):

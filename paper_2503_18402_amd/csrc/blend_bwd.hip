@@ -326,10 +326,11 @@ __device__ __forceinline__ void bwd_walk(BwdPix<TILE>& P, WaveSum<ENTS>& S, cons
 // in registers per entry, 369 under the mask, with the sums in batches and the
 // entries that any pixel may have blended found by one ballot a chunk (12 us less than a
 // mask read and tested per entry) (16 views of mixed sizes 2730, now 2040; tiles of
-// 8: 610, now 512; of 32: 957, 635).  Measured with cheaper sums and not taken: chunks of 32
+// 8: 610, now 512; of 32: 957, 635).  Measured and not taken, all with the sums in the other
+// order above, whose 348 us they are to be held against: chunks of 32
 // and 48 entries 375 to 400, the sums through LDS alone 486, through the f32
 // matrix instruction (which shares the vector units) 548, seven waves per SIMD by
-// spilling a register 361, sums in batches of three 359 (each against 348).
+// spilling a register 361, sums in batches of three 359.
 constexpr int kBwdChunk = 64;
 
 template <int TILE>

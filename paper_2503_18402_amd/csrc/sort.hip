@@ -130,7 +130,8 @@ __device__ __forceinline__ Item load_item(const Items& S, int v, int64_t g) {
 // a footprint of thousands of tiles then keeps its wave, and at the end the whole
 // launch, for one round trip per 64 pairs: 16 views of mixed sizes of 1M Gaussians
 // stored by place, whose fullest block has 78 thousand pairs and its fullest wave 11
-// thousand, counted in 445 us and placed in 515 so, now in 306 and 442.)  Every thread of the block
+// thousand, counted in 445 us and placed in 515 so; dealt to the block 306 and 442, with
+// the launch's order of views and 1024-item blocks 199 and 234.)  Every thread of the block
 // must call it.  Returns the items' pair count.
 constexpr int kPairs = 4;
 
@@ -541,7 +542,7 @@ __device__ inline uint64_t wave_incl_scan64(uint64_t x) {
 }
 
 // Bound by the latency of one block's steps: a wave takes 64 ITEMS tiles in a row, 64 a
-// load (ITEMS 2, or 8 for more than 2 kTS tiles), and a step's loads run under the one
+// load (ITEMS 2, or 4 for more than 2 kTS tiles), and a step's loads run under the one
 // before: 8 us at 950 tiles, 37 at 35768, 80 at 81600 (15, 56 and 138 with eight
 // consecutive tiles a thread, one load per 64 cache lines).
 template <int ITEMS>
